@@ -255,8 +255,10 @@ hipError_t launch_compact(HopView hv, const TypeStatic *ts, int32_t n_types,
 // vertex (zero between uses), cand[t] and prefix[t] the candidates and the
 // exclusive prefix of their importance, scan tiles cand_tile[t] ..
 // cand_tile[t+1] of the candidate scan, and draws[t] the draws of the hop.
-// Values per tile of the layer-wise scans (256 threads, two values each).
+// Candidates per tile of the layer-wise scans (256 threads, two values each).
 constexpr int64_t kLayerTile = 512;
+// In-edges per tile of the layer-wise edge passes (256 threads, eight each).
+constexpr int64_t kEdgeTile = 2048;
 
 struct LayerArgs {
   HopView hv, next;
@@ -270,7 +272,8 @@ struct LayerArgs {
   // in-edges are positions off[p] .. off[p+1]-1, CSC slots plo[p] ..); they
   // are read from the CSC where they are needed, never written out
   int64_t n_all;
-  int64_t *tile_pair;  // [n_keep_tiles + 1]: the last pair with off <= tile * kLayerTile
+  int64_t n_edge_tiles;
+  int64_t *tile_pair;  // [n_edge_tiles + 1]: the pair of position tile * kEdgeTile
   // per node type, in a device table of the hop (see LayerTable)
   uint64_t *const *wt;        // [T] importance of every vertex of the type
   int64_t *const *cand;       // [T] the type's candidates, ascending
@@ -281,8 +284,8 @@ struct LayerArgs {
   int64_t cand_tiles, draw_threads;  // cand_tile[T], draw_base[T] (host copies)
   int64_t *tile_sum;   // per scan tile
   int64_t *tile_pre;   // per scan tile: exclusive scan over all tiles, then the grand total
-  int64_t n_keep_tiles;
-  int64_t *pos;        // [n_all + 1] exclusive scan of the kept flags
+  uint64_t *keep_bits;  // [n_edge_tiles * kEdgeTile / 64] kept flags
+  int32_t *keep_pre;    // per word: kept edges before it within its tile
   int64_t *out_eid;
   int32_t *out_src_local, *out_dst_local;
   int64_t *out_indptr;  // [P + R]
@@ -301,7 +304,7 @@ inline size_t layer_table_bytes(int32_t T) {
   return sizeof(int64_t) * (3 * size_t(T) + 2 * (size_t(T) + 1) + (size_t(T) + 1) / 2);
 }
 
-// The first pair of every kLayerTile-position tile of the in-edges (tile_pair),
+// The first pair of every kEdgeTile-position tile of the in-edges (tile_pair),
 // then the importance of every candidate: for each in-edge u -> v of the
 // frontier whose source is not in the frontier, u is marked reached and
 // wt[type(u)][u] += floor(2^32 / deg(v)^2).
@@ -312,8 +315,8 @@ hipError_t launch_lw_weights(const LayerArgs &A, hipStream_t stream);
 hipError_t launch_lw_prefix(const LayerArgs &A, hipStream_t stream);
 // The draws of every node type: marks the drawn candidates reached.
 hipError_t launch_lw_draw(const LayerArgs &A, hipStream_t stream);
-// The kept in-edges (source in the next frontier): scan of their flags,
-// emitted in order; then the block CSC, the kept edge starts per etype
+// The kept in-edges (source in the next frontier): their flags, a scan of the
+// tiles' counts, the kept ones emitted in order; then the block CSC, the kept edge starts per etype
 // (small slots after ebase) and the next hop's plan.
 hipError_t launch_lw_keep(const LayerArgs &A, hipStream_t stream);
 

@@ -8,13 +8,13 @@
 // One hop, after the counting pass has numbered every in-edge of the frontier
 // (fanout -1: pair p's in-edges are positions off[p] .. off[p+1]-1); no
 // sampler runs, and the edges are read from the CSC where needed:
-//  1. k_lw_tile_pairs, k_lw_weights : the first pair of every 512-position
+//  1. k_lw_tile_pairs, k_lw_weights : the first pair of every 2048-position
 //                    tile; then the importance of every candidate (a source
 //                    not in the frontier, which is marked reached): sum of
 //                    floor(2^32 / deg(v)^2) over its edges into the frontier,
-//                    64-bit atomics (exact in any order), blocks over tiles of
-//                    positions whose etypes and pairs are staged in LDS once
-//                    per tile (as in the kept-edge scans);
+//                    64-bit atomics (exact in any order), a block per tile of
+//                    positions whose etypes and pairs are staged in LDS (as in
+//                    the kept-edge passes);
 //  2. compaction   : (collect mode) the candidates of each type, ascending;
 //  3. k_lw_scan_*  : exclusive prefix of their importance per type
 //                    (reduce-then-scan over 512-candidate tiles);
@@ -23,8 +23,9 @@
 //                    candidate whose interval [prefix, prefix + weight) holds
 //                    r (binary search);
 //  5. compaction   : the drawn vertices join the frontier (ascending);
-//  6. k_lw_scan_*  : the kept in-edges (source in the next frontier) by an
-//                    exclusive scan of their flags, emitted in order;
+//  6. k_lw_keep_*  : the kept in-edges (source in the next frontier): one bit
+//                    per in-edge, a scan of the tiles' counts, and the kept
+//                    ones emitted in order;
 //  7. k_lw_indptr  : the block CSC, the kept edge starts per etype, and the
 //                    next hop's plan.
 #include "hg_device.hpp"
@@ -99,19 +100,20 @@ struct TileSegs {
 };
 
 // kKind 0: per_seg = importance array of the source type; 1: source map.
+// pa, pb: the pair of the range's first position and a pair not before that of
+// its last one (whose etypes bound the range's; two loads instead of two
+// searches over the etype starts).
 template <int kKind>
-__device__ void tile_segs_load(const LayerArgs &A, int64_t j0, int64_t j1, TileSegs &T) {
+__device__ void tile_segs_load(const LayerArgs &A, int64_t pa, int64_t pb, TileSegs &T) {
   const int64_t *ebase = ebase_of(A);
+  const int a = A.pa.pet[pa], b = A.pa.pet[pb];
+  const int n = b - a + 1 <= kTileSegs ? b - a + 1 : 0;
   if (threadIdx.x == 0) {
-    const int a = find_segment(ebase, A.n_etypes, j0);
-    const int b = find_segment(ebase, A.n_etypes, j1 - 1);
     T.e0 = a;
-    T.n = b - a + 1 <= kTileSegs ? b - a + 1 : 0;
+    T.n = n;
   }
-  __syncthreads();
-  const int n = T.n;
   if (int(threadIdx.x) <= n && n > 0) {
-    const int e = T.e0 + int(threadIdx.x);
+    const int e = a + int(threadIdx.x);
     T.start[threadIdx.x] = ebase[e];
     if (int(threadIdx.x) < n) {
       const EtypeStatic &E = A.es[e];
@@ -125,7 +127,6 @@ __device__ void tile_segs_load(const LayerArgs &A, int64_t j0, int64_t j1, TileS
       T.pair_base[threadIdx.x] = A.hv.pair_base[e];
     }
   }
-  __syncthreads();
 }
 
 // Segment of position j in the block's table, from a hint not above it (the
@@ -143,66 +144,71 @@ struct SegView {
   uint8_t *reached;
   int64_t pair_base;
 };
+// The etype of position j: its segment of the block's table, or without a
+// table the etype itself.
+__device__ __forceinline__ int seg_index(const LayerArgs &A, const TileSegs &T, int &s,
+                                         int64_t j) {
+  if (T.n > 0) return s = tile_seg(T, s, j);
+  return find_segment(ebase_of(A), A.n_etypes, j);
+}
 template <int kKind>
-__device__ __forceinline__ SegView seg_view(const LayerArgs &A, const TileSegs &T, int &s,
-                                            int64_t j) {
-  if (T.n > 0) {
-    s = tile_seg(T, s, j);
-    return SegView{T.fbits[s], T.per_seg[s], T.indices[s], T.reached[s], T.pair_base[s]};
-  }
-  const int e = find_segment(ebase_of(A), A.n_etypes, j);
-  const EtypeStatic &E = A.es[e];
+__device__ __forceinline__ SegView seg_view(const LayerArgs &A, const TileSegs &T, int x) {
+  if (T.n > 0)
+    return SegView{T.fbits[x], T.per_seg[x], T.indices[x], T.reached[x], T.pair_base[x]};
+  const EtypeStatic &E = A.es[x];
   return SegView{A.ts[E.src_type].fbits,
                  kKind == 0 ? static_cast<void *>(A.wt[E.src_type]) : static_cast<void *>(E.src_map),
-                 E.indices, E.src_reached, A.hv.pair_base[e]};
+                 E.indices, E.src_reached, A.hv.pair_base[x]};
 }
 
-// tile_pair[t] = the last pair p with off[p] <= t * kLwTile, for every tile t
-// of positions; tile_pair[n_tiles] = the last pair.  Each non-empty pair writes
+// tile_pair[t] = the pair of position t * kEdgeTile, for every tile t of
+// positions; tile_pair[n_tiles] = the last pair.  Each non-empty pair writes
 // the tiles that start inside it.
 __global__ __launch_bounds__(256) void k_lw_tile_pairs(LayerArgs A) {
   for (int64_t p = gs_start(); p < A.n_pairs; p += gs_step()) {
     const int64_t lo = A.pa.off[p], hi = A.pa.off[p + 1];
-    for (int64_t t = (lo + kLwTile - 1) / kLwTile; t * kLwTile < hi; ++t) A.tile_pair[t] = p;
+    for (int64_t t = (lo + kEdgeTile - 1) / kEdgeTile; t * kEdgeTile < hi; ++t)
+      A.tile_pair[t] = p;
   }
-  if (gs_start() == 0) A.tile_pair[A.n_keep_tiles] = A.n_pairs - 1;
+  if (gs_start() == 0) A.tile_pair[A.n_edge_tiles] = A.n_pairs - 1;
 }
 
-// The pairs of a block's positions [j0, j1) in LDS: from tile_pair of the tile
-// holding j0 to tile_pair of the tile after j1 - 1 (which may hold one pair
-// past j1).  More than kTilePairs pairs (runs of empty pairs) leave n = 0, and
-// each position then searches the pair offsets.
-constexpr int kTilePairs = 1024;
-template <int N>
+// The pairs of a tile of positions in LDS: from tile_pair of the tile to
+// tile_pair of the next one (which may hold one pair past the tile).  More than
+// kTilePairs pairs (runs of empty pairs) leave n = 0, and each position then
+// searches the pair offsets.  `w`: the importance that each in-edge of the pair
+// adds to its source (kKind 0), computed once per pair instead of per edge.
+constexpr int kTilePairs = 512;
 struct TilePairs {
-  int64_t off[N], plo[N], deg[N];
+  int64_t off[kTilePairs], plo[kTilePairs];
+  uint64_t w[kTilePairs];
 };
 struct PairRange {
-  int64_t p0;
+  int64_t p0, p1;
   int n;
 };
-template <int N>
-__device__ PairRange tile_pairs_load(const LayerArgs &A, int64_t j0, int64_t j1,
-                                     TilePairs<N> &Q) {
-  const int64_t pa = A.tile_pair[j0 / kLwTile];
-  const int64_t pb = A.tile_pair[(j1 - 1) / kLwTile + 1];
-  const int n = pb - pa + 1 <= N ? int(pb - pa + 1) : 0;
+template <int kKind>
+__device__ void tile_tables(const LayerArgs &A, int64_t tile, TileSegs &T, TilePairs &Q,
+                            PairRange &R) {
+  const int64_t pa = A.tile_pair[tile], pb = A.tile_pair[tile + 1];
+  const int n = pb - pa + 1 <= kTilePairs ? int(pb - pa + 1) : 0;
   for (int k = threadIdx.x; k < n; k += blockDim.x) {
-    Q.off[k] = A.pa.off[pa + k];
-    Q.plo[k] = A.pa.plo[pa + k];
-    Q.deg[k] = A.pa.pdeg[pa + k];
+    const int64_t lo = A.pa.off[pa + k];
+    Q.off[k] = lo;
+    // (an empty pair has no in-edge position: nothing is read of it)
+    const bool any = A.pa.off[pa + k + 1] > lo;
+    Q.plo[k] = any ? A.pa.plo[pa + k] : 0;
+    if (kKind == 0) Q.w[k] = any ? layer_weight(A.pa.pdeg[pa + k]) : 0;
   }
+  tile_segs_load<kKind>(A, pa, pb, T);
   __syncthreads();
-  return PairRange{pa, n};
+  R = PairRange{pa, pb, n};
 }
 
-// Position j: its pair, its CSC slot and the pair's in-degree.
-struct EdgeAt {
-  int64_t p, slot, deg;
-};
-template <int N>
-__device__ __forceinline__ EdgeAt edge_at(const LayerArgs &A, const TilePairs<N> &Q,
-                                          const PairRange &R, int64_t j) {
+// Position j: its pair (an index into the block's table, or the pair itself)
+// and CSC slot.
+__device__ __forceinline__ int64_t pair_at(const LayerArgs &A, const TilePairs &Q,
+                                           const PairRange &R, int64_t j) {
   if (R.n > 0) {
     int lo = 0, hi = R.n;  // Q.off[lo] <= j
     while (hi - lo > 1) {
@@ -212,9 +218,9 @@ __device__ __forceinline__ EdgeAt edge_at(const LayerArgs &A, const TilePairs<N>
       else
         hi = mid;
     }
-    return EdgeAt{R.p0 + lo, Q.plo[lo] + (j - Q.off[lo]), Q.deg[lo]};
+    return lo;
   }
-  int64_t lo = 0, hi = A.n_pairs;
+  int64_t lo = R.p0, hi = R.p1 + 1;
   while (hi - lo > 1) {
     const int64_t mid = (lo + hi) >> 1;
     if (A.pa.off[mid] <= j)
@@ -222,119 +228,200 @@ __device__ __forceinline__ EdgeAt edge_at(const LayerArgs &A, const TilePairs<N>
     else
       hi = mid;
   }
-  return EdgeAt{lo, A.pa.plo[lo] + (j - A.pa.off[lo]), A.pa.pdeg[lo]};
+  return lo;
+}
+__device__ __forceinline__ int64_t slot_at(const LayerArgs &A, const TilePairs &Q,
+                                           const PairRange &R, int64_t q, int64_t j) {
+  return R.n > 0 ? Q.plo[q] + (j - Q.off[q]) : A.pa.plo[q] + (j - A.pa.off[q]);
 }
 
-// Blocks of 256 threads take tiles of kLwWeightTile positions (whole scan
-// tiles), each thread every 256th position of the tile.
-constexpr int kLwWeightItems = 8;
-constexpr int64_t kLwWeightTile = 256 * kLwWeightItems;
-static_assert(kLwWeightTile % kLwTile == 0, "weight tiles are whole scan tiles");
+// Blocks of 256 threads take tiles of kEdgeTile positions, each thread every
+// 256th position of the tile; the sources of all its positions are loaded
+// before any is used, then their frontier words.
+constexpr int kEdgeItems = int(kEdgeTile / 256);
 
-__global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
-  __shared__ TileSegs T;
-  __shared__ TilePairs<kTilePairs> Q;
-  const int64_t n_tiles = (A.n_all + kLwWeightTile - 1) / kLwWeightTile;
-  for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const int64_t j0 = tile * kLwWeightTile;
-    const int64_t j1 = j0 + kLwWeightTile < A.n_all ? j0 + kLwWeightTile : A.n_all;
-    tile_segs_load<0>(A, j0, j1, T);
-    const PairRange R = tile_pairs_load(A, j0, j1, Q);
-    int s = 0;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += 256) {
-      const SegView v = seg_view<0>(A, T, s, j);
-      const EdgeAt x = edge_at(A, Q, R, j);
-      const int64_t u = v.indices[x.slot];
-      if (in_frontier(v.fbits, u)) continue;
-      v.reached[u] = 1;  // a candidate
-      const uint64_t w = layer_weight(x.deg);
-      if (w)
-        atomicAdd(reinterpret_cast<unsigned long long *>(static_cast<uint64_t *>(v.per_seg) + u),
-                  (unsigned long long)w);
+// The source of each of a thread's positions (-1 past the end), and what the
+// position needs of its etype and pair.
+struct EdgeItems {
+  int seg[kEdgeItems];
+  int64_t pair[kEdgeItems];
+  int64_t u[kEdgeItems];
+};
+template <int kKind>
+__device__ __forceinline__ void edge_items(const LayerArgs &A, const TileSegs &T,
+                                           const TilePairs &Q, const PairRange &R, int64_t tile,
+                                           EdgeItems &I) {
+  int s = 0;
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    const int64_t j = tile * kEdgeTile + k * 256 + threadIdx.x;
+    I.u[k] = -1;
+    I.seg[k] = 0;
+    I.pair[k] = 0;
+    if (j < A.n_all) {
+      I.seg[k] = seg_index(A, T, s, j);
+      I.pair[k] = pair_at(A, Q, R, j);
+      const int64_t *ix = T.n > 0 ? T.indices[I.seg[k]] : A.es[I.seg[k]].indices;
+      I.u[k] = load_global(ix + slot_at(A, Q, R, I.pair[k], j));
     }
-    __syncthreads();  // T and Q are rebuilt for the next tile
   }
 }
 
-// ---- reduce-then-scan over tiles of kLwTile values --------------------------
-// kind 0: the candidates' importance, one segment per node type (tiles
-//         cand_tile[t] .. cand_tile[t+1]; the type's candidates are counted in
-//         small[kSlotNew + t] by the collect compaction);
-// kind 1: the kept flags of the emitted edges, one segment.
-template <int kKind>
+__global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
+  __shared__ TileSegs T;
+  __shared__ TilePairs Q;
+  const int64_t tile = blockIdx.x;
+  PairRange R;
+  tile_tables<0>(A, tile, T, Q, R);
+  EdgeItems I;
+  edge_items<0>(A, T, Q, R, tile, I);
+  uint32_t f[kEdgeItems];
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    const uint32_t *fb = T.n > 0 ? T.fbits[I.seg[k]] : A.ts[A.es[I.seg[k]].src_type].fbits;
+    f[k] = I.u[k] >= 0 ? load_global(fb + (I.u[k] >> 5)) : ~0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    const int64_t u = I.u[k];
+    if (u < 0 || ((f[k] >> (u & 31)) & 1u)) continue;
+    const SegView v = seg_view<0>(A, T, I.seg[k]);
+    v.reached[u] = 1;  // a candidate
+    const uint64_t w = R.n > 0 ? Q.w[I.pair[k]] : layer_weight(A.pa.pdeg[I.pair[k]]);
+    if (w)
+      atomicAdd(reinterpret_cast<unsigned long long *>(static_cast<uint64_t *>(v.per_seg) + u),
+                (unsigned long long)w);
+  }
+}
+
+// ---- the kept in-edges -------------------------------------------------------
+// A kept in-edge has its source in the next frontier.  Few are (a hop keeps
+// some thousands of millions of in-edges), so a first pass leaves one bit per
+// position (keep_bits, a word per 64 positions), each word's kept edges before
+// it within its tile (keep_pre) and the tile's count; after a scan of the tile
+// counts only the set bits are looked at again, and the kept edges before any
+// position are tile_pre + keep_pre + a population count.  The flags pass is
+// bound by its reads (8 B a position and a frontier word); the academic graph's
+// second hop in bundles of 16 (44M in-edges, 0.3M kept) takes 243 us for the
+// flags, 18 for the scan and 43 for the kept edges, where a reduce and an apply
+// pass that both read every source and wrote a prefix for every position took
+// 690 with their scan.  Ordering the blocks per XCD changed none of them.
+constexpr int kKeepWords = int(kEdgeTile / 64);  // words per tile
+
+__global__ __launch_bounds__(256) void k_lw_keep_flags(LayerArgs A) {
+  __shared__ TileSegs T;
+  __shared__ TilePairs Q;
+  __shared__ int32_t s_cnt[kKeepWords];
+  const int64_t tile = blockIdx.x;
+  PairRange R;
+  tile_tables<1>(A, tile, T, Q, R);
+  EdgeItems I;
+  edge_items<1>(A, T, Q, R, tile, I);
+  const int wave = int(threadIdx.x) / kWave;
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    const uint32_t *fb = T.n > 0 ? T.fbits[I.seg[k]] : A.ts[A.es[I.seg[k]].src_type].fbits;
+    const uint32_t f = I.u[k] >= 0 ? load_global(fb + (I.u[k] >> 5)) : 0u;
+    const uint64_t bal = __ballot((f >> (I.u[k] & 31)) & 1u);
+    if (lane_id() == 0) {
+      const int w = k * 4 + wave;
+      s_cnt[w] = __popcll(bal);
+      A.keep_bits[tile * kKeepWords + w] = bal;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x < kKeepWords) {
+    int inc = s_cnt[threadIdx.x];
+#pragma unroll
+    for (int d = 1; d < kKeepWords; d <<= 1) {
+      const int o = __shfl_up(inc, d, kKeepWords);
+      if (int(threadIdx.x) >= d) inc += o;
+    }
+    A.keep_pre[tile * kKeepWords + threadIdx.x] = inc - s_cnt[threadIdx.x];
+    if (threadIdx.x == kKeepWords - 1) A.tile_sum[tile] = inc;
+  }
+}
+
+// Kept edges before position i (i <= n_all).
+__device__ __forceinline__ int64_t kept_before(const LayerArgs &A, int64_t i) {
+  if (A.n_all <= 0) return 0;
+  if (i >= A.n_all) return A.tile_pre[A.n_edge_tiles];
+  const int64_t w = i >> 6;
+  return A.tile_pre[i / kEdgeTile] + A.keep_pre[w] +
+         __popcll(A.keep_bits[w] & ((uint64_t(1) << (i & 63)) - 1));
+}
+
+// Bit position of the k-th (from 0) set bit of m, which has more than k.
+__device__ __forceinline__ int select_bit(uint64_t m, int k) {
+  int pos = 0;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const int c = __popcll((m >> pos) & ((uint64_t(1) << d) - 1));
+    if (c <= k) {
+      k -= c;
+      pos += d;
+    }
+  }
+  return pos;
+}
+
+// A block per tile with kept edges: thread x writes the tile's kept edges x,
+// x + 256, ...
+__global__ __launch_bounds__(256) void k_lw_keep_emit(LayerArgs A) {
+  __shared__ TileSegs T;
+  __shared__ TilePairs Q;
+  __shared__ int32_t s_pre[kKeepWords];
+  __shared__ uint64_t s_bits[kKeepWords];
+  const int64_t tile = blockIdx.x;
+  const int64_t first = A.tile_pre[tile];
+  const int n = int(A.tile_pre[tile + 1] - first);
+  if (n == 0) return;
+  if (threadIdx.x < kKeepWords) {
+    s_pre[threadIdx.x] = A.keep_pre[tile * kKeepWords + threadIdx.x];
+    s_bits[threadIdx.x] = A.keep_bits[tile * kKeepWords + threadIdx.x];
+  }
+  PairRange R;
+  tile_tables<1>(A, tile, T, Q, R);  // also the barrier
+  int s = 0;
+  for (int x = threadIdx.x; x < n; x += 256) {
+    int w = 0;  // the last word with s_pre <= x
+#pragma unroll
+    for (int d = kKeepWords / 2; d >= 1; d >>= 1)
+      if (s_pre[w + d] <= x) w += d;
+    const int64_t j = tile * kEdgeTile + w * 64 + select_bit(s_bits[w], x - s_pre[w]);
+    const int sg = seg_index(A, T, s, j);
+    const int64_t q = pair_at(A, Q, R, j);
+    const int64_t slot = slot_at(A, Q, R, q, j);
+    const SegView v = seg_view<1>(A, T, sg);
+    A.out_eid[first + x] = slot;
+    A.out_dst_local[first + x] = int32_t((R.n > 0 ? R.p0 + q : q) - v.pair_base);
+    A.out_src_local[first + x] = static_cast<const int32_t *>(v.per_seg)[v.indices[slot]];
+  }
+}
+
+// ---- reduce-then-scan over tiles of kLwTile candidates -----------------------
+// The candidates' importance, one segment per node type (tiles cand_tile[t] ..
+// cand_tile[t+1]; the type's candidates are counted in small[kSlotNew + t] by
+// the collect compaction).
 struct ScanSeg {
   int seg;
   int64_t first_tile, n;
 };
 
-template <int kKind>
-__device__ __forceinline__ ScanSeg<kKind> seg_of(const LayerArgs &A, int64_t tile) {
-  if (kKind == 0) {
-    const int t = find_segment(A.cand_tile, A.n_types, tile);
-    return ScanSeg<kKind>{t, A.cand_tile[t], A.small[kSlotNew + t]};
-  }
-  return ScanSeg<kKind>{0, 0, A.n_all};
+__device__ __forceinline__ ScanSeg seg_of(const LayerArgs &A, int64_t tile) {
+  const int t = find_segment(A.cand_tile, A.n_types, tile);
+  return ScanSeg{t, A.cand_tile[t], A.small[kSlotNew + t]};
 }
 
-// Position i of a scan: its value (kind 0: the candidate's importance; kind 1:
-// whether the in-edge's source is in the next frontier) and, for kind 1, what
-// the apply pass writes of a kept edge.
-struct ScanItem {
-  int64_t v;
-  int64_t slot, dst, u;  // kind 1: CSC slot (edge ID), destination local ID, source
-  const int32_t *src_map;
-};
-
-// The pair table of a scan tile: kind 1 only.
-template <int kKind>
-using ScanPairs = TilePairs<kKind == 1 ? kTilePairs : 1>;
-
-template <int kKind>
-__device__ __forceinline__ ScanItem scan_item(const LayerArgs &A, const ScanSeg<kKind> &S,
-                                              const TileSegs &T, const ScanPairs<kKind> &Q,
-                                              const PairRange &R, int &s, int64_t i) {
-  ScanItem it{0, 0, 0, 0, nullptr};
-  if (i >= S.n) return it;
-  if (kKind == 0) {
-    it.v = int64_t(A.wt[S.seg][A.cand[S.seg][i]]);
-    return it;
-  }
-  const SegView sv = seg_view<1>(A, T, s, i);
-  const EdgeAt x = edge_at(A, Q, R, i);
-  it.u = sv.indices[x.slot];
-  it.v = in_frontier(sv.fbits, it.u) ? 1 : 0;
-  it.slot = x.slot;
-  it.dst = x.p - sv.pair_base;
-  it.src_map = static_cast<const int32_t *>(sv.per_seg);
-  return it;
-}
-
-// The block's etype and pair tables for a kind-1 tile.
-template <int kKind>
-__device__ __forceinline__ PairRange scan_tables(const LayerArgs &A, int64_t tile, TileSegs &T,
-                                                 ScanPairs<kKind> &Q) {
-  if (kKind == 1) {
-    const int64_t j0 = tile * kLwTile;
-    const int64_t j1 = j0 + kLwTile < A.n_all ? j0 + kLwTile : A.n_all;
-    tile_segs_load<1>(A, j0, j1, T);
-    return tile_pairs_load(A, j0, j1, Q);
-  }
-  return PairRange{0, 0};
-}
-
-template <int kKind>
 __global__ __launch_bounds__(kLwThreads) void k_lw_scan_reduce(LayerArgs A) {
   __shared__ int64_t lds[8];
-  __shared__ TileSegs T;
-  __shared__ ScanPairs<kKind> Q;
   const int64_t tile = blockIdx.x;
-  const PairRange R = scan_tables<kKind>(A, tile, T, Q);
-  const ScanSeg<kKind> S = seg_of<kKind>(A, tile);
+  const ScanSeg S = seg_of(A, tile);
   const int64_t i0 = (tile - S.first_tile) * kLwTile + threadIdx.x * kLwItems;
   int64_t v = 0;
-  int s = 0;
 #pragma unroll
-  for (int k = 0; k < kLwItems; ++k) v += scan_item<kKind>(A, S, T, Q, R, s, i0 + k).v;
+  for (int k = 0; k < kLwItems; ++k)
+    if (i0 + k < S.n) v += int64_t(A.wt[S.seg][A.cand[S.seg][i0 + k]]);
   int64_t total;
   block_excl_scan_256(v, lds, &total);
   if (threadIdx.x == 0) A.tile_sum[tile] = total;
@@ -384,47 +471,31 @@ __global__ __launch_bounds__(kLwScanThreads) void k_lw_scan_tiles(int64_t *tile_
   if (threadIdx.x == 0) tile_pre[n_tiles] = carry;
 }
 
-// Each tile's values get their exclusive prefix within the segment.
-template <int kKind>
+// Each candidate gets the exclusive prefix of its importance within its type.
 __global__ __launch_bounds__(kLwThreads) void k_lw_scan_apply(LayerArgs A) {
   __shared__ int64_t lds[8];
-  __shared__ TileSegs T;
-  __shared__ ScanPairs<kKind> Q;
   const int64_t tile = blockIdx.x;
-  const PairRange R = scan_tables<kKind>(A, tile, T, Q);
-  const ScanSeg<kKind> S = seg_of<kKind>(A, tile);
+  const ScanSeg S = seg_of(A, tile);
   const int64_t i0 = (tile - S.first_tile) * kLwTile + threadIdx.x * kLwItems;
-  ScanItem it[kLwItems];
+  int64_t c[kLwItems], v[kLwItems];
   int64_t sum = 0;
-  int s = 0;
 #pragma unroll
   for (int k = 0; k < kLwItems; ++k) {
-    it[k] = scan_item<kKind>(A, S, T, Q, R, s, i0 + k);
-    sum += it[k].v;
+    c[k] = i0 + k < S.n ? A.cand[S.seg][i0 + k] : -1;
+    v[k] = c[k] >= 0 ? int64_t(A.wt[S.seg][c[k]]) : 0;
+    sum += v[k];
   }
   int64_t total;
   int64_t pre = block_excl_scan_256(sum, lds, &total) +
                 (A.tile_pre[tile] - A.tile_pre[S.first_tile]);
 #pragma unroll
   for (int k = 0; k < kLwItems; ++k) {
-    const int64_t i = i0 + k;
-    if (i < S.n) {
-      if (kKind == 0) {
-        A.prefix[S.seg][i] = uint64_t(pre);
-        A.wt[S.seg][A.cand[S.seg][i]] = 0;  // clean for the next hop and call
-      } else {
-        A.pos[i] = pre;
-        if (it[k].v) {
-          A.out_eid[pre] = it[k].slot;
-          A.out_dst_local[pre] = int32_t(it[k].dst);
-          A.out_src_local[pre] = it[k].src_map[it[k].u];
-        }
-      }
+    if (c[k] >= 0) {
+      A.prefix[S.seg][i0 + k] = uint64_t(pre);
+      A.wt[S.seg][c[k]] = 0;  // clean for the next hop and call
     }
-    pre += it[k].v;
+    pre += v[k];
   }
-  if (kKind == 1 && tile == int64_t(gridDim.x) - 1 && threadIdx.x == kLwThreads - 1)
-    A.pos[A.n_all] = pre;  // the last thread of the last tile ends past n_all
 }
 
 // Draws: thread x of type t's range draw_base[t] .. draw_base[t+1] makes draw
@@ -471,8 +542,7 @@ __global__ __launch_bounds__(256) void k_lw_draw(LayerArgs A) {
 __global__ __launch_bounds__(256) void k_lw_indptr(LayerArgs A) {
   const int64_t *ebase = ebase_of(A);
   const int64_t *pb = A.hv.pair_base;
-  // kept edges before emitted edge i (no edges: no scan ran, and none are kept)
-  auto pos = [&](int64_t i) { return A.n_all > 0 ? A.pos[i] : int64_t(0); };
+  auto pos = [&](int64_t i) { return kept_before(A, i); };
   if (blockIdx.x == 0) {
     int64_t *kept = kept_base_of(A);
     for (int e = threadIdx.x; e <= A.n_etypes; e += blockDim.x) {
@@ -492,18 +562,18 @@ __global__ __launch_bounds__(256) void k_lw_indptr(LayerArgs A) {
 hipError_t launch_lw_weights(const LayerArgs &A, hipStream_t stream) {
   if (A.n_all <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_lw_tile_pairs, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);
-  hipLaunchKernelGGL(k_lw_weights, dim3(grid_for(A.n_all, kLwWeightTile)), dim3(256), 0, stream,
-                     A);
+  hipLaunchKernelGGL(k_lw_weights, dim3(unsigned(A.n_edge_tiles)), dim3(256), 0,
+                     stream, A);
   return hipGetLastError();
 }
 
 hipError_t launch_lw_prefix(const LayerArgs &A, hipStream_t stream) {
   const int64_t tiles = A.cand_tiles;
   if (tiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_lw_scan_reduce<0>, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream, A);
+  hipLaunchKernelGGL(k_lw_scan_reduce, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream, A);
   hipLaunchKernelGGL(k_lw_scan_tiles, dim3(1), dim3(kLwScanThreads), 0, stream, A.tile_sum,
                      A.tile_pre, tiles);
-  hipLaunchKernelGGL(k_lw_scan_apply<0>, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream, A);
+  hipLaunchKernelGGL(k_lw_scan_apply, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream, A);
   return hipGetLastError();
 }
 
@@ -515,14 +585,12 @@ hipError_t launch_lw_draw(const LayerArgs &A, hipStream_t stream) {
 }
 
 hipError_t launch_lw_keep(const LayerArgs &A, hipStream_t stream) {
-  const int64_t tiles = A.n_keep_tiles;
-  if (tiles > 0) {
-    hipLaunchKernelGGL(k_lw_scan_reduce<1>, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream,
-                       A);
+  if (A.n_all > 0) {
+    const unsigned grid = unsigned(A.n_edge_tiles);
+    hipLaunchKernelGGL(k_lw_keep_flags, dim3(grid), dim3(256), 0, stream, A);
     hipLaunchKernelGGL(k_lw_scan_tiles, dim3(1), dim3(kLwScanThreads), 0, stream, A.tile_sum,
-                       A.tile_pre, tiles);
-    hipLaunchKernelGGL(k_lw_scan_apply<1>, dim3(unsigned(tiles)), dim3(kLwThreads), 0, stream,
-                       A);
+                       A.tile_pre, A.n_edge_tiles);
+    hipLaunchKernelGGL(k_lw_keep_emit, dim3(grid), dim3(256), 0, stream, A);
   }
   // at least one block: block 0 writes the etype entries and plans the next hop
   hipLaunchKernelGGL(k_lw_indptr, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);

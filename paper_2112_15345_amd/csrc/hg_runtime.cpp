@@ -1153,7 +1153,7 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
   A.pa = pa;
   A.n_pairs = P;
   A.n_all = S;
-  A.n_keep_tiles = (S + kLayerTile - 1) / kLayerTile;
+  A.n_edge_tiles = (S + kEdgeTile - 1) / kEdgeTile;
   A.sigmas = dsigmas();
   A.key_T = T / int32_t(sigmas.size());  // node types of one copy
   A.hop = h;
@@ -1184,10 +1184,11 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
   }
   A.cand_tiles = h_ctile[T];
   A.draw_threads = h_dbase[T];
-  const int64_t scan_tiles = std::max(A.cand_tiles, A.n_keep_tiles) + 1;
+  const int64_t scan_tiles = std::max(A.cand_tiles, A.n_edge_tiles) + 1;
   Carve ec;
-  ec.add(&A.tile_pair, A.n_keep_tiles + 1);
-  ec.add(&A.pos, S + 1);
+  ec.add(&A.tile_pair, A.n_edge_tiles + 1);
+  ec.add(&A.keep_bits, A.n_edge_tiles * (kEdgeTile / 64));
+  ec.add(&A.keep_pre, A.n_edge_tiles * (kEdgeTile / 64));
   Carve cc;
   for (int32_t t = 0; t < T; ++t) {
     cc.add(&h_cand[t], cbound[t]);
@@ -1219,12 +1220,11 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
   wt_dirty = true;
   if ((e = launch_lw_weights(A, stream)) != hipSuccess) return fail_device(e, "weights");
   // 3. the candidates of each type in ascending ID (region H+2 lists them)
-  const HopView cv = view(H + 2);
+  HopView cv = view(H + 2);
+  cv.src_out = A.cand;  // the list pointers of the hop's table
   int64_t ticketed = 0;
   uint32_t epoch;
-  if ((e = launch_store_ptrs(reinterpret_cast<void **>(dreg(H + 2) + lay.src_out),
-                             reinterpret_cast<void *const *>(h_cand), T, stream)) != hipSuccess ||
-      (e = next_epoch(&epoch)) != hipSuccess ||
+  if ((e = next_epoch(&epoch)) != hipSuccess ||
       (e = launch_compact(cv, ws->d_ts, T, ws->reached, ws->fbits, g->d_tile_base, g->n_tiles, 0,
                           ws->tile_sums, epoch, ticket_base, ws->dsmall, &ticketed, stream,
                           true)) != hipSuccess)

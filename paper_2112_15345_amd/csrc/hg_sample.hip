@@ -1277,8 +1277,8 @@ __global__ __launch_bounds__(256) void k_publish(int64_t *small, int64_t *host,
 }
 
 // dst[i] = v.p[i] for i < n: small tables written in stream order with the
-// values carried in the launch itself.
-constexpr int kPtrBatch = 16;
+// values carried in the launch itself (as many as the sampler's launch carries).
+constexpr int kPtrBatch = kInlineSrcOut;
 struct PtrBatch {
   void *p[kPtrBatch];
 };
@@ -1416,7 +1416,7 @@ hipError_t launch_store_ptrs(void **dst, void *const *vals, int32_t n, hipStream
     PtrBatch v{};
     const int32_t m = n - i < kPtrBatch ? n - i : kPtrBatch;
     for (int32_t k = 0; k < m; ++k) v.p[k] = vals[i + k];
-    hipLaunchKernelGGL(k_store_ptrs, dim3(1), dim3(64), 0, stream, dst + i, v, m);
+    hipLaunchKernelGGL(k_store_ptrs, dim3(1), dim3(kPtrBatch), 0, stream, dst + i, v, m);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

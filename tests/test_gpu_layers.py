@@ -259,3 +259,28 @@ def test_layer_many_relations(olib, R):
             refk = ref if k == 0 else host.sample_layers(seeds, sizes, sigmas[k])
             diffs = compare(refk, result_dict(g, bl[k]), 2, R, H)
             assert not diffs, f"case {c} bundle copy {k}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("total", [1, 63, 64, 65, 2047, 2048, 2049, 4096, 4160, 6145])
+@pytest.mark.parametrize("pairs", [1, 3, 700])
+def test_layer_edge_tiles(olib, total, pairs):
+    """The frontier's in-edges end on, before and after the edges of a flag
+    word (64 positions) and of a tile (2048); 700 pairs (most of one in-edge
+    when there are few) overflow the tile's pair table (512).  Kept: none, a
+    few, all."""
+    pairs = min(pairs, total)
+    rng = np.random.default_rng(100 * total + pairs)
+    n = 9000
+    deg = np.full(pairs, 1)
+    deg[0] += total - pairs - (total - pairs) // 2
+    deg[-1] += (total - pairs) // 2
+    idx = [np.sort(rng.choice(n, size=k, replace=False)) for k in deg]
+    ip = np.concatenate([[0], np.cumsum(deg), np.full(n - pairs, total)]).astype(np.int64)
+    ets = [(0, 0, ip, np.concatenate(idx).astype(np.int64))]
+    g = gpu_graph([n], ets, [None])
+    # the pairs' destinations among others without in-edges
+    seeds = [np.concatenate([np.arange(pairs), np.arange(pairs, pairs + 40)])[::-1].copy()]
+    for sizes in ([[-1]], [[0]], [[7]], [[300], [5]]):
+        _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, total, g=g)
+        diffs = compare(ref, got, 1, 1, len(sizes))
+        assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
