@@ -157,9 +157,9 @@ __device__ __forceinline__ int find_segment(const int64_t *base, int n,
 // order blocks start, so every lower tile belongs to a block already running.
 __device__ __forceinline__ int64_t take_ticket(int64_t *small,
                                                uint64_t ticket_base,
-                                               int64_t *lds) {
+                                               int64_t *lds, int slot = kSlotTicket) {
   if (threadIdx.x == 0)
-    lds[0] = int64_t(atomicAdd(reinterpret_cast<unsigned long long *>(small + kSlotTicket),
+    lds[0] = int64_t(atomicAdd(reinterpret_cast<unsigned long long *>(small + slot),
                                1ull) - ticket_base);
   __syncthreads();
   const int64_t t = lds[0];

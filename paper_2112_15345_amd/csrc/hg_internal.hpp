@@ -22,9 +22,9 @@ constexpr int64_t kTile = int64_t(kTileThreads) * kTileItems;  // 512 words
 constexpr int kPairItemsSmall = 2;
 constexpr int kPairItemsLarge = 8;
 constexpr int64_t kPairLargeFrom = int64_t(kTileThreads) * kPairItemsSmall * 512;
-inline int pair_items(int64_t n_items) {
-  return n_items >= kPairLargeFrom ? kPairItemsLarge : kPairItemsSmall;
-}
+// Items per thread of a counting pass over active pairs, whose number the host
+// only bounds: between the two, since they are few or many.
+constexpr int kPairItemsActive = 4;
 
 // Candidate capacity of one bottom-K selection (LDS entries per wavefront,
 // and per hub in the global candidate lists).
@@ -58,7 +58,9 @@ constexpr int kSlotEdges = 4;   // kept edges of the hop
 constexpr int kSlotHubs = 5;    // hub pairs
 constexpr int kSlotChunks = 6;  // hub chunks
 constexpr int kSlotWaves = 7;   // pairs sampled by one wavefront each
-constexpr int kSlotNew = 8;     // n_new[T], then ebase[R+1], then kept ebase[R+1]
+constexpr int kSlotActive = 8;  // pairs that may have in-edges (hops with pair bits)
+constexpr int kSlotActTicket = 9;  // tile tickets of their counting pass
+constexpr int kSlotNew = 10;    // n_new[T], then ebase[R+1], then kept ebase[R+1]
 
 constexpr int32_t kErrSeedRange = 1;   // a frontier vertex out of range
 constexpr int32_t kErrSeedRepeat = 2;  // a vertex twice in a frontier
@@ -81,15 +83,34 @@ struct EtypeStatic {
   int64_t n_dst_nodes;
   int32_t src_type;
   int32_t dst_type;
-  // Graphs with many edge types into one node type: per destination vertex a
-  // row of nz_words words whose bit nz_slot says whether this edge type has
-  // an in-edge there (nullptr: no mask, read indptr).
-  const uint32_t *nz_mask;
-  int32_t nz_words, nz_slot;
 };
 
-// Node types with at least this many incoming edge types get the mask above.
+// Node types with at least this many incoming edge types get a non-empty mask:
+// per vertex a row of `words` 32-bit words whose bit s says whether the type's
+// s-th incoming edge type has an in-edge there.
 constexpr int32_t kNzMaskMinEtypes = 16;
+// A node type with edges into it (per workspace, a bundle's copies each; only
+// for graphs with a mask): its incoming edge types, in the order of the mask's
+// bits, are nz_et[first] .. nz_et[first + n_in - 1].  mask: NULL for a type
+// without one, whose pairs all count as non-empty.
+struct NzType {
+  const uint32_t *mask;
+  int64_t num_nodes;
+  int32_t type, words, n_in, first;
+};
+// Hops of a graph with such a type work on the active pairs, those whose bit is
+// set (every pair of the other types): of the pairs of a 200-relation graph 3%
+// are.  The bit of pair (etype e, destination local ID i) is bit i & 63 of word
+// pair_word(pair_base[e], e, i): the words of an etype are followed by at most
+// one zero word before the next etype's, so the words in order hold the pairs
+// in order, and there are pair_words(P, R) of them.
+__host__ __device__ inline int64_t pair_word(int64_t pair_base, int e, int64_t i) {
+  return (pair_base >> 6) + e + (i >> 6);
+}
+__host__ __device__ inline int64_t pair_words(int64_t n_pairs, int32_t n_etypes) {
+  return (n_pairs >> 6) + n_etypes;
+}
+constexpr int kPairListItems = 4;  // words per thread of the pass that lists the active pairs
 
 // Static per node type (per workspace).
 // Per node type one flag byte and one frontier bit per vertex: the sampler
@@ -158,16 +179,22 @@ __host__ __device__ inline uint32_t hash_slot(uint64_t key, uint32_t mask) {
   return uint32_t((key * 0x9E3779B97F4A7C15ull) >> 32) & mask;
 }
 
-// Per-pair arrays of one hop (device), n_items entries each.
+// Per-pair arrays of one hop (device), n_items entries each.  Items are the
+// hop's pairs, or (act_pair not NULL) its active pairs in pair order.
 struct PairArrays {
   int64_t *plo;      // first in-edge slot
   int64_t *pdeg;     // in-degree
   int64_t *off;      // exclusive scan of kept edges
-  int32_t *pet;      // edge type of the pair
-  int64_t *wlist;    // the pair of each wavefront pair, in pair order
+  int32_t *pet;      // edge type of the item
+  int64_t *wlist;    // the item of each wavefront pair, in pair order
   int32_t *hub_cnt;  // per hub: candidates appended
-  int64_t *hub_pair; // per hub: its pair
+  int64_t *hub_pair; // per hub: its item
   int64_t *hub_choff; // per hub: its first chunk (strictly increasing)
+  int64_t *act_pair; // per item: its pair
+  uint64_t *bits;    // per word: its pairs' non-empty bits
+  int64_t *act_pre;  // per word: active pairs before it
+  int32_t *word_et;  // per word: its edge type
+  __device__ int64_t pair_of(int64_t item) const { return act_pair ? act_pair[item] : item; }
 };
 
 // ---- runtime hooks (hg_runtime.cpp) for the pipeline ------------------------
@@ -197,11 +224,21 @@ hipError_t launch_insert_frontier(HopView hv, const TypeStatic *ts,
                                   int32_t n_types, int64_t total, int64_t *small,
                                   hipStream_t stream);
 
+// The active pairs of a hop of a graph with masked types (nz, n_nz of them, every
+// node type with edges into it among them): the words of their bits, then the
+// list of the active pairs and their edge types in pair order.  max_front: at
+// least the largest frontier; n_items: at least P + 1.
+int64_t pair_list_tiles(int64_t n_items, int32_t n_etypes);
+hipError_t launch_pair_list(HopView hv, const NzType *nz, const int32_t *nz_et, int32_t n_nz,
+                            int32_t n_etypes, int64_t max_front, int64_t n_items, PairArrays pa,
+                            Lookback lb, uint32_t epoch, uint64_t ticket_base, int64_t *small,
+                            hipStream_t stream, StageEv ev);
+
 // Counting pass over n_items >= P + 1 pair slots (P = pair_base[R]): per pair
 // its in-edge range; exclusive scans of kept edges, hub chunks, wavefront
 // pairs and hub flags; per-etype edge starts (ebase) and the hop totals into
 // `small`.  Single pass, tiles taken by ticket.
-int64_t count_tiles(int64_t n_items);
+int64_t count_tiles(int64_t n_items, bool active);
 hipError_t launch_count_scan(HopView hv, const EtypeStatic *es, int32_t n_etypes,
                              int32_t n_types, int64_t n_items, PairArrays pa,
                              Lookback lb, uint32_t epoch, uint64_t ticket_base,
@@ -218,7 +255,7 @@ hipError_t launch_count_scan(HopView hv, const EtypeStatic *es, int32_t n_etypes
 // stores src_out[0..n_src_out) into src_out_slot (the hop's table entries).
 // Edge type e is keyed as type e % key_R with seed sigmas[e / key_R] (device).
 hipError_t launch_sample(HopView hv, const EtypeStatic *es, int32_t n_etypes,
-                         int32_t n_types, int64_t n_pairs, int64_t n_wave,
+                         int32_t n_types, int64_t n_items, int64_t n_words, int64_t n_wave,
                          int64_t n_chunks, int64_t n_hubs, PairArrays pa,
                          uint64_t *cand, const int64_t *small, const uint64_t *sigmas,
                          int32_t key_R, int32_t hop, int32_t key_bits, int64_t *src_gid,
@@ -267,7 +304,7 @@ struct LayerArgs {
   const int64_t *tile_base;  // bitmap tiles per type (plans the next hop)
   int32_t n_types, n_etypes;
   PairArrays pa;
-  int64_t n_pairs;
+  int64_t n_pairs, n_words;  // items, and words of active pairs' bits (0: items are pairs)
   // n_all in-edges of the frontier, numbered by the counting pass (pair p's
   // in-edges are positions off[p] .. off[p+1]-1, CSC slots plo[p] ..); they
   // are read from the CSC where they are needed, never written out

@@ -28,6 +28,8 @@
 //                    ones emitted in order;
 //  7. k_lw_indptr  : the block CSC, the kept edge starts per etype, and the
 //                    next hop's plan.
+#include <algorithm>
+
 #include "hg_device.hpp"
 #include "hg_internal.hpp"
 
@@ -394,7 +396,8 @@ __global__ __launch_bounds__(256) void k_lw_keep_emit(LayerArgs A) {
     const int64_t slot = slot_at(A, Q, R, q, j);
     const SegView v = seg_view<1>(A, T, sg);
     A.out_eid[first + x] = slot;
-    A.out_dst_local[first + x] = int32_t((R.n > 0 ? R.p0 + q : q) - v.pair_base);
+    A.out_dst_local[first + x] =
+        int32_t(A.pa.pair_of(R.n > 0 ? R.p0 + q : q) - v.pair_base);
     A.out_src_local[first + x] = static_cast<const int32_t *>(v.per_seg)[v.indices[slot]];
   }
 }
@@ -551,9 +554,21 @@ __global__ __launch_bounds__(256) void k_lw_indptr(LayerArgs A) {
     }
     plan_next_hop(A.hv, A.next, A.es, A.tile_base, A.small, A.n_types, A.n_etypes);
   }
-  for (int64_t p = gs_start(); p < A.n_pairs; p += gs_step()) {
-    const int e = A.pa.pet[p];
-    A.out_indptr[pb[e] + e + (p - pb[e])] = pos(A.pa.off[p]) - pos(ebase[e]);
+  if (A.n_words == 0) {
+    for (int64_t p = gs_start(); p < A.n_pairs; p += gs_step()) {
+      const int e = A.pa.pet[p];
+      A.out_indptr[pb[e] + e + (p - pb[e])] = pos(A.pa.off[p]) - pos(ebase[e]);
+    }
+    return;
+  }
+  // active pairs: lane i of a wavefront takes pair i of a word, whose entry is
+  // that of the first active pair not before it
+  for (int64_t y = gs_start(); y < A.n_words * kWave; y += gs_step()) {
+    const int64_t x = y / kWave;
+    const int e = A.pa.word_et[x];
+    const int64_t i = ((x - pair_word(pb[e], e, 0)) << 6) + lane_id();
+    const int64_t a = A.pa.act_pre[x] + __popcll(A.pa.bits[x] & lanes_below());
+    if (i < pb[e + 1] - pb[e]) A.out_indptr[pb[e] + e + i] = pos(A.pa.off[a]) - pos(ebase[e]);
   }
 }
 
@@ -593,7 +608,8 @@ hipError_t launch_lw_keep(const LayerArgs &A, hipStream_t stream) {
     hipLaunchKernelGGL(k_lw_keep_emit, dim3(grid), dim3(256), 0, stream, A);
   }
   // at least one block: block 0 writes the etype entries and plans the next hop
-  hipLaunchKernelGGL(k_lw_indptr, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);
+  hipLaunchKernelGGL(k_lw_indptr, dim3(grid_for(std::max(A.n_pairs, A.n_words * kWave), 256)), dim3(256),
+                     0, stream, A);
   return hipGetLastError();
 }
 

@@ -118,7 +118,7 @@ struct ETypeInfo {
   const int64_t *indices;
   // the destination type's non-empty mask (owned by the graph), if it has one
   const uint32_t *nz_mask = nullptr;
-  int32_t nz_words = 0, nz_slot = 0;
+  int32_t nz_words = 0;
 };
 
 // A device buffer that grows (stream-ordered) and is reused across calls.
@@ -200,6 +200,8 @@ struct Workspace {
   uint64_t publish_seq = 0;        // flag value of the last publish
   EtypeStatic *d_es = nullptr;     // static per-etype table
   TypeStatic *d_ts = nullptr;      // static per-type table
+  NzType *d_nz = nullptr;          // node types with edges into them (graphs with a mask)
+  int32_t *d_nz_et = nullptr;      // their incoming edge types
   int64_t *tile_sums = nullptr;    // per bitmap tile: prefix and count (compaction)
   Scratch tab;                     // per-hop tables (device)
   char *htab = nullptr;            // per-hop tables (pinned host)
@@ -400,6 +402,8 @@ void free_workspace(Workspace *w) {
   (void)hipFree(w->dsmall);
   (void)hipFree(w->d_es);
   (void)hipFree(w->d_ts);
+  (void)hipFree(w->d_nz);
+  (void)hipFree(w->d_nz_et);
   (void)hipFree(w->tile_sums);
   w->tab.release();
   w->pairs.release();
@@ -418,6 +422,29 @@ void free_workspace(Workspace *w) {
 
 // n_new[T], then ebase[R+1], then the kept ebase[R+1] of layer-wise hops
 size_t small_slots(const hg_graph *g) { return size_t(kSlotNew + g->T + 2 * (g->R + 1)); }
+
+// The node types of g with edges into them, when one of them has a non-empty mask
+// (else none), and the number of their incoming edge types.
+std::vector<NzType> nz_types(const hg_graph *g) {
+  std::vector<NzType> nz;
+  bool any = false;
+  for (const ETypeInfo &E : g->et) any = any || E.nz_mask;
+  if (!any) return nz;
+  std::vector<int32_t> at(size_t(g->T), -1);
+  for (const ETypeInfo &E : g->et) {
+    if (at[size_t(E.dst)] < 0) {
+      at[size_t(E.dst)] = int32_t(nz.size());
+      nz.push_back(NzType{E.nz_mask, g->nt[E.dst].num_nodes, E.dst, E.nz_words, 0, 0});
+    }
+    ++nz[size_t(at[size_t(E.dst)])].n_in;
+  }
+  int32_t first = 0;
+  for (NzType &N : nz) {
+    N.first = first;
+    first += N.n_in;
+  }
+  return nz;
+}
 
 // Takes a free workspace (or makes one) with table room for `tab_bytes`.
 hg_status acquire_workspace(hg_graph *g, size_t tab_bytes, hipStream_t stream,
@@ -475,8 +502,7 @@ hg_status acquire_workspace(hg_graph *g, size_t tab_bytes, hipStream_t stream,
         es[i] = EtypeStatic{E.indptr, E.indices, w->map + g->map_off[E.src],
                             w->reached + g->tile_base[E.src] * kTile * 32,
                             w->rbits + g->tile_base[E.src] * kTile,
-                            g->nt[E.dst].num_nodes, E.src, E.dst,
-                            E.nz_mask, E.nz_words, E.nz_slot};
+                            g->nt[E.dst].num_nodes, E.src, E.dst};
       }
       std::vector<TypeStatic> ts(g->T);
       for (int32_t t = 0; t < g->T; ++t)
@@ -486,6 +512,19 @@ hg_status acquire_workspace(hg_graph *g, size_t tab_bytes, hipStream_t stream,
       e = hipMemcpy(w->d_es, es.data(), sizeof(EtypeStatic) * es.size(), hipMemcpyHostToDevice);
       if (e == hipSuccess)
         e = hipMemcpy(w->d_ts, ts.data(), sizeof(TypeStatic) * ts.size(), hipMemcpyHostToDevice);
+      const std::vector<NzType> nz = nz_types(g);
+      if (e == hipSuccess && !nz.empty()) {
+        // the edge types of each node type in order (the order of its mask's bits)
+        std::vector<int32_t> et(size_t(g->R)), next(size_t(g->T), 0);
+        for (const NzType &N : nz) next[size_t(N.type)] = N.first;
+        for (int32_t i = 0; i < g->R; ++i) et[size_t(next[size_t(g->et[i].dst)]++)] = i;
+        e = hipMalloc(&w->d_nz, sizeof(NzType) * nz.size());
+        if (e == hipSuccess) e = hipMalloc(&w->d_nz_et, sizeof(int32_t) * et.size());
+        if (e == hipSuccess)
+          e = hipMemcpy(w->d_nz, nz.data(), sizeof(NzType) * nz.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess)
+          e = hipMemcpy(w->d_nz_et, et.data(), sizeof(int32_t) * et.size(), hipMemcpyHostToDevice);
+      }
     }
     if (e != hipSuccess) {
       free_workspace(w);
@@ -678,7 +717,7 @@ struct SampleRun {
   int32_t *lw_srcl = nullptr, *lw_dstl = nullptr;
   hg_status close_layer_edges();
   hg_status layer_hop(int32_t h, const HopView &hv, const HopView &nv, const PairArrays &pa,
-                      int64_t P, int64_t S, const std::vector<int64_t> &nF,
+                      int64_t items, int64_t words, int64_t S, const std::vector<int64_t> &nF,
                       const std::vector<int64_t> &cbound, int64_t *indptr_all,
                       int64_t *eid_all, int32_t *srcl_all, int32_t *dstl_all,
                       int64_t **src_slot, std::vector<int64_t *> &src_out, bool inline_ptrs);
@@ -1135,7 +1174,7 @@ hg_status SampleRun::close_layer_edges() {
 // the frontier): the candidates' importance and their per-type lists, the
 // draws, the next frontier, and the kept in-edges into the block arrays.
 hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
-                               const PairArrays &pa, int64_t P, int64_t S,
+                               const PairArrays &pa, int64_t items, int64_t words, int64_t S,
                                const std::vector<int64_t> &nF,
                                const std::vector<int64_t> &cbound, int64_t *indptr_all,
                                int64_t *eid_all, int32_t *srcl_all, int32_t *dstl_all,
@@ -1151,7 +1190,8 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
   A.n_types = T;
   A.n_etypes = R;
   A.pa = pa;
-  A.n_pairs = P;
+  A.n_pairs = items;
+  A.n_words = words;
   A.n_all = S;
   A.n_edge_tiles = (S + kEdgeTile - 1) / kEdgeTile;
   A.sigmas = dsigmas();
@@ -1291,12 +1331,17 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
   std::vector<int64_t *> last_src(T, nullptr);
   std::vector<int64_t> last_bound(T, 0);
   int64_t keys_before = 0;
+  // frontier sizes, or bounds of them, of the hop about to be counted
+  std::vector<int64_t> front(nF);
+  const std::vector<NzType> nz = nz_types(g);
   for (int32_t h = 0; h < H; ++h) {
     const HopView hv = view(h), nv = view(h + 1);
     // ---- 1. counting pass over at most n_items pair slots ----------------
-    const int64_t tiles = count_tiles(n_items);
+    const bool active = !nz.empty();  // items are the active pairs
+    const int64_t tiles = count_tiles(n_items, active);
+    const int64_t list_tiles = active ? pair_list_tiles(n_items, R) : 0;
     Carve pc;
-    PairArrays pa;
+    PairArrays pa{};
     pc.add(&pa.plo, n_items);
     pc.add(&pa.pdeg, n_items);
     pc.add(&pa.off, n_items);
@@ -1305,8 +1350,15 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
     pc.add(&pa.hub_cnt, n_items);
     pc.add(&pa.hub_pair, n_items);
     pc.add(&pa.hub_choff, n_items);
+    if (active) {
+      pc.add(&pa.act_pair, n_items);
+      pc.add(&pa.bits, pair_words(n_items, R));
+      pc.add(&pa.act_pre, pair_words(n_items, R));
+      pc.add(&pa.word_et, pair_words(n_items, R));
+    }
     if (!pc.in_scratch(ws->pairs, stream) ||
-        !ws->lb_pairs.ensure(sizeof(uint64_t) * 4 * size_t(tiles), stream))
+        !ws->lb_pairs.ensure(sizeof(uint64_t) * std::max(4 * size_t(tiles), size_t(list_tiles)),
+                             stream))
       return fail(HG_ENOMEM, "hop %d: pair scratch", h);
     Lookback lb{static_cast<uint64_t *>(ws->lb_pairs.p)};
     // new look-back words start with no tile published
@@ -1314,12 +1366,25 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
         (e = launch_fill_u32(static_cast<uint32_t *>(ws->lb_pairs.p),
                              int64_t(ws->lb_pairs.cap / sizeof(uint32_t)), 0u, stream)) != hipSuccess)
       return fail_device(e, "fill");
+    // the stage's first launch carries its start event
+    StageEv ev_count = stage_ev(h, HG_STAGE_COUNT);
     uint32_t epoch;
+    if (active) {
+      int64_t most = 0;
+      for (const NzType &N : nz) most = std::max(most, front[size_t(N.type)]);
+      if ((e = next_epoch(&epoch)) != hipSuccess ||
+          (e = launch_pair_list(hv, ws->d_nz, ws->d_nz_et, int32_t(nz.size()), R, most, n_items,
+                                pa, lb, epoch, ticket_base, ws->dsmall, stream,
+                                StageEv{ev_count.start, nullptr})) != hipSuccess)
+        return fail_device(e, "pair list");
+      ticket_base += uint64_t(list_tiles);
+      ev_count.start = nullptr;
+    }
     if ((e = next_epoch(&epoch)) != hipSuccess ||
         (e = launch_count_scan(hv, ws->d_es, R, T, n_items, pa, lb, epoch, ticket_base, X,
-                               ws->dsmall, stream, stage_ev(h, HG_STAGE_COUNT))) != hipSuccess)
+                               ws->dsmall, stream, ev_count)) != hipSuccess)
       return fail_device(e, "count");
-    ticket_base += uint64_t(tiles);
+    if (!active) ticket_base += uint64_t(tiles);
     // wait: this hop's sizes (and the previous hop's new-vertex counts)
     if ((e = sync_small()) != hipSuccess) return fail_device(e, "sync");
     hg_status st = check_flags("count");
@@ -1353,6 +1418,9 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
     P = hs[kSlotPairs];
     if (P != pb[R]) return fail(HG_EDEVICE, "hop %d: pair count mismatch", h);
     const int64_t S = hs[kSlotEdges];
+    const int64_t items = active ? hs[kSlotActive] : P;
+    const int64_t words = active ? pair_words(P, R) : 0;
+    if (items > P) return fail(HG_EDEVICE, "hop %d: active pair count mismatch", h);
     const int64_t n_hubs = hs[kSlotHubs], n_chunks = hs[kSlotChunks], n_wave = hs[kSlotWaves];
     std::vector<int64_t> eb(hs + kSlotNew + T, hs + kSlotNew + T + R + 1);
 
@@ -1384,6 +1452,7 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
     b->mem->ptrs.push_back(ob);
     last_src = src_out;
     last_bound = bound;
+    front = bound;
     // the sampler's scratch (a layer-wise hop launches no sampler)
     int64_t *gid_tmp = nullptr;
     uint64_t *cand = nullptr;
@@ -1407,7 +1476,7 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
       return fail_device(e, "tables");
 
     if (layer_sizes) {
-      if ((st = layer_hop(h, hv, nv, pa, P, S, nF, cbound, indptr_all, eid_all, srcl_all,
+      if ((st = layer_hop(h, hv, nv, pa, items, words, S, nF, cbound, indptr_all, eid_all, srcl_all,
                           dstl_all, src_slot, src_out, inline_ptrs)) != HG_OK)
         return st;
       for (int32_t t = 0; t < T; ++t) {
@@ -1431,7 +1500,7 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
     // blocks ordered per XCD when each XCD's share is whole mini-batches
     // (pairs and kept edges are in mini-batch order)
     const bool xcd_order = g->R / std::max(g->key_R, 1) >= kXcds;
-    if ((e = launch_sample(hv, ws->d_es, R, T, P, n_wave, n_chunks, n_hubs, pa, cand, ws->dsmall,
+    if ((e = launch_sample(hv, ws->d_es, R, T, items, words, n_wave, n_chunks, n_hubs, pa, cand, ws->dsmall,
                            dsigmas(), g->key_R, h, key_bits, gid_tmp, eid_all, dstl_all,
                            indptr_all,
                            src_slot, src_out.data(), inline_ptrs ? T : 0, X, stream,
@@ -1541,7 +1610,6 @@ hipError_t build_nonempty_masks(hg_graph *g, hipStream_t stream) {
       ETypeInfo &E = g->et[ets[k]];
       E.nz_mask = mask;
       E.nz_words = words;
-      E.nz_slot = int32_t(k);
     }
   }
   return hipSuccess;

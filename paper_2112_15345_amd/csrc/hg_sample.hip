@@ -109,6 +109,106 @@ __global__ void k_insert_frontier(HopView hv, const TypeStatic *ts,
 
 // ---- counting pass ---------------------------------------------------------
 
+// The pairs' bits for the frontier of node type nz[blockIdx.y]: a wavefront per
+// 64 frontier vertices loads their mask rows (one read of each row, where the
+// pairs of every edge type would each read a word of it) and turns two words of
+// them into 64 ballots, one per edge type, which the lanes write.  One step past
+// the frontier writes the zero word that may follow an etype's words.
+//
+// Why active pairs: on the 200-relation graph (20M vertices; bundles of 4, 14.8M
+// pairs in the second hop, 3% with in-edges) a counting pass over every pair took
+// 442 us (each block stages its edge types, scans and looks back for 2048 pairs
+// that are nearly all empty) and the sampler 228 us, most of it block-CSC entries
+// written one pair per lane.  Bits, list, a counting pass over the active pairs
+// and the sampler take 22 + 30 + 35 + 75 us there, the whole call 565 us
+// instead of 1148.  A graph without a mask (fewer than kNzMaskMinEtypes edge
+// types into every node type) keeps every pair: most are non-empty there.
+__global__ __launch_bounds__(256) void k_pair_bits(HopView hv, const NzType *nz,
+                                                   const int32_t *nz_et, int32_t n_etypes,
+                                                   int64_t n_words, PairArrays pa) {
+  const NzType N = nz[blockIdx.y];
+  const int64_t n = hv.nF[N.type];
+  const int64_t *front = hv.frontier[N.type];
+  const int lane = lane_id();
+  const int64_t waves = int64_t(gridDim.x) * (256 / kWave);
+  for (int64_t c = int64_t(blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
+       c * kWave < n + kWave; c += waves) {
+    const int64_t i = c * kWave + lane;
+    const int64_t v = i < n ? front[i] : -1;
+    // (an out-of-range seed has been flagged already: it has no active pair)
+    const bool ok = v >= 0 && v < N.num_nodes;
+    for (int32_t q = 0; q * 32 < N.n_in; q += 2) {
+      uint32_t m0 = 0, m1 = 0;
+      if (ok) {
+        m0 = N.mask ? N.mask[v * N.words + q] : ~0u;
+        m1 = !N.mask ? ~0u : (q + 1 < N.words ? N.mask[v * N.words + q + 1] : 0);
+      }
+      uint64_t mine = 0;
+#pragma unroll
+      for (int k = 0; k < 32; ++k) {
+        const uint64_t b0 = __ballot((m0 >> k) & 1u), b1 = __ballot((m1 >> k) & 1u);
+        if (lane == k) mine = b0;
+        if (lane == k + 32) mine = b1;
+      }
+      const int32_t s = q * 32 + lane;
+      if (s < N.n_in) {
+        const int e = nz_et[N.first + s];
+        const int64_t x = pair_word(hv.pair_base[e], e, c * kWave);
+        if (x < pair_word(hv.pair_base[e + 1], e + 1, 0) && x < n_words) {
+          pa.bits[x] = mine;
+          pa.word_et[x] = e;
+        }
+      }
+    }
+  }
+}
+
+// The active pairs from their bits, in pair order (a single-pass scan of the
+// words' population counts); the counting pass that follows takes its tickets
+// from zero.
+constexpr int64_t kPairListTile = int64_t(kTileThreads) * kPairListItems;
+__global__ __launch_bounds__(kTileThreads) void k_pair_list(HopView hv, int32_t n_etypes,
+                                                            int64_t n_items, PairArrays pa,
+                                                            Lookback lb, uint32_t epoch,
+                                                            uint64_t ticket_base,
+                                                            int64_t *small) {
+  __shared__ int64_t lds[8];
+  const int64_t tile = take_ticket(small, ticket_base, lds);
+  const int64_t P = hv.pair_base[n_etypes];
+  const int64_t W = P < n_items ? pair_words(P, n_etypes) : 0;
+  const int64_t x0 = tile * kPairListTile + int64_t(threadIdx.x) * kPairListItems;
+  uint64_t w[kPairListItems];
+  int32_t et[kPairListItems];
+  int64_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPairListItems; ++k) {
+    w[k] = x0 + k < W ? pa.bits[x0 + k] : 0;
+    et[k] = x0 + k < W ? pa.word_et[x0 + k] : 0;
+    sum += __popcll(w[k]);
+  }
+  int64_t agg[1], ex[1];
+  int64_t a = block_excl_scan_256(sum, lds, &agg[0]);
+  tile_lookback<1>(lb, tile, 0, epoch, agg, ex, small);
+  a += ex[0];
+#pragma unroll
+  for (int k = 0; k < kPairListItems; ++k) {
+    if (x0 + k < W) pa.act_pre[x0 + k] = a;
+    if (w[k]) {
+      const int64_t pb = hv.pair_base[et[k]];
+      const int64_t p0 = pb + ((x0 + k - pair_word(pb, et[k], 0)) << 6);
+      for (uint64_t m = w[k]; m; m &= m - 1) {
+        pa.act_pair[a] = p0 + (__ffsll((unsigned long long)m) - 1);
+        pa.pet[a] = et[k];
+        ++a;
+      }
+    }
+  }
+  if (tile == int64_t(gridDim.x) - 1 && threadIdx.x == kTileThreads - 1) {
+    small[kSlotActive] = a;
+    small[kSlotActTicket] = 0;
+  }
+}
+
 // Per pair: kept edges s, hub chunks, "one wavefront" flag, hub flag.
 // What the counting pass keeps of a pair until its outputs are written, next
 // to its kept count: its hub chunk count (a pair has fewer than 2^32 in-edges,
@@ -116,28 +216,24 @@ __global__ void k_insert_frontier(HopView hv, const TypeStatic *ts,
 constexpr uint32_t kPairWave = 1u << 30, kPairHub = 1u << 31, kPairChunks = kPairWave - 1;
 
 // Per edge type, what the counting pass reads for every pair; staged in
-// (dynamic) LDS, 52 bytes per edge type, when the graph has at most
+// (dynamic) LDS, 36 bytes per edge type, when the graph has at most
 // kCountMaxEtypes edge types (a bundle's virtual graph counts each copy).
-constexpr int kCountMaxEtypes = 1200;
+constexpr int kCountMaxEtypes = 1800;
 struct CountTable {
   int64_t *pbase;  // [n + 1]
   const int64_t **indptr;
   const int64_t **front;
   int64_t *n_dst;
-  const uint32_t **nz_mask;
-  int32_t *fanout, *nz_words, *nz_slot;
+  int32_t *fanout;
   __host__ __device__ static constexpr size_t bytes(int n) {
-    return size_t(8) * (n + 1) + size_t(8) * 4 * n + size_t(4) * 3 * n;
+    return size_t(8) * (n + 1) + size_t(8) * 3 * n + size_t(4) * n;
   }
   __device__ void carve(char *p, int n) {
     pbase = reinterpret_cast<int64_t *>(p);
     indptr = reinterpret_cast<const int64_t **>(pbase + n + 1);
     front = reinterpret_cast<const int64_t **>(indptr + n);
     n_dst = reinterpret_cast<int64_t *>(front + n);
-    nz_mask = reinterpret_cast<const uint32_t **>(n_dst + n);
-    fanout = reinterpret_cast<int32_t *>(nz_mask + n);
-    nz_words = fanout + n;
-    nz_slot = nz_words + n;
+    fanout = reinterpret_cast<int32_t *>(n_dst + n);
   }
 };
 static_assert(CountTable::bytes(kCountMaxEtypes) <= 64 * 1024, "the table fits 64 KiB of LDS");
@@ -154,22 +250,27 @@ struct CountView {
   }
   __device__ int64_t n_dst(int e) const { return kStaged ? t->n_dst[e] : es[e].n_dst_nodes; }
   __device__ int32_t fanout(int e) const { return kStaged ? t->fanout[e] : hv->fanout[e]; }
-  __device__ const uint32_t *nz_mask(int e) const { return kStaged ? t->nz_mask[e] : es[e].nz_mask; }
-  __device__ int32_t nz_words(int e) const { return kStaged ? t->nz_words[e] : es[e].nz_words; }
-  __device__ int32_t nz_slot(int e) const { return kStaged ? t->nz_slot[e] : es[e].nz_slot; }
 };
 
-// Thread i of a tile owns kPairItems consecutive pairs.  The pair's edge type
-// comes from the (staged) table; the frontier vertices of all items are
-// loaded together, then their indptr entries, so a thread waits on two
-// rounds of memory accesses.
-template <bool kStaged, int kPairItems>
+// Thread i of a tile owns kPairItems consecutive items: pairs, or (kActive)
+// active pairs.  The edge type of a pair comes from the (staged) table, an
+// active pair's from the list; the frontier vertices of all items are loaded
+// together, then their indptr entries, so a thread waits on two rounds of memory
+// accesses.  With active pairs the grid is sized for every pair, and blocks past
+// the active ones end before they take a ticket.
+template <bool kStaged, int kPairItems, bool kActive>
 __global__ __launch_bounds__(kTileThreads) void k_count_scan(
     HopView hv, const EtypeStatic *es, int32_t n_etypes, int32_t n_types,
     int64_t n_items, PairArrays pa, Lookback lb, uint32_t epoch,
     uint64_t ticket_base, ExclView X, int64_t *small) {
   __shared__ int64_t lds[16];
   extern __shared__ __align__(16) char count_lds[];
+  constexpr int64_t kPerTile = int64_t(kTileThreads) * kPairItems;
+  int64_t n_tiles = gridDim.x;
+  if (kActive) {
+    n_tiles = min(n_tiles, small[kSlotActive] / kPerTile + 1);  // items 0 .. active
+    if (int64_t(blockIdx.x) >= n_tiles) return;
+  }
   CountTable table;
   if (kStaged) {
     table.carve(count_lds, n_etypes);
@@ -181,24 +282,33 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
         table.front[e] = hv.frontier[E.dst_type];
         table.n_dst[e] = E.n_dst_nodes;
         table.fanout[e] = hv.fanout[e];
-        table.nz_mask[e] = E.nz_mask;
-        table.nz_words[e] = E.nz_words;
-        table.nz_slot[e] = E.nz_slot;
       }
     }
   }
-  const int64_t tile = take_ticket(small, ticket_base, lds);  // also a barrier
+  // (also a barrier)
+  const int64_t tile =
+      kActive ? take_ticket(small, 0, lds, kSlotActTicket) : take_ticket(small, ticket_base, lds);
   const CountView<kStaged> V{&table, &hv, es};
   const int64_t P = V.pbase(n_etypes);
+  const int64_t N = kActive ? small[kSlotActive] : P;
   const int64_t base = (tile * kTileThreads + threadIdx.x) * kPairItems;
   int32_t *err = reinterpret_cast<int32_t *>(small + kSlotErr);
   if (tile == 0 && threadIdx.x == 0 && P + 1 > n_items) atomicOr(err, kErrBound);
 
-  // edge type of every item; bit k of `valid` says item k is a pair (not past
-  // the pairs), bit k of `reads` that it reads its indptr entries
+  // pair and edge type of every item; bit k of `valid` says item k exists, bit
+  // k of `reads` that it reads its indptr entries
+  int64_t pr[kPairItems];
   int etype[kPairItems];
   uint32_t valid = 0, reads = 0;
-  {
+  if (kActive) {
+#pragma unroll
+    for (int k = 0; k < kPairItems; ++k) {
+      const bool in = base + k < N;
+      valid |= in ? 1u << k : 0u;
+      pr[k] = in ? load_global(pa.act_pair + base + k) : P;
+      etype[k] = in ? load_global(pa.pet + base + k) : n_etypes;
+    }
+  } else {
     int e = 0;
     if (base < P) {
       int lo = 0, hi = n_etypes;  // pbase(lo) <= base < pbase(hi)
@@ -213,9 +323,9 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
     }
 #pragma unroll
     for (int k = 0; k < kPairItems; ++k) {
-      const int64_t p = base + k;
-      if (p < P) {
-        while (V.pbase(e + 1) <= p) ++e;
+      pr[k] = base + k;
+      if (pr[k] < P) {
+        while (V.pbase(e + 1) <= pr[k]) ++e;
         valid |= 1u << k;
       }
       etype[k] = e;
@@ -225,7 +335,7 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
   int64_t v[kPairItems];
 #pragma unroll
   for (int k = 0; k < kPairItems; ++k)
-    v[k] = (valid >> k) & 1 ? load_global(V.front(etype[k]) + (base + k - V.pbase(etype[k]))) : 0;
+    v[k] = (valid >> k) & 1 ? load_global(V.front(etype[k]) + (pr[k] - V.pbase(etype[k]))) : 0;
 #pragma unroll
   for (int k = 0; k < kPairItems; ++k) {
     if ((valid >> k) & 1) {
@@ -235,23 +345,13 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
         atomicOr(err, kErrSeedRange);
     }
   }
-  // with a non-empty mask, a pair whose destination has no in-edge of its
-  // type reads no indptr (one mask word, shared by the vertex's edge types)
-#pragma unroll
-  for (int k = 0; k < kPairItems; ++k) {
-    const uint32_t *m = (reads >> k) & 1 ? V.nz_mask(etype[k]) : nullptr;
-    if (m) {
-      const int32_t slot = V.nz_slot(etype[k]);
-      const uint32_t w = load_global(m + v[k] * V.nz_words(etype[k]) + (slot >> 5));
-      if (((w >> (slot & 31)) & 1u) == 0) reads &= ~(1u << k);
-    }
-  }
   int64_t lo[kPairItems], hi[kPairItems];
 #pragma unroll
   for (int k = 0; k < kPairItems; ++k) {
-    const int64_t *ip = V.indptr(etype[k]) + v[k];
-    lo[k] = (reads >> k) & 1 ? load_global(ip) : 0;
-    hi[k] = (reads >> k) & 1 ? load_global(ip + 1) : 0;
+    const bool rd = (reads >> k) & 1;
+    const int64_t *ip = V.indptr(rd ? etype[k] : 0) + v[k];
+    lo[k] = rd ? load_global(ip) : 0;
+    hi[k] = rd ? load_global(ip + 1) : 0;
   }
 
   // per item: kept count cs and the packed chunk count and role flags cf;
@@ -262,14 +362,13 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
   int64_t keys = 0;
 #pragma unroll
   for (int k = 0; k < kPairItems; ++k) {
-    const int64_t p = base + k;
     cs[k] = 0;
     cf[k] = 0;
     if (!((valid >> k) & 1)) continue;  // past the pairs (an out-of-range vertex counts as deg 0)
     const int64_t deg = hi[k] - lo[k];
     const int64_t K = V.fanout(etype[k]);
     // in-edges that take part: all but the excluded ones
-    const int32_t nx = excl_count(X, etype[k], p - V.pbase(etype[k]));
+    const int32_t nx = deg > 0 ? excl_count(X, etype[k], pr[k] - V.pbase(etype[k])) : 0;
     const int64_t avail = deg - nx;
     const int64_t s = (K < 0 || avail <= K) ? avail : K;
     cs[k] = s;
@@ -282,8 +381,8 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
       cf[k] = kPairWave;  // pairs with excluded edges always take this role
     }
     if (deg > 0) {  // nothing reads these for an empty pair
-      pa.plo[p] = lo[k];
-      pa.pdeg[p] = deg;
+      pa.plo[base + k] = lo[k];
+      pa.pdeg[base + k] = deg;
     }
   }
 
@@ -318,24 +417,28 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
   for (int a = 0; a < 4; ++a) pre[a] += ex[a];
 
   int64_t *ebase = small + kSlotNew + n_types;
+  // the pair before the thread's first item (every pair, or every active one)
+  int64_t before = kActive ? (base > 0 && base <= N ? load_global(pa.act_pair + base - 1) : -1)
+                           : base - 1;
 #pragma unroll
   for (int k = 0; k < kPairItems; ++k) {
-    const int64_t p = base + k;
+    const int64_t x = base + k;
     const bool wave = (cf[k] & kPairWave) != 0, hub = (cf[k] & kPairHub) != 0;
-    if (p < n_items) {
-      pa.off[p] = pre[0];
-      pa.pet[p] = etype[k];
-      if (wave) pa.wlist[pre[2]] = p;
+    if (x < n_items && x <= N) {
+      pa.off[x] = pre[0];
+      if (!kActive) pa.pet[x] = etype[k];
+      if (wave) pa.wlist[pre[2]] = x;
       if (hub) {
         pa.hub_cnt[pre[3]] = 0;
-        pa.hub_pair[pre[3]] = p;
+        pa.hub_pair[pre[3]] = x;
         pa.hub_choff[pre[3]] = pre[1];
       }
-      // edge start of every etype whose first pair (or end, for the last) is p
-      if (p <= P) {
-        const int e = p < P ? etype[k] : n_etypes;
-        for (int e2 = e; e2 >= 0 && V.pbase(e2) == p; --e2) ebase[e2] = pre[0];
-      }
+      // edge start of every etype whose first pair lies after the item before
+      // and not after this one (or, for the end of the items, of those left)
+      const int64_t p = x < N ? pr[k] : P;
+      for (int e2 = x < N ? etype[k] : n_etypes; e2 >= 0 && V.pbase(e2) > before; --e2)
+        ebase[e2] = pre[0];
+      before = p;
     }
     pre[0] += cs[k];
     pre[1] += cf[k] & kPairChunks;
@@ -343,7 +446,7 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
     pre[3] += hub ? 1 : 0;
   }
   // the last tile holds the totals
-  if (tile == int64_t(gridDim.x) - 1 && threadIdx.x == kTileThreads - 1) {
+  if (tile == n_tiles - 1 && threadIdx.x == kTileThreads - 1) {
     small[kSlotPairs] = P;
     small[kSlotEdges] = pre[0];
     small[kSlotChunks] = pre[1];
@@ -505,7 +608,8 @@ struct SampleArgs {
   HopView hv;
   const EtypeStatic *es;
   int32_t n_etypes, n_types;
-  int64_t n_pairs, n_wave, n_chunks, n_hubs;
+  int64_t n_pairs, n_wave, n_chunks, n_hubs;  // n_pairs: items (pairs, or active pairs)
+  int64_t n_words;  // words of the active pairs' bits (0: items are pairs)
   int64_t blocks_a, blocks_b, blocks_c;
   int64_t chunks_per_wave;
   PairArrays pa;
@@ -635,9 +739,9 @@ __device__ void role_pair_groups(const SampleArgs &A, GroupLds &L, int64_t group
   int take = 0;
   if (p < A.n_pairs) {
     const int e = A.pa.pet[p];
-    const int64_t i = p - pb[e];
+    const int64_t i = A.pa.pair_of(p) - pb[e];
     const int64_t o = A.pa.off[p];
-    A.indptr_all[pb[e] + e + i] = o - ebase[e];
+    if (!A.n_words) A.indptr_all[pb[e] + e + i] = o - ebase[e];  // else role D's
     const int64_t s = A.pa.off[p + 1] - o;
     const int64_t deg = s > 0 ? A.pa.pdeg[p] : 0;
     uint64_t pick = 0;
@@ -720,7 +824,7 @@ struct WavePair {
 __device__ __forceinline__ WavePair wave_pair(const SampleArgs &A, int64_t p) {
   WavePair P;
   P.e = A.pa.pet[p];
-  const int64_t i = p - A.hv.pair_base[P.e];
+  const int64_t i = A.pa.pair_of(p) - A.hv.pair_base[P.e];
   P.c = make_ctx(A.es[P.e], A.src_gid, A.eid, A.dst_local, i, A.bits);
   P.kc = key_ctx(A, P.e);
   P.lo = A.pa.plo[p];
@@ -907,10 +1011,9 @@ __device__ HubParams hub_params(const SampleArgs &A, int64_t hub) {
   H.deg = uniform64(A.pa.pdeg[p]);
   H.o = uniform64(A.pa.off[p]);
   H.K = uniform64(A.pa.off[p + 1]) - H.o;
-  H.dst = uniform64(p - A.hv.pair_base[H.e]);
+  H.dst = uniform64(A.pa.pair_of(p) - A.hv.pair_base[H.e]);
   H.tau = uint64_t(uniform64(int64_t(cand_threshold(H.K, H.deg, uint64_t(1) << A.key_bits))));
-  H.nx = int32_t(__builtin_amdgcn_readfirstlane(
-      uint32_t(excl_count(A.X, H.e, p - A.hv.pair_base[H.e]))));
+  H.nx = int32_t(__builtin_amdgcn_readfirstlane(uint32_t(excl_count(A.X, H.e, H.dst))));
   return H;
 }
 
@@ -1078,8 +1181,8 @@ __global__ __launch_bounds__(kSampleThreads) void k_hub_finish(SampleArgs A) {
   const uint64_t key_space = uint64_t(1) << A.key_bits;
   const KeyCtx kc = key_ctx(A, e);
   const uint64_t tau = cand_threshold(K, deg, key_space);
-  const EmitCtx c = make_ctx(A.es[e], A.src_gid, A.eid, A.dst_local,
-                             p - A.hv.pair_base[e], A.bits);
+  const int64_t i = A.pa.pair_of(p) - A.hv.pair_base[e];
+  const EmitCtx c = make_ctx(A.es[e], A.src_gid, A.eid, A.dst_local, i, A.bits);
   const int64_t n_cand = A.pa.hub_cnt[hub];
   if (n_cand >= K && n_cand <= kCandCap) {
     const uint64_t *list = A.cand + hub * kCandCap;
@@ -1115,10 +1218,40 @@ __global__ __launch_bounds__(kSampleThreads) void k_hub_finish(SampleArgs A) {
   }
   uint64_t a, b;
   bisection_bounds(n_cand, K, tau, key_space, deg, &a, &b);
-  const int32_t nx = excl_count(A.X, e, p - A.hv.pair_base[e]);
+  const int32_t nx = excl_count(A.X, e, i);
   select_by_bisection(c, lo, deg, K, o, a, b,
                       philox_line(kc.k0, kc.k1, uint32_t(A.hop), uint32_t(kc.ke)), shift, A.X,
                       e, nx > 0);
+}
+
+// Role D (hops with active pairs): the block-CSC entries of kCscWords words of
+// 64 pairs per wavefront.  A pair's entry is the offset of the first active pair
+// not before it.
+constexpr int kCscWords = 8;
+__device__ void role_csc(const SampleArgs &A, int64_t w) {
+  const int64_t *ebase = A.small + kSlotNew + A.n_types;
+  const int64_t x0 = w * kCscWords;
+  int64_t at[kCscWords];
+  int e[kCscWords];
+#pragma unroll
+  for (int k = 0; k < kCscWords; ++k) {
+    e[k] = -1;
+    at[k] = 0;
+    if (x0 + k < A.n_words) {
+      e[k] = A.pa.word_et[x0 + k];
+      at[k] = A.pa.act_pre[x0 + k] + __popcll(A.pa.bits[x0 + k] & lanes_below());
+    }
+  }
+  int64_t o[kCscWords];
+#pragma unroll
+  for (int k = 0; k < kCscWords; ++k) o[k] = e[k] >= 0 ? A.pa.off[at[k]] : 0;
+#pragma unroll
+  for (int k = 0; k < kCscWords; ++k) {
+    if (e[k] < 0) continue;
+    const int64_t p0 = A.hv.pair_base[e[k]];
+    const int64_t i = ((x0 + k - pair_word(p0, e[k], 0)) << 6) + lane_id();
+    if (i < A.hv.pair_base[e[k] + 1] - p0) A.indptr_all[p0 + e[k] + i] = o[k] - ebase[e[k]];
+  }
 }
 
 __global__ __launch_bounds__(kSampleThreads) void k_sample(SampleArgs A) {
@@ -1164,10 +1297,12 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample(SampleArgs A) {
     const int64_t w = rc * kSampleWaves + wave;
     if (w * A.chunks_per_wave < A.n_chunks)
       role_hub_chunks(A, w, reinterpret_cast<uint64_t *>(&s_cand[wave][0][0]));
-  } else {
-    const int64_t w =
-        xcd_block(b - A.blocks_a - A.blocks_c, A.blocks_b, A.xcd) * kSampleWaves + wave;
+  } else if (b < n_ac + A.blocks_b) {
+    const int64_t w = xcd_block(b - n_ac, A.blocks_b, A.xcd) * kSampleWaves + wave;
     if (w * kWavePairs < A.n_wave) role_wave_pairs(A, s_cand[wave][0], s_cand[wave][1], w);
+  } else {
+    const int64_t w = (b - n_ac - A.blocks_b) * kSampleWaves + wave;
+    if (w * kCscWords < A.n_words) role_csc(A, w);
   }
 }
 
@@ -1299,19 +1434,40 @@ hipError_t launch_insert_frontier(HopView hv, const TypeStatic *ts,
   return hipGetLastError();
 }
 
-int64_t count_tiles(int64_t n_items) {
-  const int64_t per_tile = int64_t(kTileThreads) * pair_items(n_items);
+int64_t pair_list_tiles(int64_t n_items, int32_t n_etypes) {
+  return pair_words(n_items, n_etypes) / kPairListTile + 1;
+}
+
+hipError_t launch_pair_list(HopView hv, const NzType *nz, const int32_t *nz_et, int32_t n_nz,
+                            int32_t n_etypes, int64_t max_front, int64_t n_items, PairArrays pa,
+                            Lookback lb, uint32_t epoch, uint64_t ticket_base, int64_t *small,
+                            hipStream_t stream, StageEv ev) {
+  launch_k(k_pair_bits, dim3(grid_for(max_front + kWave, 256, 4096), unsigned(n_nz)), dim3(256), 0,
+           stream, ev.start, nullptr, hv, nz, nz_et, n_etypes, pair_words(n_items, n_etypes), pa);
+  launch_k(k_pair_list, dim3(unsigned(pair_list_tiles(n_items, n_etypes))), dim3(kTileThreads), 0,
+           stream, nullptr, ev.stop, hv, n_etypes, n_items, pa, lb, epoch, ticket_base, small);
+  return hipGetLastError();
+}
+
+// Items per thread of a counting pass over n_items slots.
+int count_items(int64_t n_items, bool active) {
+  if (active) return kPairItemsActive;
+  return n_items >= kPairLargeFrom ? kPairItemsLarge : kPairItemsSmall;
+}
+
+int64_t count_tiles(int64_t n_items, bool active) {
+  const int64_t per_tile = int64_t(kTileThreads) * count_items(n_items, active);
   const int64_t t = (n_items + per_tile - 1) / per_tile;
   return t < 1 ? 1 : t;
 }
 
-template <bool kStaged, int kItems>
+template <bool kStaged, int kItems, bool kActive>
 void count_launch(HopView hv, const EtypeStatic *es, int32_t n_etypes, int32_t n_types,
                   int64_t n_items, PairArrays pa, Lookback lb, uint32_t epoch,
                   uint64_t ticket_base, ExclView X, int64_t *small, hipStream_t stream,
                   StageEv ev) {
   const size_t lds = kStaged ? CountTable::bytes(n_etypes) : 0;
-  launch_k(k_count_scan<kStaged, kItems>, dim3(unsigned(count_tiles(n_items))),
+  launch_k(k_count_scan<kStaged, kItems, kActive>, dim3(unsigned(count_tiles(n_items, kActive))),
            dim3(kTileThreads), lds, stream, ev.start, ev.stop, hv, es, n_etypes, n_types,
            n_items, pa, lb, epoch, ticket_base, X, small);
 }
@@ -1321,24 +1477,28 @@ hipError_t launch_count_scan(HopView hv, const EtypeStatic *es, int32_t n_etypes
                              Lookback lb, uint32_t epoch, uint64_t ticket_base,
                              ExclView X, int64_t *small, hipStream_t stream, StageEv ev) {
   const bool staged = n_etypes <= kCountMaxEtypes;
-  const bool large = pair_items(n_items) == kPairItemsLarge;
-  if (staged && large)
-    count_launch<true, kPairItemsLarge>(hv, es, n_etypes, n_types, n_items, pa, lb, epoch,
-                                        ticket_base, X, small, stream, ev);
+  const bool active = pa.act_pair != nullptr;
+  const bool large = count_items(n_items, false) == kPairItemsLarge;
+  auto go = [&](auto launch) {
+    launch(hv, es, n_etypes, n_types, n_items, pa, lb, epoch, ticket_base, X, small, stream, ev);
+  };
+  if (active && staged)
+    go(count_launch<true, kPairItemsActive, true>);
+  else if (active)
+    go(count_launch<false, kPairItemsActive, true>);
+  else if (staged && large)
+    go(count_launch<true, kPairItemsLarge, false>);
   else if (staged)
-    count_launch<true, kPairItemsSmall>(hv, es, n_etypes, n_types, n_items, pa, lb, epoch,
-                                        ticket_base, X, small, stream, ev);
+    go(count_launch<true, kPairItemsSmall, false>);
   else if (large)
-    count_launch<false, kPairItemsLarge>(hv, es, n_etypes, n_types, n_items, pa, lb, epoch,
-                                         ticket_base, X, small, stream, ev);
+    go(count_launch<false, kPairItemsLarge, false>);
   else
-    count_launch<false, kPairItemsSmall>(hv, es, n_etypes, n_types, n_items, pa, lb, epoch,
-                                         ticket_base, X, small, stream, ev);
+    go(count_launch<false, kPairItemsSmall, false>);
   return hipGetLastError();
 }
 
 hipError_t launch_sample(HopView hv, const EtypeStatic *es, int32_t n_etypes,
-                         int32_t n_types, int64_t n_pairs, int64_t n_wave,
+                         int32_t n_types, int64_t n_items, int64_t n_words, int64_t n_wave,
                          int64_t n_chunks, int64_t n_hubs, PairArrays pa,
                          uint64_t *cand, const int64_t *small, const uint64_t *sigmas,
                          int32_t key_R, int32_t hop, int32_t key_bits, int64_t *src_gid,
@@ -1356,13 +1516,14 @@ hipError_t launch_sample(HopView hv, const EtypeStatic *es, int32_t n_etypes,
   A.es = es;
   A.n_etypes = n_etypes;
   A.n_types = n_types;
-  A.n_pairs = n_pairs;
+  A.n_pairs = n_items;
+  A.n_words = n_words;
   A.n_wave = n_wave;
   A.n_chunks = n_chunks;
   A.n_hubs = n_hubs;
   // role A always has blocks, for the closing CSC entries; every role's block
   // count is rounded up to a multiple of kXcds (its spare blocks find no work)
-  A.blocks_a = xcd_round(std::max<int64_t>(1, (n_pairs + kSampleThreads - 1) / kSampleThreads));
+  A.blocks_a = xcd_round(std::max<int64_t>(1, (n_items + kSampleThreads - 1) / kSampleThreads));
   A.blocks_b = xcd_round(((n_wave + kWavePairs - 1) / kWavePairs + kSampleWaves - 1) / kSampleWaves);
   // runs of chunks per wavefront: long enough to amortise finding the hub,
   // short enough to leave about kHubWaves wavefronts for the chip
@@ -1383,7 +1544,8 @@ hipError_t launch_sample(HopView hv, const EtypeStatic *es, int32_t n_etypes,
   A.eid = eid;
   A.dst_local = dst_local;
   A.indptr_all = indptr_all;
-  const int64_t blocks = A.blocks_a + A.blocks_b + blocks_c;
+  const int64_t blocks_d = (n_words + kCscWords * kSampleWaves - 1) / (kCscWords * kSampleWaves);
+  const int64_t blocks = A.blocks_a + A.blocks_b + blocks_c + blocks_d;
   launch_k(k_sample, dim3(unsigned(blocks)), dim3(kSampleThreads), 0, stream, ev_sample.start,
            ev_sample.stop, A);
   if (n_hubs > 0) {

@@ -388,3 +388,41 @@ def test_reached_bit_mode(olib, pad):
     for b, blocks in enumerate(got):
         ref = host.sample_blocks(W.seeds_per_type(wl, b), fan, b)
         assert not compare(ref, result_dict(g, blocks), g.T, g.R, len(fan))
+
+
+@pytest.mark.parametrize("R", [16, 31, 32, 33, 64, 65, 130])
+def test_mask_bits_of_the_frontier(olib, R):
+    """Node types with a non-empty mask: the frontier's mask rows are transposed
+    64 vertices and 64 edge types at a time.  Frontiers that end on, before and
+    after a wavefront's 64 vertices, edge types on, before and after a mask
+    word's 32; two such node types; single calls and a bundle, whose copies'
+    pairs start anywhere in a word."""
+    rng = np.random.default_rng(300 + R)
+    nn = [400, 150]
+    ets = []
+    for e in range(2 * R):
+        d = e & 1
+        s = int(rng.integers(0, 2))
+        indptr, indices = [0], []
+        for _v in range(nn[d]):
+            k = int(rng.integers(1, 7)) if rng.random() < 0.1 else 0
+            indices.extend(int(x) for x in np.sort(rng.choice(nn[s], size=k, replace=False)))
+            indptr.append(len(indices))
+        ets.append((s, d, np.array(indptr, np.int64), np.array(indices, np.int64)))
+    g = gpu_graph(nn, ets, [None, None])
+    host = oracle.HostGraph([(n, None) for n in nn], ets, lib=olib)
+    fan = [[3] * (2 * R), [2] * (2 * R)]
+    batches = []
+    for n0, n1 in ((1, 0), (63, 1), (64, 64), (65, 63), (128, 149), (129, 0)):
+        batches.append([rng.choice(nn[0], size=n0, replace=False).astype(np.int64),
+                        rng.choice(nn[1], size=n1, replace=False).astype(np.int64)])
+    refs = [host.sample_blocks(s, fan, 5 + b) for b, s in enumerate(batches)]
+    for b, s in enumerate(batches):
+        got = result_dict(g, g.sample_blocks(gpu_seeds(s), fan, 5 + b))
+        diffs = compare(refs[b], got, 2, 2 * R, 2)
+        assert not diffs, f"seeds {[x.size for x in s]}: " + "\n".join(diffs[:10])
+    bl = g.sample_bundle([gpu_seeds(s) for s in batches], fan,
+                         [5 + b for b in range(len(batches))], gather=[])
+    for b in range(len(batches)):
+        diffs = compare(refs[b], result_dict(g, bl[b]), 2, 2 * R, 2)
+        assert not diffs, f"bundle batch {b}: " + "\n".join(diffs[:10])
