@@ -3,7 +3,8 @@ generation on MI355X (DistDGLv2, arXiv 2112.15345, Sec. 3.2 and Sec. 4.2).
 
 Argument marshalling only: every step of the path runs in the library's gfx950
 kernels.  PyTorch supplies device memory (the graph, feature tables, outputs)
-and the stream (the current torch stream).  Import fails loudly if the library
+and the stream (the current torch stream).  The tensors over a mini-batch's
+arrays are made by the native module _hgviews.so.  Import fails loudly if either
 is not built; there is no CPU path.
 
     g = Graph(ntypes=[(num_nodes, feat_or_None), ...],
@@ -24,6 +25,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhg.so")
+VIEWS_PATH = os.path.join(_HERE, "_hgviews.so")
 
 HG_OK, HG_EINVAL, HG_ENOMEM, HG_EDEVICE, HG_EUNSUPPORTED = 0, -1, -2, -3, -4
 HG_DT_NONE, HG_DT_F32, HG_DT_F16, HG_DT_BF16 = 0, 1, 2, 3
@@ -151,16 +153,25 @@ def _bind(lib: ctypes.CDLL) -> ctypes.CDLL:
 
 
 _lib = None
+_views = None
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
-    """Loads libhg.so; raises if it has not been built (no fallback path)."""
-    global _lib
+    """Loads libhg.so and the binding's native module; raises if either has not
+    been built (no fallback path)."""
+    global _lib, _views
     if _lib is None:
-        if not os.path.exists(path):
-            raise ImportError(f"{path} is missing: build it with "
-                              "`python -m paper_2112_15345_amd.build`")
-        _lib = _bind(ctypes.CDLL(path))
+        for need in (path, VIEWS_PATH):
+            if not os.path.exists(need):
+                raise ImportError(f"{need} is missing: build it with "
+                                  "`python -m paper_2112_15345_amd.build`")
+        lib = _bind(ctypes.CDLL(path))
+        from . import _hgviews
+        _hgviews.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.hg_blocks_nodes, lib.hg_blocks_edges, lib.hg_blocks_input_nodes,
+            lib.hg_blocks_features, lib.hg_blocks_seeds, lib.hg_blocks_edge_pairs)))
+        _views = _hgviews
+        _lib = lib
     return _lib
 
 
@@ -179,24 +190,12 @@ def _dev_i64(x, device) -> torch.Tensor:
     return t.contiguous()
 
 
-class _DeviceArray:
-    """Presents library-owned device memory through __cuda_array_interface__;
-    holds a reference to the owning handle so that it outlives the view."""
-
-    def __init__(self, ptr: int, n: int, typestr: str, owner):
-        self.__cuda_array_interface__ = {"shape": (n,), "typestr": typestr,
-                                         "data": (ptr, False), "version": 3,
-                                         "strides": None, "stream": None}
-        self._owner = owner
-
-
-_TYPESTR = {torch.int64: "<i8", torch.int32: "<i4", torch.uint8: "|u1"}
-
-
-def _view(ptr: int, n: int, dtype, owner, device) -> torch.Tensor:
-    if n == 0 or not ptr:
-        return torch.empty(0, dtype=dtype, device=device)
-    return torch.as_tensor(_DeviceArray(ptr, n, _TYPESTR[dtype], owner), device=device)
+def _made(r):
+    """What a call of the native module returned: its tensors, or the failed
+    accessor's status as an int."""
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 class Blocks:
@@ -207,6 +206,7 @@ class Blocks:
         self._h = handle
         self.n_hops = n_hops
         self.device = graph.device
+        self._dev = -1 if graph.device.index is None else graph.device.index
 
     def __del__(self):
         h = getattr(self, "_h", None)
@@ -220,24 +220,14 @@ class Blocks:
 
     def nodes(self, hop: int, ntype: int):
         """(n_dst, src_gid): src_gid[:n_dst] is the frontier of this hop."""
-        nd, ns, p = _I64(), _I64(), ctypes.c_void_p()
-        _check(load_library().hg_blocks_nodes(self._h, hop, ntype, ctypes.byref(nd),
-                                              ctypes.byref(ns), ctypes.byref(p)))
-        return nd.value, _view(p.value, ns.value, torch.int64, self, self.device)
+        return _made(_views.nodes(self._h.value or 0, hop, ntype, self._dev, self))
 
     def edges(self, hop: int, etype: int):
         """(indptr, src_local, dst_local, eid) of one edge type in block `hop`."""
-        ne = _I64()
-        pi, ps, pd, pe = (ctypes.c_void_p() for _ in range(4))
-        _check(load_library().hg_blocks_edges(self._h, hop, etype, ctypes.byref(ne),
-                                              ctypes.byref(pi), ctypes.byref(ps),
-                                              ctypes.byref(pd), ctypes.byref(pe)))
-        d = self.graph.etypes[etype][1]
-        n_dst = self.nodes(hop, d)[0]
-        return (_view(pi.value, n_dst + 1, torch.int64, self, self.device),
-                _view(ps.value, ne.value, torch.int32, self, self.device),
-                _view(pd.value, ne.value, torch.int32, self, self.device),
-                _view(pe.value, ne.value, torch.int64, self, self.device))
+        ets = self.graph.etypes
+        # (an edge type out of range is the accessor's error)
+        d = ets[etype][1] if 0 <= etype < len(ets) else 0
+        return _made(_views.edges(self._h.value or 0, hop, etype, d, self._dev, self))
 
     def num_edges(self, hop: int, etype: int) -> int:
         ne = _I64()
@@ -270,25 +260,16 @@ class Blocks:
         return sum(sum(row) for row in self.edge_counts())
 
     def input_nodes(self, ntype: int) -> torch.Tensor:
-        n, p = _I64(), ctypes.c_void_p()
-        _check(load_library().hg_blocks_input_nodes(self._h, ntype, ctypes.byref(n),
-                                                    ctypes.byref(p)))
-        return _view(p.value, n.value, torch.int64, self, self.device)
+        return _made(_views.input_nodes(self._h.value or 0, ntype, self._dev, self))
 
     def features(self, ntype: int):
         """Rows gathered for `ntype` by sample_blocks(..., gather=...): a
         [rows, dim] tensor of the type's dtype (a view of library memory), or
         None when the type was not gathered."""
-        rows, p = _I64(), ctypes.c_void_p()
-        _check(load_library().hg_blocks_features(self._h, ntype, ctypes.byref(rows),
-                                                 ctypes.byref(p)))
-        if not p.value:
-            return None
-        feat = self.graph.ntypes[ntype][1]
-        dim = feat.shape[1]
-        nbytes = rows.value * dim * feat.element_size()
-        return _view(p.value, nbytes, torch.uint8, self, self.device).view(feat.dtype).view(
-            rows.value, dim)
+        nts = self.graph.ntypes
+        feat = nts[ntype][1] if 0 <= ntype < len(nts) else None
+        dim, code = (0, HG_DT_NONE) if feat is None else (feat.shape[1], _DTYPE_CODE[feat.dtype])
+        return _made(_views.features(self._h.value or 0, ntype, dim, code, self._dev, self))
 
     def num_input_nodes(self, ntype: int) -> int:
         n = _I64()
@@ -298,21 +279,12 @@ class Blocks:
     def seeds(self, ntype: int) -> torch.Tensor:
         """The seeds of `ntype`: an edge-seeded batch's endpoints in ascending
         ID, or the given seeds of a vertex-seeded one."""
-        n, p = _I64(), ctypes.c_void_p()
-        _check(load_library().hg_blocks_seeds(self._h, ntype, ctypes.byref(n), ctypes.byref(p)))
-        return _view(p.value, n.value, torch.int64, self, self.device)
+        return _made(_views.seeds(self._h.value or 0, ntype, self._dev, self))
 
     def edge_pairs(self, etype: int):
         """(pos_src, pos_dst, neg_dst) of an edge-seeded batch: local IDs among
         the seeds; negative i * n_neg + k has source pos_src[i]."""
-        npos, nneg = _I64(), _I64()
-        ps, pd, pn = (ctypes.c_void_p() for _ in range(3))
-        _check(load_library().hg_blocks_edge_pairs(self._h, etype, ctypes.byref(npos),
-                                                   ctypes.byref(ps), ctypes.byref(pd),
-                                                   ctypes.byref(nneg), ctypes.byref(pn)))
-        return (_view(ps.value, npos.value, torch.int32, self, self.device),
-                _view(pd.value, npos.value, torch.int32, self, self.device),
-                _view(pn.value, nneg.value, torch.int32, self, self.device))
+        return _made(_views.edge_pairs(self._h.value or 0, etype, self._dev, self))
 
 
 class Graph:

@@ -1,7 +1,9 @@
-"""Builds libhg.so (the gfx950 kernels and the C ABI of include/hg.h) in-tree.
+"""Builds libhg.so (the gfx950 kernels and the C ABI of include/hg.h) and the
+Python binding's native module _hgviews.so in-tree.
 
-Every source is compiled with hipcc for gfx950 only, then linked into one shared
-library next to this file.  `python -m paper_2112_15345_amd.build` runs it.
+Every source of the library is compiled with hipcc for gfx950 only, then linked
+into one shared library next to this file; _hgviews.so is host code against the
+installed PyTorch.  `python -m paper_2112_15345_amd.build` runs it.
 """
 from __future__ import annotations
 
@@ -10,12 +12,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 REPO = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(REPO, "include")
 LIB = os.path.join(HERE, "libhg.so")
+VIEWS = os.path.join(HERE, "_hgviews.so")
 OBJDIR = os.path.join(REPO, "_build", "hg")
 
 SOURCES = ["hg_sample.hip", "hg_compact.hip", "hg_gather.hip", "hg_edges.hip",
@@ -47,11 +51,35 @@ def _compile(src: str, verbose: bool) -> str:
     return obj
 
 
+def _build_views(verbose: bool) -> None:
+    """Compiles and links _hgviews.so (host code only)."""
+    import torch
+    import torch.utils.cpp_extension as ext
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = VIEWS + ".tmp"
+    inc = [x for p in (*ext.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include")
+           for x in ("-isystem", p)]
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+           "-D__HIP_PLATFORM_AMD__=1", "-I", INCLUDE, *inc,
+           os.path.join(CSRC, "hg_views.cpp"), "-o", tmp, "-L", libdir, "-ltorch", "-ltorch_cpu",
+           "-lc10", "-ltorch_python", f"-Wl,-rpath,{libdir}"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"g++ failed on hg_views.cpp:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, VIEWS)
+
+
 def build(verbose: bool = False) -> str:
-    """Compiles every source for gfx950 and links libhg.so; returns its path."""
+    """Compiles every source for gfx950 and links libhg.so (returns its path), and
+    builds _hgviews.so."""
     os.makedirs(OBJDIR, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
+        views = ex.submit(_build_views, verbose)
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
+        views.result()
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:
