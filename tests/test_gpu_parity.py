@@ -426,3 +426,18 @@ def test_mask_bits_of_the_frontier(olib, R):
     for b in range(len(batches)):
         diffs = compare(refs[b], result_dict(g, bl[b]), 2, 2 * R, 2)
         assert not diffs, f"bundle batch {b}: " + "\n".join(diffs[:10])
+
+
+# key bits for which a hub's candidate list (about K + 4 sqrt(K) + 16 entries, at
+# most 512) holds equal keys: several to a value, pairs of them, hardly any; lists
+# of 1 to 3 entries past a multiple of four, and of several per lane
+@pytest.mark.parametrize("deg,K,bits", [(3000, 20, 12), (3000, 20, 16), (2049, 1, 12),
+                                        (2049, 2, 14), (5000, 3, 20), (70000, 300, 14),
+                                        (70000, 380, 20), (70000, 100, 32)])
+def test_hub_equal_keys(olib, deg, K, bits):
+    nn, ets, feats = hub_graph(deg)
+    for sigma in range(6):
+        _, _, ref, got = run_both(olib, nn, ets, feats, [np.array([0, 3, 1], np.int64)], [[K]],
+                                  sigma, bits)
+        diffs = compare(ref, got, 1, 1, 1)
+        assert not diffs, f"sigma {sigma}: " + "\n".join(diffs[:10])
