@@ -297,6 +297,15 @@ constexpr int64_t kLayerTile = 512;
 // In-edges per tile of the layer-wise edge passes (256 threads, eight each).
 constexpr int64_t kEdgeTile = 2048;
 
+// The candidates' importance is summed in LDS, a bin of kBinVerts vertices (half a
+// bitmap tile: bin b of all types has frontier words b * kBinVerts / 32 ...) to a
+// block, when the call's vertices make at most kMaxBins bins (each block of the
+// binning passes counts every bin in LDS); else by global atomics into an array of
+// every vertex's importance.
+constexpr int64_t kBinVerts = 8192;
+constexpr int64_t kBinsPerTile = kTile * 32 / kBinVerts;
+constexpr int64_t kMaxBins = 8192;
+
 struct LayerArgs {
   HopView hv, next;
   const EtypeStatic *es;
@@ -321,6 +330,18 @@ struct LayerArgs {
   int64_t cand_tiles, draw_threads;  // cand_tile[T], draw_base[T] (host copies)
   int64_t *tile_sum;   // per scan tile
   int64_t *tile_pre;   // per scan tile: exclusive scan over all tiles, then the grand total
+  // binned importance (n_bins > 0): per bin its in-edges, their first record and
+  // the room for its candidates (exclusive scans), its candidates and their
+  // importance, and those of the bins before it
+  int64_t n_bins;
+  const uint32_t *fbits;   // frontier bits of all types
+  uint32_t *bin_edges, *bin_at;
+  int64_t *bin_rec, *bin_cap;  // [n_bins + 1]
+  uint32_t *rec;           // [n_all] (edge_record)
+  int32_t *bin_cand_off;   // per candidate: its vertex's place in the bin
+  uint64_t *bin_cand_pre;  // per candidate: importance before it in the bin
+  int64_t *bin_n, *bin_n_pre;  // [n_bins], [n_bins + 1]
+  int64_t *bin_w, *bin_w_pre;  // [n_bins], [n_bins + 1]
   uint64_t *keep_bits;  // [n_edge_tiles * kEdgeTile / 64] kept flags
   int32_t *keep_pre;    // per word: kept edges before it within its tile
   int64_t *out_eid;
@@ -346,11 +367,16 @@ inline size_t layer_table_bytes(int32_t T) {
 // frontier whose source is not in the frontier, u is marked reached and
 // wt[type(u)][u] += floor(2^32 / deg(v)^2).
 hipError_t launch_lw_weights(const LayerArgs &A, hipStream_t stream);
+// The same by bins: records of the in-edges grouped by bin, then each bin's
+// candidates with their importance prefix, and the scans over the bins.  Touches
+// neither the reached flags nor an importance array.
+hipError_t launch_lw_bins(const LayerArgs &A, hipStream_t stream);
 // Exclusive prefix of the candidates' importance per node type (three
 // launches: tile sums, one scan of the tile sums, apply); zeroes the
 // candidates' importance entries.
 hipError_t launch_lw_prefix(const LayerArgs &A, hipStream_t stream);
-// The draws of every node type: marks the drawn candidates reached.
+// The draws of every node type (among the bins' candidates with n_bins > 0):
+// marks the drawn candidates reached.
 hipError_t launch_lw_draw(const LayerArgs &A, hipStream_t stream);
 // The kept in-edges (source in the next frontier): their flags, a scan of the
 // tiles' counts, the kept ones emitted in order; then the block CSC, the kept edge starts per etype

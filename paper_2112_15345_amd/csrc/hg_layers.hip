@@ -8,6 +8,11 @@
 // One hop, after the counting pass has numbered every in-edge of the frontier
 // (fanout -1: pair p's in-edges are positions off[p] .. off[p+1]-1); no
 // sampler runs, and the edges are read from the CSC where needed:
+//  1-3. k_lw_tile_pairs, k_lw_bin_* : the first pair of every 2048-position tile;
+//                    then the in-edges grouped into bins of 8192 sources, each
+//                    bin's importance summed in LDS and its candidates listed
+//                    with its prefix; k_lw_bin_draw draws among them.  Calls of
+//                    more than kMaxBins bins instead:
 //  1. k_lw_tile_pairs, k_lw_weights : the first pair of every 2048-position
 //                    tile; then the importance of every candidate (a source
 //                    not in the frontier, which is marked reached): sum of
@@ -73,6 +78,18 @@ __device__ __forceinline__ uint64_t layer_weight(int64_t d) {
   return q;
 }
 
+// A record of an in-edge: its source's place in the bin (13 bits) and the code of
+// the destination's in-degree d (17 bits): d, or 0 past 65536, where the
+// importance floor(2^32 / d^2) is 0.
+__device__ __forceinline__ uint32_t degree_code(int64_t d) {
+  return d <= 65536 ? uint32_t(d) : 0u;
+}
+constexpr int kBinBits = 13;
+static_assert(kBinVerts == int64_t(1) << kBinBits, "a place in a bin takes 13 bits");
+__device__ __forceinline__ uint64_t code_weight(uint32_t d) {
+  return d ? layer_weight(int64_t(d)) : 0;
+}
+
 __device__ __forceinline__ const int64_t *ebase_of(const LayerArgs &A) {
   return A.small + kSlotNew + A.n_types;  // starts of each etype's emitted edges
 }
@@ -98,10 +115,11 @@ struct TileSegs {
   const int64_t *indices[kTileSegs];
   uint8_t *reached[kTileSegs];       // reached flags of the source type
   int64_t pair_base[kTileSegs];
+  int32_t bin0[kTileSegs];           // first bin of the source type
   int e0, n;
 };
 
-// kKind 0: per_seg = importance array of the source type; 1: source map.
+// kKind 0: per_seg = importance array of the source type; 1: source map; 2: bins.
 // pa, pb: the pair of the range's first position and a pair not before that of
 // its last one (whose etypes bound the range's; two loads instead of two
 // searches over the etype starts).
@@ -122,11 +140,13 @@ __device__ void tile_segs_load(const LayerArgs &A, int64_t pa, int64_t pb, TileS
       T.fbits[threadIdx.x] = A.ts[E.src_type].fbits;
       if (kKind == 0)
         T.per_seg[threadIdx.x] = A.wt[E.src_type];
-      else
+      else if (kKind == 1)
         T.per_seg[threadIdx.x] = E.src_map;
       T.indices[threadIdx.x] = E.indices;
       T.reached[threadIdx.x] = E.src_reached;
       T.pair_base[threadIdx.x] = A.hv.pair_base[e];
+      if (kKind == 2)
+        T.bin0[threadIdx.x] = int32_t(kBinsPerTile * A.tile_base[E.src_type]);
     }
   }
 }
@@ -179,7 +199,8 @@ __global__ __launch_bounds__(256) void k_lw_tile_pairs(LayerArgs A) {
 // tile_pair of the next one (which may hold one pair past the tile).  More than
 // kTilePairs pairs (runs of empty pairs) leave n = 0, and each position then
 // searches the pair offsets.  `w`: the importance that each in-edge of the pair
-// adds to its source (kKind 0), computed once per pair instead of per edge.
+// adds to its source (kKind 0), computed once per pair instead of per edge, or its
+// code in a record (kKind 2).
 constexpr int kTilePairs = 512;
 struct TilePairs {
   int64_t off[kTilePairs], plo[kTilePairs];
@@ -201,6 +222,7 @@ __device__ void tile_tables(const LayerArgs &A, int64_t tile, TileSegs &T, TileP
     const bool any = A.pa.off[pa + k + 1] > lo;
     Q.plo[k] = any ? A.pa.plo[pa + k] : 0;
     if (kKind == 0) Q.w[k] = any ? layer_weight(A.pa.pdeg[pa + k]) : 0;
+    if (kKind == 2) Q.w[k] = any ? degree_code(A.pa.pdeg[pa + k]) : 0;
   }
   tile_segs_load<kKind>(A, pa, pb, T);
   __syncthreads();
@@ -293,6 +315,315 @@ __global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
     if (w)
       atomicAdd(reinterpret_cast<unsigned long long *>(static_cast<uint64_t *>(v.per_seg) + u),
                 (unsigned long long)w);
+  }
+}
+
+// ---- importance by bins -------------------------------------------------------
+// Global atomics run at 24e9 per second on this GPU wherever their targets lie (8
+// MiB or 256 MiB, on one XCD or all), so adding every in-edge's importance to a
+// global array takes 1.2 ms for the academic graph's second hop in bundles of 16
+// (44M in-edges), and the candidates then have to be listed and scanned (0.27 ms).
+// Grouped by bin first (count, scan, scatter: 4 bytes an in-edge), a bin's sums
+// live in LDS, its candidates come out in ascending ID with their prefix, and only
+// the bins are scanned: 170 us counting, 270 scattering, 200 summing and 20 for the
+// scans in place of 1.5 ms.  A call whose vertices make more than kMaxBins bins
+// (67M vertices) keeps the atomics: its in-edges are few next to its vertices, and
+// a block's counts of the bins would no longer fit in LDS beside its tables.
+
+// Blocks of 256 threads take kBinTiles tiles of positions.
+constexpr int kBinTiles = 2;
+
+// The bin and record of each of a thread's positions in a tile (bin -1: past the
+// end).
+__device__ __forceinline__ void bin_items(const LayerArgs &A, const TileSegs &T,
+                                          const TilePairs &Q, const PairRange &R, int64_t tile,
+                                          int32_t (&bin)[kEdgeItems], uint32_t (&rec)[kEdgeItems]) {
+  EdgeItems I;
+  edge_items<2>(A, T, Q, R, tile, I);
+#pragma unroll
+  for (int k = 0; k < kEdgeItems; ++k) {
+    bin[k] = -1;
+    rec[k] = 0;
+    if (I.u[k] < 0) continue;
+    const int32_t b0 = T.n > 0 ? T.bin0[I.seg[k]]
+                               : int32_t(kBinsPerTile * A.tile_base[A.es[I.seg[k]].src_type]);
+    const uint32_t d = R.n > 0 ? uint32_t(Q.w[I.pair[k]]) : degree_code(A.pa.pdeg[I.pair[k]]);
+    bin[k] = b0 + int32_t(I.u[k] >> kBinBits);
+    rec[k] = uint32_t(I.u[k] & (kBinVerts - 1)) | (d << kBinBits);
+  }
+}
+
+// In-edges per bin.
+__global__ __launch_bounds__(256) void k_lw_bin_count(LayerArgs A) {
+  __shared__ TileSegs T;
+  __shared__ TilePairs Q;
+  extern __shared__ __align__(16) char bin_lds[];
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(bin_lds);
+  for (int b = threadIdx.x; b < A.n_bins; b += 256) cnt[b] = 0;
+  for (int x = 0; x < kBinTiles; ++x) {
+    const int64_t tile = int64_t(blockIdx.x) * kBinTiles + x;
+    if (tile >= A.n_edge_tiles) break;
+    __syncthreads();  // the counts are clear, and the tables free again
+    PairRange R;
+    tile_tables<2>(A, tile, T, Q, R);
+    int32_t bin[kEdgeItems];
+    uint32_t rec[kEdgeItems];
+    bin_items(A, T, Q, R, tile, bin, rec);
+#pragma unroll
+    for (int k = 0; k < kEdgeItems; ++k)
+      if (bin[k] >= 0) atomicAdd(cnt + bin[k], 1u);
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < A.n_bins; b += 256)
+    if (cnt[b]) atomicAdd(A.bin_edges + b, cnt[b]);
+}
+
+// Two exclusive scans over n values each in one block of 1024 threads: pa[i] of
+// a(i), pb[i] of b(i), and their totals at n.
+template <typename FA, typename FB>
+__device__ void scan_two(int64_t n, FA a, FB b, int64_t *pa, int64_t *pb) {
+  constexpr int kWaves = 1024 / kWave;
+  constexpr int kPer = 8;
+  __shared__ int64_t s_a[kWaves], s_b[kWaves];
+  const int wave = int(threadIdx.x) / kWave, lane = lane_id();
+  int64_t ca = 0, cb = 0;
+  for (int64_t c0 = 0; c0 < n; c0 += 1024 * kPer) {
+    const int64_t i0 = c0 + int64_t(threadIdx.x) * kPer;
+    int64_t xa[kPer], xb[kPer], ma = 0, mb = 0;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      xa[k] = i0 + k < n ? a(i0 + k) : 0;
+      xb[k] = i0 + k < n ? b(i0 + k) : 0;
+      ma += xa[k];
+      mb += xb[k];
+    }
+    const int64_t ia = wave_incl_scan_i64(ma), ib = wave_incl_scan_i64(mb);
+    if (lane == kWave - 1) {
+      s_a[wave] = ia;
+      s_b[wave] = ib;
+    }
+    __syncthreads();
+    int64_t ra = ca + ia - ma, rb = cb + ib - mb;
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) {
+        ra += s_a[w];
+        rb += s_b[w];
+      }
+      ca += s_a[w];
+      cb += s_b[w];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if (i0 + k < n) {
+        pa[i0 + k] = ra;
+        pb[i0 + k] = rb;
+      }
+      ra += xa[k];
+      rb += xb[k];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    pa[n] = ca;
+    pb[n] = cb;
+  }
+}
+
+// Where each bin's records start, and the room for its candidates.
+__global__ __launch_bounds__(1024) void k_lw_bin_starts(LayerArgs A) {
+  scan_two(
+      A.n_bins, [&](int64_t b) { return int64_t(A.bin_edges[b]); },
+      [&](int64_t b) { return min(int64_t(A.bin_edges[b]), kBinVerts); }, A.bin_rec, A.bin_cap);
+  __syncthreads();
+  for (int64_t b = threadIdx.x; b < A.n_bins; b += 1024) A.bin_at[b] = uint32_t(A.bin_rec[b]);
+}
+
+// The records, grouped by bin (in any order within one): a block counts its
+// in-edges per bin in LDS, takes room for them in each bin with one global atomic
+// and writes them.
+__global__ __launch_bounds__(256) void k_lw_bin_scatter(LayerArgs A) {
+  __shared__ TileSegs T;
+  __shared__ TilePairs Q;
+  extern __shared__ __align__(16) char bin_lds[];
+  uint32_t *cnt = reinterpret_cast<uint32_t *>(bin_lds);
+  for (int b = threadIdx.x; b < A.n_bins; b += 256) cnt[b] = 0;
+  int32_t bin[kBinTiles][kEdgeItems];
+  uint32_t rec[kBinTiles][kEdgeItems], rank[kBinTiles][kEdgeItems];
+#pragma unroll
+  for (int x = 0; x < kBinTiles; ++x) {
+    const int64_t tile = int64_t(blockIdx.x) * kBinTiles + x;
+    __syncthreads();  // the counts are clear, and the tables free again
+    if (tile < A.n_edge_tiles) {
+      PairRange R;
+      tile_tables<2>(A, tile, T, Q, R);
+      bin_items(A, T, Q, R, tile, bin[x], rec[x]);
+#pragma unroll
+      for (int k = 0; k < kEdgeItems; ++k)
+        rank[x][k] = bin[x][k] >= 0 ? atomicAdd(cnt + bin[x][k], 1u) : 0;
+    } else {
+#pragma unroll
+      for (int k = 0; k < kEdgeItems; ++k) {
+        bin[x][k] = -1;
+        rec[x][k] = rank[x][k] = 0;
+      }
+    }
+  }
+  __syncthreads();
+  for (int b = threadIdx.x; b < A.n_bins; b += 256)
+    if (cnt[b]) cnt[b] = atomicAdd(A.bin_at + b, cnt[b]);
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < kBinTiles; ++x)
+#pragma unroll
+    for (int k = 0; k < kEdgeItems; ++k)
+      if (bin[x][k] >= 0) A.rec[cnt[bin[x][k]] + rank[x][k]] = rec[x][k];
+}
+
+// A block per bin: the importance of its vertices summed in LDS, then its
+// candidates (sources of in-edges that are not in the frontier) in ascending ID
+// with the importance before them.  An in-edge of no importance sets its source's
+// top bit instead (the sums stay below 2^63: fewer than 2^31 in-edges of at most
+// 2^32).  A thread lists 16 consecutive vertices; the place of a vertex in its
+// group of 16 is turned by the group's number, so that the threads' reads spread
+// over the LDS banks.
+constexpr int kBinThreads = 512;
+constexpr int kBinPer = int(kBinVerts) / kBinThreads;
+static_assert(kBinPer == 16, "a thread lists half a frontier word");
+constexpr int kBinLoads = 8;
+__device__ __forceinline__ int bin_place(int v) { return v ^ ((v / kBinPer) & (kBinPer - 1)); }
+__global__ __launch_bounds__(kBinThreads) void k_lw_bin_sum(LayerArgs A) {
+  __shared__ unsigned long long acc[kBinVerts];
+  constexpr unsigned long long kMark = 1ull << 63;
+  constexpr int kWaves = kBinThreads / kWave;
+  const int64_t b = blockIdx.x;
+  const int64_t r0 = A.bin_rec[b], r1 = A.bin_rec[b + 1];
+  if (r0 == r1) {
+    if (threadIdx.x == 0) A.bin_n[b] = A.bin_w[b] = 0;
+    return;
+  }
+  for (int i = threadIdx.x; i < int(kBinVerts); i += kBinThreads) acc[i] = 0;
+  __syncthreads();
+  // (records loaded kBinLoads at a time: one by one, the block would wait on
+  // each load in turn)
+  for (int64_t r = r0 + threadIdx.x; r < r1; r += kBinLoads * kBinThreads) {
+    uint32_t x[kBinLoads];
+#pragma unroll
+    for (int k = 0; k < kBinLoads; ++k)
+      x[k] = r + k * kBinThreads < r1 ? load_global(A.rec + r + k * kBinThreads) : ~0u;
+#pragma unroll
+    for (int k = 0; k < kBinLoads; ++k) {
+      if (x[k] == ~0u) continue;  // (a record takes 30 bits)
+      const int at = bin_place(int(x[k] & uint32_t(kBinVerts - 1)));
+      const uint64_t w = code_weight(x[k] >> kBinBits);
+      if (w)
+        atomicAdd(acc + at, (unsigned long long)w);
+      else
+        atomicOr(acc + at, kMark);
+    }
+  }
+  __syncthreads();
+  const int v0 = int(threadIdx.x) * kBinPer;
+  const uint32_t front = A.fbits[b * (kBinVerts / 32) + v0 / 32] >> (v0 & 31);
+  int64_t n = 0, w = 0;
+  uint32_t cand = 0;
+  int64_t a[kBinPer];
+#pragma unroll
+  for (int k = 0; k < kBinPer; ++k) {
+    const unsigned long long x = acc[bin_place(v0 + k)];
+    a[k] = int64_t(x & ~kMark);
+    if (x != 0 && !((front >> k) & 1u)) {
+      cand |= 1u << k;
+      ++n;
+      w += a[k];
+    }
+  }
+  __syncthreads();  // the sums are read: their place holds the block scan
+  int64_t *s_n = reinterpret_cast<int64_t *>(acc), *s_w = s_n + kWaves;
+  const int wave = int(threadIdx.x) / kWave;
+  const int64_t in = wave_incl_scan_i64(n), iw = wave_incl_scan_i64(w);
+  if (lane_id() == kWave - 1) {
+    s_n[wave] = in;
+    s_w[wave] = iw;
+  }
+  __syncthreads();
+  int64_t at = A.bin_cap[b] + in - n, pre = iw - w;
+  int64_t tn = 0, tw = 0;
+  for (int x = 0; x < kWaves; ++x) {
+    if (x < wave) {
+      at += s_n[x];
+      pre += s_w[x];
+    }
+    tn += s_n[x];
+    tw += s_w[x];
+  }
+#pragma unroll
+  for (int k = 0; k < kBinPer; ++k) {
+    if (!((cand >> k) & 1u)) continue;
+    A.bin_cand_off[at] = v0 + k;
+    A.bin_cand_pre[at] = uint64_t(pre);
+    pre += a[k];
+    ++at;
+  }
+  if (threadIdx.x == 0) {
+    A.bin_n[b] = tn;
+    A.bin_w[b] = tw;
+  }
+}
+
+// Candidates and importance before each bin; the bins' in-edge counts are clear
+// for the next hop.
+__global__ __launch_bounds__(1024) void k_lw_bin_totals(LayerArgs A) {
+  scan_two(
+      A.n_bins, [&](int64_t b) { return A.bin_n[b]; }, [&](int64_t b) { return A.bin_w[b]; },
+      A.bin_n_pre, A.bin_w_pre);
+  for (int64_t b = threadIdx.x; b < A.n_bins; b += 1024) A.bin_edges[b] = 0;
+}
+
+// The last i in [lo, hi) with pre[i] <= x (pre non-decreasing, pre[lo] <= x).
+template <typename V>
+__device__ __forceinline__ int64_t last_not_above(const V *pre, int64_t lo, int64_t hi, V x) {
+  while (hi - lo > 1) {
+    const int64_t m = lo + (hi - lo) / 2;
+    if (pre[m] <= x)
+      lo = m;
+    else
+      hi = m;
+  }
+  return lo;
+}
+
+// k_lw_draw over the bins' candidates: a bin by its prefix, then a candidate in
+// it.  As in k_lw_draw, a candidate (or bin) of no importance shares the prefix of
+// the next one, and is never the last with a prefix not above r.
+__global__ __launch_bounds__(256) void k_lw_bin_draw(LayerArgs A) {
+  const int64_t n = A.draw_base[A.n_types];
+  for (int64_t x = gs_start(); x < n; x += gs_step()) {
+    const int t = find_segment(A.draw_base, A.n_types, x);
+    const int64_t k = x - A.draw_base[t];
+    const int64_t b0 = kBinsPerTile * A.tile_base[t], b1 = kBinsPerTile * A.tile_base[t + 1];
+    if (b0 == b1) continue;
+    int64_t b, c;
+    if (A.draws[t] < 0) {
+      if (k >= A.bin_n_pre[b1] - A.bin_n_pre[b0]) continue;
+      const int64_t y = A.bin_n_pre[b0] + k;
+      b = last_not_above(A.bin_n_pre, b0, b1, y);
+      c = A.bin_cap[b] + (y - A.bin_n_pre[b]);
+    } else {
+      const int copy = t / A.key_T;
+      const uint64_t sigma = A.sigmas[copy];
+      const int64_t w0 = A.bin_w_pre[b0];
+      const uint64_t total = uint64_t(A.bin_w_pre[b1] - w0);
+      if (total == 0) continue;
+      const U32x4 r4 = philox4x32_10(U32x4{uint32_t(k), uint32_t(uint64_t(k) >> 32),
+                                           0x40000000u | uint32_t(A.hop),
+                                           uint32_t(t - copy * A.key_T)},
+                                     uint32_t(sigma), uint32_t(sigma >> 32));
+      const uint64_t r = __umul64hi(uint64_t(r4.x) | (uint64_t(r4.y) << 32), total);
+      b = last_not_above(A.bin_w_pre, b0, b1, w0 + int64_t(r));
+      const uint64_t in = r - uint64_t(A.bin_w_pre[b] - w0);
+      c = last_not_above(A.bin_cand_pre, A.bin_cap[b], A.bin_cap[b] + A.bin_n[b], in);
+    }
+    A.ts[t].reached[(b - b0) * kBinVerts + A.bin_cand_off[c]] = 1;
   }
 }
 
@@ -582,6 +913,21 @@ hipError_t launch_lw_weights(const LayerArgs &A, hipStream_t stream) {
   return hipGetLastError();
 }
 
+hipError_t launch_lw_bins(const LayerArgs &A, hipStream_t stream) {
+  const size_t lds = sizeof(uint32_t) * size_t(A.n_bins);
+  const unsigned grid = unsigned((A.n_edge_tiles + kBinTiles - 1) / kBinTiles);
+  if (A.n_all > 0) {
+    hipLaunchKernelGGL(k_lw_tile_pairs, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);
+    hipLaunchKernelGGL(k_lw_bin_count, dim3(grid), dim3(256), lds, stream, A);
+  }
+  hipLaunchKernelGGL(k_lw_bin_starts, dim3(1), dim3(1024), 0, stream, A);
+  if (A.n_all > 0)
+    hipLaunchKernelGGL(k_lw_bin_scatter, dim3(grid), dim3(256), lds, stream, A);
+  hipLaunchKernelGGL(k_lw_bin_sum, dim3(unsigned(A.n_bins)), dim3(kBinThreads), 0, stream, A);
+  hipLaunchKernelGGL(k_lw_bin_totals, dim3(1), dim3(1024), 0, stream, A);
+  return hipGetLastError();
+}
+
 hipError_t launch_lw_prefix(const LayerArgs &A, hipStream_t stream) {
   const int64_t tiles = A.cand_tiles;
   if (tiles <= 0) return hipSuccess;
@@ -595,6 +941,10 @@ hipError_t launch_lw_prefix(const LayerArgs &A, hipStream_t stream) {
 hipError_t launch_lw_draw(const LayerArgs &A, hipStream_t stream) {
   const int64_t n = A.draw_threads;
   if (n <= 0) return hipSuccess;
+  if (A.n_bins > 0) {
+    hipLaunchKernelGGL(k_lw_bin_draw, dim3(grid_for(n, 256)), dim3(256), 0, stream, A);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_lw_draw, dim3(grid_for(n, 256)), dim3(256), 0, stream, A);
   return hipGetLastError();
 }

@@ -210,6 +210,7 @@ struct Workspace {
   Scratch targets;                 // edge-seeded calls: endpoints and exclusion tables
   Scratch lw_weight;               // layer-wise calls: importance per vertex (zero between uses)
   Scratch lw_edges, lw_cand;       // layer-wise calls: every in-edge of a hop; candidates
+  Scratch lw_bins;                 // layer-wise calls: in-edges per bin (zero between uses)
   uint32_t epoch = 0;              // look-back launches so far (mod kEpochLimit)
   // Recorded at the end of every call on that call's stream (`last`); the
   // next call on another stream waits for it.  An event must never outlive
@@ -414,6 +415,7 @@ void free_workspace(Workspace *w) {
   w->lw_weight.release();
   w->lw_edges.release();
   w->lw_cand.release();
+  w->lw_bins.release();
   if (w->hsmall) (void)hipHostFree(w->hsmall);
   if (w->htab) (void)hipHostFree(w->htab);
   delete w;
@@ -715,9 +717,15 @@ struct SampleRun {
   int32_t lw_hop = -1;
   int64_t *lw_eid = nullptr;
   int32_t *lw_srcl = nullptr, *lw_dstl = nullptr;
+  // bins of a hop with S in-edges, or 0: importance by global atomics
+  int64_t layer_bins(int64_t S) const {
+    const int64_t n = g->n_tiles * kBinsPerTile;
+    return n <= kMaxBins && S < (int64_t(1) << 31) ? n : 0;
+  }
   hg_status close_layer_edges();
   hg_status layer_hop(int32_t h, const HopView &hv, const HopView &nv, const PairArrays &pa,
-                      int64_t items, int64_t words, int64_t S, const std::vector<int64_t> &nF,
+                      int64_t items, int64_t words, int64_t S,
+                      const std::vector<int64_t> &etype_edges, const std::vector<int64_t> &nF,
                       const std::vector<int64_t> &cbound, int64_t *indptr_all,
                       int64_t *eid_all, int32_t *srcl_all, int32_t *dstl_all,
                       int64_t **src_slot, std::vector<int64_t *> &src_out, bool inline_ptrs);
@@ -1140,15 +1148,6 @@ hg_status SampleRun::run_layers(const int64_t *const *seeds, const int64_t *n_se
     }
     return HG_OK;
   }
-  // the importance array: one uint64 per vertex, zero between uses
-  const int64_t map_n = g->map_off[T];
-  if (!ws->lw_weight.ensure(sizeof(uint64_t) * size_t(std::max<int64_t>(map_n, 1)), stream))
-    return fail(HG_ENOMEM, "layer-wise: importance array");
-  if (ws->lw_weight.fresh &&
-      (e = launch_fill_u32(static_cast<uint32_t *>(ws->lw_weight.p),
-                           int64_t(ws->lw_weight.cap / sizeof(uint32_t)), 0u, stream)) !=
-          hipSuccess)
-    return fail_device(e, "fill");
   return hops(nF, P + 1);
 }
 
@@ -1175,6 +1174,7 @@ hg_status SampleRun::close_layer_edges() {
 // draws, the next frontier, and the kept in-edges into the block arrays.
 hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
                                const PairArrays &pa, int64_t items, int64_t words, int64_t S,
+                               const std::vector<int64_t> &etype_edges,
                                const std::vector<int64_t> &nF,
                                const std::vector<int64_t> &cbound, int64_t *indptr_all,
                                int64_t *eid_all, int32_t *srcl_all, int32_t *dstl_all,
@@ -1220,17 +1220,42 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
     h_draws[t] = k;
     h_ctile[t + 1] = h_ctile[t] + (cbound[t] + kLayerTile - 1) / kLayerTile;
     h_dbase[t + 1] = h_dbase[t] + (k < 0 ? cbound[t] : (cbound[t] > 0 ? k : 0));
-    h_wt[t] = static_cast<uint64_t *>(ws->lw_weight.p) + g->map_off[t];
+    h_wt[t] = nullptr;
   }
   A.cand_tiles = h_ctile[T];
   A.draw_threads = h_dbase[T];
+  A.n_bins = layer_bins(S);
+  A.fbits = ws->fbits;
   const int64_t scan_tiles = std::max(A.cand_tiles, A.n_edge_tiles) + 1;
   Carve ec;
   ec.add(&A.tile_pair, A.n_edge_tiles + 1);
   ec.add(&A.keep_bits, A.n_edge_tiles * (kEdgeTile / 64));
   ec.add(&A.keep_pre, A.n_edge_tiles * (kEdgeTile / 64));
   Carve cc;
+  if (A.n_bins > 0) {
+    // a type's bins have room for as many candidates as it has in-edges here, and
+    // vertices in its bins
+    std::vector<int64_t> per_type(T, 0);
+    for (int32_t i = 0; i < R; ++i) per_type[g->et[i].src] += etype_edges[i + 1] - etype_edges[i];
+    int64_t room = 0;
+    for (int32_t t = 0; t < T; ++t)
+      room += std::min(per_type[t],
+                       (g->tile_base[t + 1] - g->tile_base[t]) * kBinsPerTile * kBinVerts);
+    ec.add(&A.rec, S);
+    cc.add(&A.bin_cand_off, room);
+    cc.add(&A.bin_cand_pre, room);
+    cc.add(&A.bin_at, A.n_bins);
+    cc.add(&A.bin_rec, A.n_bins + 1);
+    cc.add(&A.bin_cap, A.n_bins + 1);
+    cc.add(&A.bin_n, A.n_bins);
+    cc.add(&A.bin_n_pre, A.n_bins + 1);
+    cc.add(&A.bin_w, A.n_bins);
+    cc.add(&A.bin_w_pre, A.n_bins + 1);
+  }
   for (int32_t t = 0; t < T; ++t) {
+    h_cand[t] = nullptr;
+    h_prefix[t] = nullptr;
+    if (A.n_bins > 0) continue;
     cc.add(&h_cand[t], cbound[t]);
     cc.add(&h_prefix[t], cbound[t]);
   }
@@ -1238,6 +1263,27 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
   cc.add(&A.tile_pre, scan_tiles);
   if (!ec.in_scratch(ws->lw_edges, stream) || !cc.in_scratch(ws->lw_cand, stream))
     return fail(HG_ENOMEM, "hop %d: layer-wise scratch", h);
+  if (A.n_bins > 0) {
+    // the bins' in-edge counts, zero between hops
+    if (!ws->lw_bins.ensure(sizeof(uint32_t) * size_t(A.n_bins), stream))
+      return fail(HG_ENOMEM, "hop %d: layer-wise scratch", h);
+    A.bin_edges = static_cast<uint32_t *>(ws->lw_bins.p);
+    if (ws->lw_bins.fresh &&
+        (e = launch_fill_u32(A.bin_edges, A.n_bins, 0u, stream)) != hipSuccess)
+      return fail_device(e, "fill");
+  } else {
+    // the importance array: one uint64 per vertex, zero between uses
+    const int64_t map_n = g->map_off[T];
+    if (!ws->lw_weight.ensure(sizeof(uint64_t) * size_t(std::max<int64_t>(map_n, 1)), stream))
+      return fail(HG_ENOMEM, "layer-wise: importance array");
+    if (ws->lw_weight.fresh &&
+        (e = launch_fill_u32(static_cast<uint32_t *>(ws->lw_weight.p),
+                             int64_t(ws->lw_weight.cap / sizeof(uint32_t)), 0u, stream)) !=
+            hipSuccess)
+      return fail_device(e, "fill");
+    for (int32_t t = 0; t < T; ++t)
+      h_wt[t] = static_cast<uint64_t *>(ws->lw_weight.p) + g->map_off[t];
+  }
   if ((e = upload(tab_off, tab_off + layer_table_bytes(T))) != hipSuccess)
     return fail_device(e, "layer table");
   char *dt = static_cast<char *>(ws->tab.p) + tab_off;
@@ -1255,24 +1301,30 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
                              reinterpret_cast<void *const *>(src_out.data()), T, stream)) !=
           hipSuccess)
     return fail_device(e, "source lists");
-  // 2. importance of the candidates, which marks them reached
-  reached_dirty = true;
-  wt_dirty = true;
-  if ((e = launch_lw_weights(A, stream)) != hipSuccess) return fail_device(e, "weights");
-  // 3. the candidates of each type in ascending ID (region H+2 lists them)
-  HopView cv = view(H + 2);
-  cv.src_out = A.cand;  // the list pointers of the hop's table
   int64_t ticketed = 0;
   uint32_t epoch;
-  if ((e = next_epoch(&epoch)) != hipSuccess ||
-      (e = launch_compact(cv, ws->d_ts, T, ws->reached, ws->fbits, g->d_tile_base, g->n_tiles, 0,
-                          ws->tile_sums, epoch, ticket_base, ws->dsmall, &ticketed, stream,
-                          true)) != hipSuccess)
-    return fail_device(e, "candidates");
-  ticket_base += uint64_t(ticketed);
-  // 4. their importance prefix per type (which zeroes the importance array)
-  if ((e = launch_lw_prefix(A, stream)) != hipSuccess) return fail_device(e, "prefix");
-  wt_dirty = false;
+  if (A.n_bins > 0) {
+    // 2-4. the candidates by bins, with their importance and its prefix
+    if ((e = launch_lw_bins(A, stream)) != hipSuccess) return fail_device(e, "bins");
+    reached_dirty = true;
+  } else {
+    // 2. importance of the candidates, which marks them reached
+    reached_dirty = true;
+    wt_dirty = true;
+    if ((e = launch_lw_weights(A, stream)) != hipSuccess) return fail_device(e, "weights");
+    // 3. the candidates of each type in ascending ID (region H+2 lists them)
+    HopView cv = view(H + 2);
+    cv.src_out = A.cand;  // the list pointers of the hop's table
+    if ((e = next_epoch(&epoch)) != hipSuccess ||
+        (e = launch_compact(cv, ws->d_ts, T, ws->reached, ws->fbits, g->d_tile_base, g->n_tiles,
+                            0, ws->tile_sums, epoch, ticket_base, ws->dsmall, &ticketed, stream,
+                            true)) != hipSuccess)
+      return fail_device(e, "candidates");
+    ticket_base += uint64_t(ticketed);
+    // 4. their importance prefix per type (which zeroes the importance array)
+    if ((e = launch_lw_prefix(A, stream)) != hipSuccess) return fail_device(e, "prefix");
+    wt_dirty = false;
+  }
   // 5. the draws set the reached flags of the drawn candidates
   if ((e = launch_lw_draw(A, stream)) != hipSuccess) return fail_device(e, "draw");
   // 6. the drawn vertices join the frontier: the source lists of the hop
@@ -1476,7 +1528,7 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
       return fail_device(e, "tables");
 
     if (layer_sizes) {
-      if ((st = layer_hop(h, hv, nv, pa, items, words, S, nF, cbound, indptr_all, eid_all, srcl_all,
+      if ((st = layer_hop(h, hv, nv, pa, items, words, S, eb, nF, cbound, indptr_all, eid_all, srcl_all,
                           dstl_all, src_slot, src_out, inline_ptrs)) != HG_OK)
         return st;
       for (int32_t t = 0; t < T; ++t) {

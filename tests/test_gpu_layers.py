@@ -284,3 +284,58 @@ def test_layer_edge_tiles(olib, total, pairs):
         _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, total, g=g)
         diffs = compare(ref, got, 1, 1, len(sizes))
         assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
+
+
+def bins_graph(n, degs, rng, near):
+    """One node type of n vertices; destination k has degs[k] in-edges, half of
+    them from vertices next to a multiple of 8192 when `near` (the bins' ends), the
+    others from anywhere."""
+    ends = np.unique(np.concatenate([np.arange(0, n, 8192) + d for d in (-1, 0, 1)]))
+    ends = ends[(ends >= 0) & (ends < n)]
+    idx = []
+    for k in degs:
+        a = rng.choice(ends, size=min(k // 2, ends.size), replace=False) if near else ends[:0]
+        rest = rng.choice(n, size=2 * k + 8, replace=False)
+        rest = rest[~np.isin(rest, a)][:k - a.size]
+        idx.append(np.sort(np.concatenate([a, rest])))
+    ip = np.concatenate([[0], np.cumsum(degs), np.full(n - len(degs), sum(degs))])
+    return [(0, 0, ip.astype(np.int64), np.concatenate(idx).astype(np.int64))]
+
+
+@pytest.mark.parametrize("n", [8191, 8192, 8193, 16384, 16385, 40_000])
+def test_layer_importance_bins(olib, n):
+    """The candidates' importance is summed a bin of 8192 vertices at a time: node
+    types that end on, before and after a bin and a bitmap tile (two bins), sources
+    at the bins' ends, candidates reached by several destinations."""
+    rng = np.random.default_rng(n)
+    degs = [min(3000, n // 3), 500, 40, 3, 1, 1, 0, 700]
+    ets = bins_graph(n, degs, rng, True)
+    g = gpu_graph([n], ets, [None])
+    seeds = [np.array([7, 0, 3, 1, 6, 2, 5, 4, n - 1])]
+    for sizes in ([[-1]], [[50]], [[2000], [9]]):
+        for sigma in (1, 2**50):
+            _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, sigma, g=g)
+            diffs = compare(ref, got, 1, 1, len(sizes))
+            assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
+
+
+def test_layer_more_bins_than_fit(olib):
+    """A bundle whose copies make more than 8192 bins sums the importance with
+    global atomics: each mini-batch equals its own call (binned) and two equal the
+    oracle."""
+    n, B = 2_120_000, 32  # 130 bitmap tiles of two bins each, per copy
+    rng = np.random.default_rng(5)
+    ets = bins_graph(n, [70_000, 3000, 3000, 40, 1, 5], rng, True)
+    g = gpu_graph([n], ets, [None])
+    host = oracle.HostGraph([(n, None)], ets, lib=olib)
+    sizes = [[300], [-1]]
+    seeds = [[rng.permutation(6)[:1 + b % 6].astype(np.int64)] for b in range(B)]
+    bl = g.sample_layers_bundle([gpu_seeds(s) for s in seeds], sizes, list(range(B)), gather=[])
+    for b in range(B):
+        got = result_dict(g, bl[b])
+        one = result_dict(g, g.sample_layers(gpu_seeds(seeds[b]), sizes, b))
+        diffs = compare(one, got, 1, 1, 2)
+        assert not diffs, f"batch {b}: " + "\n".join(diffs[:10])
+        if b in (5, 30):
+            diffs = compare(host.sample_layers(seeds[b], sizes, b), got, 1, 1, 2)
+            assert not diffs, f"batch {b} vs oracle: " + "\n".join(diffs[:10])
