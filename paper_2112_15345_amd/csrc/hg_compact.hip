@@ -20,10 +20,6 @@ namespace hg {
 
 namespace {
 
-__device__ __forceinline__ int64_t gs_step() {
-  return int64_t(gridDim.x) * blockDim.x;
-}
-
 unsigned grid_for(int64_t n, int threads, int64_t cap = 1 << 20) {
   int64_t b = (n + threads - 1) / threads;
   if (b < 1) b = 1;
@@ -261,8 +257,17 @@ __global__ __launch_bounds__(256) void k_relabel(HopView hv, HopView next, const
                                                  const int64_t *tile_base, const int64_t *small,
                                                  int32_t n_types, int32_t n_etypes,
                                                  int64_t n_edges, const int64_t *src_gid,
-                                                 int32_t *src_local, bool xcd) {
+                                                 int32_t *src_local, bool xcd,
+                                                 int64_t n_blocks, uint4 *clear,
+                                                 int64_t clear_vecs) {
   extern __shared__ __align__(16) char relabel_lds[];
+  if (int64_t(blockIdx.x) >= n_blocks) {  // the blocks past the edges' clear
+    const int64_t threads = (int64_t(gridDim.x) - n_blocks) * blockDim.x;
+    for (int64_t i = (int64_t(blockIdx.x) - n_blocks) * blockDim.x + threadIdx.x; i < clear_vecs;
+         i += threads)
+      clear[i] = uint4{0, 0, 0, 0};
+    return;
+  }
   if (blockIdx.x == 0)
     plan_next_hop(hv, next, es, tile_base, small, n_types, n_etypes);
   const int64_t *ebase = small + kSlotNew + n_types;
@@ -275,10 +280,10 @@ __global__ __launch_bounds__(256) void k_relabel(HopView hv, HopView next, const
     }
     __syncthreads();
   }
-  // the grid is a multiple of kXcds blocks, so that its blocks can be ordered
+  // n_blocks is a multiple of kXcds, so that the blocks can be ordered
   // per XCD (xcd_block): a mini-batch's map lines then stay in one L2
-  const int64_t step = gs_step();
-  for (int64_t j0 = xcd_block(blockIdx.x, gridDim.x, xcd) * blockDim.x + threadIdx.x;
+  const int64_t step = n_blocks * blockDim.x;
+  for (int64_t j0 = xcd_block(blockIdx.x, n_blocks, xcd) * blockDim.x + threadIdx.x;
        j0 < n_edges; j0 += kRelabelItems * step) {
     int64_t g[kRelabelItems];
     int32_t *m[kRelabelItems];
@@ -339,17 +344,22 @@ hipError_t launch_relabel(HopView hv, HopView next, const EtypeStatic *es,
                           const int64_t *tile_base, const int64_t *small,
                           int32_t n_types, int32_t n_etypes, int64_t n_edges,
                           const int64_t *src_gid, int32_t *src_local,
-                          hipStream_t stream, StageEv ev, bool xcd_order) {
+                          hipStream_t stream, StageEv ev, bool xcd_order, uint32_t *clear,
+                          int64_t clear_words) {
   // at least one block: block 0 plans the next hop
-  const unsigned grid =
-      unsigned(xcd_round(grid_for((n_edges + kRelabelItems - 1) / kRelabelItems, 256, 1 << 20)));
+  const int64_t blocks =
+      xcd_round(grid_for((n_edges + kRelabelItems - 1) / kRelabelItems, 256, 1 << 20));
+  const int64_t vecs = clear_words / 4;
+  const unsigned grid = unsigned(blocks + (vecs > 0 ? grid_for(vecs, 1024, 2048) : 0));
+  uint4 *clear_v = reinterpret_cast<uint4 *>(clear);
   if (n_etypes <= kRelabelMaxEtypes)
     launch_k(k_relabel<true>, dim3(grid), dim3(256), size_t(16) * (n_etypes + 1), stream,
              ev.start, ev.stop, hv, next, es, tile_base, small, n_types, n_etypes, n_edges,
-             src_gid, src_local, xcd_order);
+             src_gid, src_local, xcd_order, blocks, clear_v, vecs);
   else
     launch_k(k_relabel<false>, dim3(grid), dim3(256), 0, stream, ev.start, ev.stop, hv, next,
-             es, tile_base, small, n_types, n_etypes, n_edges, src_gid, src_local, xcd_order);
+             es, tile_base, small, n_types, n_etypes, n_edges, src_gid, src_local, xcd_order, blocks,
+             clear_v, vecs);
   return hipGetLastError();
 }
 

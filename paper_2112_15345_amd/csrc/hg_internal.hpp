@@ -234,6 +234,18 @@ hipError_t launch_pair_list(HopView hv, const NzType *nz, const int32_t *nz_et, 
                             Lookback lb, uint32_t epoch, uint64_t ticket_base, int64_t *small,
                             hipStream_t stream, StageEv ev);
 
+// A counting pass of one tile that publishes (host not NULL): its block ends with
+// what launch_publish does, copying the n readback slots to pinned host memory and
+// then writing seq to host[n].  A pass of several tiles leaves that to
+// launch_publish: its blocks would have to make their writes visible to the last
+// of them, and that (an L2 write-back each) cost more than the launch, at 9 tiles
+// (14.6 us against 11.1 + 4) as at 391 (63 against 25 + 4).
+struct Publish {
+  int64_t *host = nullptr;
+  int32_t n = 0;
+  uint64_t seq = 0;
+};
+
 // Counting pass over n_items >= P + 1 pair slots (P = pair_base[R]): per pair
 // its in-edge range; exclusive scans of kept edges, hub chunks, wavefront
 // pairs and hub flags; per-etype edge starts (ebase) and the hop totals into
@@ -242,7 +254,7 @@ int64_t count_tiles(int64_t n_items, bool active);
 hipError_t launch_count_scan(HopView hv, const EtypeStatic *es, int32_t n_etypes,
                              int32_t n_types, int64_t n_items, PairArrays pa,
                              Lookback lb, uint32_t epoch, uint64_t ticket_base,
-                             ExclView X, int64_t *small, hipStream_t stream,
+                             ExclView X, Publish pub, int64_t *small, hipStream_t stream,
                              StageEv ev = {});
 
 // The sampler, two launches.  First: block CSC entries and small take-all
@@ -386,12 +398,14 @@ hipError_t launch_lw_keep(const LayerArgs &A, hipStream_t stream);
 // src_local[j] = map_{src_type(e)}[src_gid[j]] for the edges of etype e,
 // which are [ebase[e], ebase[e+1]), ebase = small + kSlotNew + n_types.
 // Block 0 also writes the next hop's frontier sizes (this hop's plus its new
-// vertices) and pair layout into `next`.
+// vertices) and pair layout into `next`.  With clear_words, further blocks zero
+// that many words at `clear` (16-byte aligned, a multiple of four).
 hipError_t launch_relabel(HopView hv, HopView next, const EtypeStatic *es,
                           const int64_t *tile_base, const int64_t *small,
                           int32_t n_types, int32_t n_etypes, int64_t n_edges,
                           const int64_t *src_gid, int32_t *src_local,
-                          hipStream_t stream, StageEv ev = {}, bool xcd_order = false);
+                          hipStream_t stream, StageEv ev = {}, bool xcd_order = false,
+                          uint32_t *clear = nullptr, int64_t clear_words = 0);
 
 // Fill helpers (kernels, so that they are safe under graph capture).
 // One block copies small[0..n) to pinned host memory host[0..n) and then
@@ -408,6 +422,15 @@ hipError_t launch_fill_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t strea
 // the host link (no DMA copy on the stream); dst and src 8-byte aligned, else
 // hipErrorInvalidValue.  The host must not rewrite src until the kernel ran.
 hipError_t launch_upload(void *dst, const void *src, int64_t n, hipStream_t stream);
+
+// launch_upload of n bytes and then launch_insert_frontier over hv, whose tables
+// are among them: one launch of one block for small calls (at most kStartBytes and
+// kStartSeeds: with 4096 seeds the block takes 24 us, and the two launches 7), else
+// both.
+constexpr int64_t kStartBytes = 16384;
+constexpr int64_t kStartSeeds = 1024;
+hipError_t launch_start(void *dst, const void *src, int64_t n, HopView hv, const TypeStatic *ts,
+                        int32_t n_types, int64_t total, int64_t *small, hipStream_t stream);
 
 // The non-empty mask of one destination type: for v < n, bit k of row v
 // (words per row) is set when indptrs[k][v + 1] > indptrs[k][v]; indptrs is a

@@ -685,6 +685,7 @@ struct SampleRun {
   // zero again once a clearing publish has run
   bool reached_dirty = false;
   bool small_clean = false;
+  bool fbits_clean = false;  // the frontier bits have been cleared
 
   // an edge-seeded call: its batch, the excluded edges and its extra tables
   // (a region for the seeds' compaction after regions 0 .. H+1, then the
@@ -835,7 +836,7 @@ struct SampleRun {
                               stream);
         (void)launch_fill_u32(ws->rbits, g->n_tiles * kTile, 0u, stream);
       }
-      (void)launch_fill_u32(ws->fbits, g->n_tiles * kTile, 0u, stream);
+      if (!fbits_clean) (void)launch_fill_u32(ws->fbits, g->n_tiles * kTile, 0u, stream);
       if (!small_clean)
         (void)launch_fill_i32(reinterpret_cast<int32_t *>(ws->dsmall),
                               2 * int64_t(small_slots(g)), 0, stream);
@@ -919,13 +920,11 @@ hg_status SampleRun::run(const int64_t *const *seeds, const int64_t *n_seeds) {
   // (the readback slots are zero: a new workspace starts so, and every call
   // clears them when it ends)
   std::memcpy(ws->htab, sigmas.data(), sizeof(uint64_t) * sigmas.size());
-  if ((e = upload(0, sig_bytes + size_t(H + 1) * lay.size)) != hipSuccess)
-    return fail_device(e, "start");
   int64_t total = 0;
   for (int64_t n : nF) total += n;
-  if ((e = launch_insert_frontier(view(0), ws->d_ts, T, total, ws->dsmall, stream)) !=
-      hipSuccess)
-    return fail_device(e, "insert seeds");
+  if ((e = launch_start(ws->tab.p, ws->htab, int64_t(sig_bytes + size_t(H + 1) * lay.size),
+                        view(0), ws->d_ts, T, total, ws->dsmall, stream)) != hipSuccess)
+    return fail_device(e, "start");
   if (H == 0) {
     if ((e = sync_small(true)) != hipSuccess) return fail_device(e, "sync");
     hg_status st = check_flags("seeds");
@@ -1122,12 +1121,11 @@ hg_status SampleRun::run_layers(const int64_t *const *seeds, const int64_t *n_se
     }
   }
   std::memcpy(ws->htab, sigmas.data(), sizeof(uint64_t) * sigmas.size());
-  if ((e = upload(0, table_bytes())) != hipSuccess) return fail_device(e, "start");
   int64_t total = 0;
   for (int64_t n : nF) total += n;
-  if ((e = launch_insert_frontier(view(0), ws->d_ts, T, total, ws->dsmall, stream)) !=
-      hipSuccess)
-    return fail_device(e, "insert seeds");
+  if ((e = launch_start(ws->tab.p, ws->htab, int64_t(table_bytes()), view(0), ws->d_ts, T, total,
+                        ws->dsmall, stream)) != hipSuccess)
+    return fail_device(e, "start");
   if (H == 0) {
     if ((e = sync_small(true)) != hipSuccess) return fail_device(e, "sync");
     hg_status st = check_flags("seeds");
@@ -1432,13 +1430,17 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
       ticket_base += uint64_t(list_tiles);
       ev_count.start = nullptr;
     }
+    Publish pub;
+    if (tiles == 1)
+      pub = Publish{ws->hsmall, int32_t(small_slots(g)), ++ws->publish_seq};
     if ((e = next_epoch(&epoch)) != hipSuccess ||
-        (e = launch_count_scan(hv, ws->d_es, R, T, n_items, pa, lb, epoch, ticket_base, X,
+        (e = launch_count_scan(hv, ws->d_es, R, T, n_items, pa, lb, epoch, ticket_base, X, pub,
                                ws->dsmall, stream, ev_count)) != hipSuccess)
       return fail_device(e, "count");
     if (!active) ticket_base += uint64_t(tiles);
     // wait: this hop's sizes (and the previous hop's new-vertex counts)
-    if ((e = sync_small()) != hipSuccess) return fail_device(e, "sync");
+    if ((e = pub.host ? wait_published(pub.seq) : sync_small()) != hipSuccess)
+      return fail_device(e, "sync");
     hg_status st = check_flags("count");
     if (st != HG_OK) return st;
     const int64_t *hs = ws->hsmall;
@@ -1569,10 +1571,15 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
       return fail_device(e, "compact");
     ticket_base += uint64_t(ticketed);
     reached_dirty = false;
+    // the last hop's relabel clears the frontier bits for the next call: nothing
+    // after it reads them
+    const bool last = h == H - 1;
     if ((e = launch_relabel(hv, nv, ws->d_es, g->d_tile_base, ws->dsmall, T, R, S, gid_tmp,
-                            srcl_all, stream, stage_ev(h, HG_STAGE_RELABEL),
-                            xcd_order)) != hipSuccess)
+                            srcl_all, stream, stage_ev(h, HG_STAGE_RELABEL), xcd_order,
+                            last ? ws->fbits : nullptr, last ? g->n_tiles * kTile : 0)) !=
+        hipSuccess)
       return fail_device(e, "relabel");
+    fbits_clean = last;
     // the map now holds the source lists of this hop, which are region h+1's
     // frontier; the relabel pass wrote their sizes into that region
 

@@ -84,27 +84,46 @@ __device__ __forceinline__ bool is_excluded(const ExclView &X, int e, uint64_t e
 
 // ---- frontier map maintenance --------------------------------------------
 
+// Item x of the hop-0 frontier.
+__device__ __forceinline__ void insert_seed(const HopView &hv, const TypeStatic *ts,
+                                            int32_t n_types, int64_t x, int32_t *err) {
+  int64_t first;
+  const int t = type_of(hv.nF, n_types, x, &first);
+  const int64_t i = x - first;
+  if (i >= hv.nF[t]) return;
+  const int64_t v = hv.frontier[t][i];
+  if (v < 0 || v >= ts[t].num_nodes) {
+    atomicOr(err, kErrSeedRange);
+    return;
+  }
+  // the first seed to set the frontier bit owns the vertex; a later one
+  // is a repeat
+  const uint32_t bit = 1u << (v & 31);
+  if (atomicOr(ts[t].fbits + (v >> 5), bit) & bit)
+    atomicOr(err, kErrSeedRepeat);
+  else
+    ts[t].map[v] = int32_t(i);
+}
+
 __global__ void k_insert_frontier(HopView hv, const TypeStatic *ts,
                                   int32_t n_types, int64_t total, int64_t *small) {
   int32_t *err = reinterpret_cast<int32_t *>(small + kSlotErr);
-  for (int64_t x = grid_stride_start(); x < total; x += grid_stride_step()) {
-    int64_t first;
-    const int t = type_of(hv.nF, n_types, x, &first);
-    const int64_t i = x - first;
-    if (i >= hv.nF[t]) continue;
-    const int64_t v = hv.frontier[t][i];
-    if (v < 0 || v >= ts[t].num_nodes) {
-      atomicOr(err, kErrSeedRange);
-      continue;
-    }
-    // the first seed to set the frontier bit owns the vertex; a later one
-    // is a repeat
-    const uint32_t bit = 1u << (v & 31);
-    if (atomicOr(ts[t].fbits + (v >> 5), bit) & bit)
-      atomicOr(err, kErrSeedRepeat);
-    else
-      ts[t].map[v] = int32_t(i);
-  }
+  for (int64_t x = grid_stride_start(); x < total; x += grid_stride_step())
+    insert_seed(hv, ts, n_types, x, err);
+}
+
+// The start of a small call in one block: its tables, read over the host link, and
+// then the seeds, whose sizes and pointers are among them.
+constexpr int kStartThreads = 1024;
+__global__ __launch_bounds__(kStartThreads) void k_start(uint64_t *dst, const uint64_t *src,
+                                                         int32_t words, HopView hv,
+                                                         const TypeStatic *ts, int32_t n_types,
+                                                         int64_t total, int64_t *small) {
+  for (int i = threadIdx.x; i < words; i += kStartThreads) dst[i] = src[i];
+  __syncthreads();  // the block's stores are visible to it
+  int32_t *err = reinterpret_cast<int32_t *>(small + kSlotErr);
+  for (int64_t x = threadIdx.x; x < total; x += kStartThreads)
+    insert_seed(hv, ts, n_types, x, err);
 }
 
 // ---- counting pass ---------------------------------------------------------
@@ -252,6 +271,20 @@ struct CountView {
   __device__ int32_t fanout(int e) const { return kStaged ? t->fanout[e] : hv->fanout[e]; }
 };
 
+// Copies the n readback slots to host memory, then sets the flag word host[n] to
+// `seq`: a host that sees `seq` there reads the slots as they are at this point.
+// Every thread of the block calls it.
+__device__ __forceinline__ void publish_slots(const int64_t *small, int64_t *host, int32_t n,
+                                              uint64_t seq) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x)
+    host[i] = small[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(host + n), seq, __ATOMIC_RELEASE,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Thread i of a tile owns kPairItems consecutive items: pairs, or (kActive)
 // active pairs.  The edge type of a pair comes from the (staged) table, an
 // active pair's from the list; the frontier vertices of all items are loaded
@@ -262,7 +295,7 @@ template <bool kStaged, int kPairItems, bool kActive>
 __global__ __launch_bounds__(kTileThreads) void k_count_scan(
     HopView hv, const EtypeStatic *es, int32_t n_etypes, int32_t n_types,
     int64_t n_items, PairArrays pa, Lookback lb, uint32_t epoch,
-    uint64_t ticket_base, ExclView X, int64_t *small) {
+    uint64_t ticket_base, ExclView X, Publish pub, int64_t *small) {
   __shared__ int64_t lds[16];
   extern __shared__ __align__(16) char count_lds[];
   constexpr int64_t kPerTile = int64_t(kTileThreads) * kPairItems;
@@ -452,6 +485,10 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
     small[kSlotChunks] = pre[1];
     small[kSlotWaves] = pre[2];
     small[kSlotHubs] = pre[3];
+  }
+  if (pub.host) {  // the only block: its own writes, and those of earlier launches
+    __syncthreads();
+    publish_slots(small, pub.host, pub.n, pub.seq);
   }
 }
 
@@ -1442,17 +1479,10 @@ __global__ __launch_bounds__(256) void k_philox_rate(uint32_t k0, uint32_t k1, u
 
 // ---- host handshake -----------------------------------------------------------
 
-// Copies the n readback slots to host memory, then sets the flag word
-// host[n] to `seq`: a host that sees `seq` there reads the slots as they are
-// at this point of the stream (every earlier kernel has finished).
 __global__ __launch_bounds__(256) void k_publish(int64_t *small, int64_t *host,
                                                  int32_t n, uint64_t seq, bool clear) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) host[i] = small[i];
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0)
-    __hip_atomic_store(reinterpret_cast<uint64_t *>(host + n), seq, __ATOMIC_RELEASE,
-                       __HIP_MEMORY_SCOPE_SYSTEM);
+  // (every earlier kernel has finished)
+  publish_slots(small, host, n, seq);
   // the call is over: its readback slots start the next call at zero (each
   // thread clears the slots it copied)
   if (clear)
@@ -1512,23 +1542,25 @@ int64_t count_tiles(int64_t n_items, bool active) {
 template <bool kStaged, int kItems, bool kActive>
 void count_launch(HopView hv, const EtypeStatic *es, int32_t n_etypes, int32_t n_types,
                   int64_t n_items, PairArrays pa, Lookback lb, uint32_t epoch,
-                  uint64_t ticket_base, ExclView X, int64_t *small, hipStream_t stream,
-                  StageEv ev) {
+                  uint64_t ticket_base, ExclView X, Publish pub, int64_t *small,
+                  hipStream_t stream, StageEv ev) {
   const size_t lds = kStaged ? CountTable::bytes(n_etypes) : 0;
   launch_k(k_count_scan<kStaged, kItems, kActive>, dim3(unsigned(count_tiles(n_items, kActive))),
            dim3(kTileThreads), lds, stream, ev.start, ev.stop, hv, es, n_etypes, n_types,
-           n_items, pa, lb, epoch, ticket_base, X, small);
+           n_items, pa, lb, epoch, ticket_base, X, pub, small);
 }
 
 hipError_t launch_count_scan(HopView hv, const EtypeStatic *es, int32_t n_etypes,
                              int32_t n_types, int64_t n_items, PairArrays pa,
                              Lookback lb, uint32_t epoch, uint64_t ticket_base,
-                             ExclView X, int64_t *small, hipStream_t stream, StageEv ev) {
+                             ExclView X, Publish pub, int64_t *small, hipStream_t stream,
+                             StageEv ev) {
   const bool staged = n_etypes <= kCountMaxEtypes;
   const bool active = pa.act_pair != nullptr;
   const bool large = count_items(n_items, false) == kPairItemsLarge;
   auto go = [&](auto launch) {
-    launch(hv, es, n_etypes, n_types, n_items, pa, lb, epoch, ticket_base, X, small, stream, ev);
+    launch(hv, es, n_etypes, n_types, n_items, pa, lb, epoch, ticket_base, X, pub, small, stream,
+           ev);
   };
   if (active && staged)
     go(count_launch<true, kPairItemsActive, true>);
@@ -1653,6 +1685,20 @@ hipError_t launch_upload(void *dst, const void *src, int64_t n, hipStream_t stre
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_upload, dim3(grid_for((n >> 3) + 1, 256, 64)), dim3(256), 0, stream,
                      static_cast<uint8_t *>(dst), static_cast<const uint8_t *>(src), n);
+  return hipGetLastError();
+}
+
+hipError_t launch_start(void *dst, const void *src, int64_t n, HopView hv, const TypeStatic *ts,
+                        int32_t n_types, int64_t total, int64_t *small, hipStream_t stream) {
+  const bool words = ((reinterpret_cast<uintptr_t>(dst) | reinterpret_cast<uintptr_t>(src) |
+                       uint64_t(n)) & 7) == 0;
+  if (n <= 0 || n > kStartBytes || total > kStartSeeds || !words) {
+    hipError_t e = launch_upload(dst, src, n, stream);
+    return e == hipSuccess ? launch_insert_frontier(hv, ts, n_types, total, small, stream) : e;
+  }
+  hipLaunchKernelGGL(k_start, dim3(1), dim3(kStartThreads), 0, stream,
+                     static_cast<uint64_t *>(dst), static_cast<const uint64_t *>(src),
+                     int32_t(n / 8), hv, ts, n_types, total, small);
   return hipGetLastError();
 }
 

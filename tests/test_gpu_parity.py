@@ -441,3 +441,36 @@ def test_hub_equal_keys(olib, deg, K, bits):
                                   sigma, bits)
         diffs = compare(ref, got, 1, 1, 1)
         assert not diffs, f"sigma {sigma}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("n", [1, 510, 511, 512, 513, 1023, 1024, 1025, 1500])
+def test_small_call_limits(olib, n):
+    """Seeds on and around the limits of a one-block start (1024) and of a
+    counting pass that publishes its own sizes (one tile: 511 pairs and the end),
+    over two hops and again after calls that failed, which leave the frontier bits
+    to be cleared."""
+    rng = np.random.default_rng(n)
+    nn = [1600, 900]
+    ets = []
+    for s, d in ((0, 0), (1, 0), (0, 1)):
+        deg = rng.integers(0, 9, size=nn[d])
+        idx = [np.sort(rng.choice(nn[s], size=k, replace=False)) for k in deg]
+        ets.append((s, d, np.concatenate([[0], np.cumsum(deg)]).astype(np.int64),
+                    np.concatenate(idx).astype(np.int64)))
+    g = gpu_graph(nn, ets, [None, None])
+    host = oracle.HostGraph([(k, None) for k in nn], ets, lib=olib)
+    fan = [[3, 2, 4], [2, 0, -1]]
+    for split in (n, n // 2):
+        seeds = [rng.choice(nn[0], size=split, replace=False).astype(np.int64),
+                 rng.choice(nn[1], size=min(n - split, 900), replace=False).astype(np.int64)]
+        ref = host.sample_blocks(seeds, fan, n)
+        for again in range(2):
+            diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(seeds), fan, n)), 2, 3, 2)
+            assert not diffs, f"split {split} call {again}: " + "\n".join(diffs[:10])
+            for bad in (nn[0], -1, seeds[0][0] if split > 1 else nn[0]):
+                wrong = [seeds[0].copy(), seeds[1]]
+                if split:
+                    wrong[0][-1] = bad
+                    with pytest.raises(hg.HGError) as ex:
+                        g.sample_blocks(gpu_seeds(wrong), fan, n)
+                    assert ex.value.status == hg.HG_EINVAL
