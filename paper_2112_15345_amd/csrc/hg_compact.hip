@@ -73,6 +73,13 @@ __device__ __forceinline__ TileWords tile_words(const CompactArgs &A, int64_t ti
   return TileWords{uint2{pack16(r0) | (pack16(r1) << 16), pack16(r2) | (pack16(r3) << 16)},
                    front};
 }
+// A lane's value on every lane, in scalar registers.
+__device__ __forceinline__ int64_t uniform_from(int64_t x, int lane) {
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint64_t(x)), lane));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint64_t(x) >> 32), lane));
+  return int64_t((uint64_t(hi) << 32) | lo);
+}
+
 // Clears the thread's reached bytes or bits (when any is set).
 __device__ __forceinline__ void clear_reached(const CompactArgs &A, int64_t tile,
                                               const TileWords &tw) {
@@ -176,29 +183,52 @@ __global__ __launch_bounds__(kScanThreads) void k_bits_scan(CompactArgs A) {
 
 // Gives the new vertices of the thread's share of a tile (the first has local
 // ID `local`) their local IDs, adds them to the frontier bits and clears the
-// reached bits.
+// reached bits.  All threads of a wavefront call it.  Where many of its vertices
+// are new, the wavefront takes its 64 shares of 64 vertices one after the other, a
+// lane per vertex, so that the map entries and the listed IDs of a share are
+// written together: lanes that each write their own share's vertices make every
+// store touch up to 64 lines.  Where few are, those lanes are done in a few
+// stores.  A share taken together costs about 35 cycles, a round of stores of n
+// lanes about 2 n and not less than those: together it is when some share has more
+// new vertices than there are shares with any, or than 17.  (Academic graph, second
+// hop, 16 mini-batches, 3.7M new vertices of 31M: 72 us by lanes, 48 together;
+// first hop, 0.25M: 13 by lanes, 19 together.)
+constexpr int kTogetherFrom = 17;
 __device__ __forceinline__ void assign_bits(const CompactArgs &A, int t, int64_t first,
                                             int64_t tile, const TileWords &tw, int64_t local) {
   clear_reached(A, tile, tw);
   const uint2 ab = tw.fresh();
-  if ((ab.x | ab.y) == 0) return;
-  if (!A.collect)
+  const uint64_t shares = __ballot((ab.x | ab.y) != 0);
+  if (shares == 0) return;
+  if ((ab.x | ab.y) != 0 && !A.collect)
     *reinterpret_cast<uint2 *>(A.fbits + tile * kTile + threadIdx.x * kTileItems) =
         uint2{tw.front.x | ab.x, tw.front.y | ab.y};
   int32_t *map = A.ts[t].map;
   int64_t *out = A.hv.src_out[t];
-  const uint32_t words[kTileItems] = {ab.x, ab.y};
   const int64_t v0 = ((tile - first) * kTile + threadIdx.x * kTileItems) * 32;
-#pragma unroll
-  for (int k = 0; k < kTileItems; ++k) {
-    uint32_t m = words[k];
-    while (m) {
-      const int bit = __ffs(m) - 1;
-      m &= m - 1;
-      const int64_t v = v0 + k * 32 + bit;
+  const int many = min(kTogetherFrom, __popcll(shares));
+  if (__ballot(__popc(ab.x) + __popc(ab.y) > many) == 0) {
+    uint64_t m = uint64_t(ab.x) | (uint64_t(ab.y) << 32);
+    for (; m; m &= m - 1) {
+      const int64_t v = v0 + (__ffsll((unsigned long long)m) - 1);
       if (!A.collect) map[v] = int32_t(local);
       out[local] = v;
       ++local;
+    }
+    return;
+  }
+  const int lane = lane_id();
+  const uint64_t below = lanes_below();
+  const int64_t w0 = v0 - lane * (kTileItems * 32);  // the wavefront's first vertex
+  for (uint64_t m = shares; m; m &= m - 1) {
+    const int from = __ffsll((unsigned long long)m) - 1;
+    const uint64_t w = uint64_t(uint32_t(__builtin_amdgcn_readlane(int(ab.x), from))) |
+                       (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(ab.y), from))) << 32);
+    const int64_t at = uniform_from(local, from) + __popcll(w & below);
+    const int64_t v = w0 + from * (kTileItems * 32) + lane;
+    if ((w >> lane) & 1) {
+      if (!A.collect) map[v] = int32_t(at);
+      out[at] = v;
     }
   }
 }
@@ -245,14 +275,20 @@ __global__ __launch_bounds__(kTileThreads) void k_bits_single(CompactArgs A, uin
   assign_bits(A, t, first, tile, tw, A.hv.nF[t] + ex[0] + pre);
 }
 
-// Edge types whose edge starts and source maps the relabel stages in LDS.
-constexpr int kRelabelMaxEtypes = 2048;
-constexpr int kRelabelItems = 1;
+// Edges per thread of the relabel: four once that leaves eight blocks a CU, else
+// one, since the map's random reads are spread over the CUs by the blocks (25k
+// edges: 3.9 us with one, 6.0 with four; 7M: 64 and 59).
+constexpr int64_t kRelabelLargeFrom = int64_t(2048) * 1024;
 
-// src_local[j] = map of edge j's source type at src_gid[j].  The etype of an
-// edge is found by binary search over the edge starts (in LDS when staged);
-// each thread looks up kRelabelItems edges at once.
-template <bool kStaged>
+// src_local[j] = map of edge j's source type at src_gid[j].  A block takes
+// kRelabelTile consecutive edges; the edge types of its first and last edge are
+// found by all its threads at once (one round of loads and a barrier), and in a
+// block of one edge type, as most are, no edge looks for its own.  Bound by
+// the map entries' random reads: a block of 256 edges that staged every edge start
+// in LDS and searched them for each edge waited on its steps for 80% of its time
+// (75 us in the academic graph's second hop in bundles of 16, 7M edges, against
+// 59).
+template <int kRelabelItems>
 __global__ __launch_bounds__(256) void k_relabel(HopView hv, HopView next, const EtypeStatic *es,
                                                  const int64_t *tile_base, const int64_t *small,
                                                  int32_t n_types, int32_t n_etypes,
@@ -260,7 +296,7 @@ __global__ __launch_bounds__(256) void k_relabel(HopView hv, HopView next, const
                                                  int32_t *src_local, bool xcd,
                                                  int64_t n_blocks, uint4 *clear,
                                                  int64_t clear_vecs) {
-  extern __shared__ __align__(16) char relabel_lds[];
+  constexpr int64_t kRelabelTile = 256 * kRelabelItems;
   if (int64_t(blockIdx.x) >= n_blocks) {  // the blocks past the edges' clear
     const int64_t threads = (int64_t(gridDim.x) - n_blocks) * blockDim.x;
     for (int64_t i = (int64_t(blockIdx.x) - n_blocks) * blockDim.x + threadIdx.x; i < clear_vecs;
@@ -271,39 +307,56 @@ __global__ __launch_bounds__(256) void k_relabel(HopView hv, HopView next, const
   if (blockIdx.x == 0)
     plan_next_hop(hv, next, es, tile_base, small, n_types, n_etypes);
   const int64_t *ebase = small + kSlotNew + n_types;
-  int64_t *s_eb = reinterpret_cast<int64_t *>(relabel_lds);
-  int32_t **s_map = reinterpret_cast<int32_t **>(s_eb + n_etypes + 1);
-  if (kStaged) {
-    for (int e = threadIdx.x; e <= n_etypes; e += blockDim.x) {
-      s_eb[e] = ebase[e];
-      if (e < n_etypes) s_map[e] = es[e].src_map;
-    }
-    __syncthreads();
-  }
   // n_blocks is a multiple of kXcds, so that the blocks can be ordered
   // per XCD (xcd_block): a mini-batch's map lines then stay in one L2
-  const int64_t step = n_blocks * blockDim.x;
-  for (int64_t j0 = xcd_block(blockIdx.x, n_blocks, xcd) * blockDim.x + threadIdx.x;
-       j0 < n_edges; j0 += kRelabelItems * step) {
+  for (int64_t blk = xcd_block(blockIdx.x, n_blocks, xcd); blk * kRelabelTile < n_edges;
+       blk += n_blocks) {
+    const int64_t j0 = blk * kRelabelTile;
+    const int64_t j1 = j0 + kRelabelTile < n_edges ? j0 + kRelabelTile : n_edges;
     int64_t g[kRelabelItems];
-    int32_t *m[kRelabelItems];
 #pragma unroll
     for (int u = 0; u < kRelabelItems; ++u) {
-      const int64_t j = j0 + u * step;
-      g[u] = 0;
-      m[u] = nullptr;
-      if (j < n_edges) {
-        g[u] = src_gid[j];
-        const int e = find_segment(kStaged ? s_eb : ebase, n_etypes, j);
-        m[u] = kStaged ? s_map[e] : es[e].src_map;
+      const int64_t j = j0 + u * 256 + threadIdx.x;
+      g[u] = j < j1 ? load_global(src_gid + j) : 0;
+    }
+    // the thread whose edge type holds the first (last) edge says so
+    __shared__ int s_e0, s_e1;
+    __shared__ const int32_t *s_map;
+    for (int e = threadIdx.x; e < n_etypes; e += 256) {
+      const int64_t start = ebase[e], end = ebase[e + 1];
+      const int32_t *map = es[e].src_map;
+      if (start <= j0 && j0 < end) {
+        s_e0 = e;
+        s_map = map;
+      }
+      if (start < j1 && j1 <= end) s_e1 = e;
+    }
+    __syncthreads();
+    const int e0 = s_e0, e1 = s_e1;
+    const int32_t *map = s_map;
+    __syncthreads();  // they are written again for the next tile
+    int32_t l[kRelabelItems];
+    if (e0 == e1) {
+#pragma unroll
+      for (int u = 0; u < kRelabelItems; ++u)
+        l[u] = j0 + u * 256 + threadIdx.x < j1 ? load_global(map + g[u]) : 0;
+    } else {
+#pragma unroll
+      for (int u = 0; u < kRelabelItems; ++u) {
+        const int64_t j = j0 + u * 256 + threadIdx.x;
+        l[u] = 0;
+        if (j < j1) {
+          // ebase[e0] <= j0 <= j < ebase[e1 + 1]
+          const int e = e0 + find_segment(ebase + e0, e1 + 1 - e0, j);
+          l[u] = load_global(es[e].src_map + g[u]);
+        }
       }
     }
-    int32_t l[kRelabelItems];
 #pragma unroll
-    for (int u = 0; u < kRelabelItems; ++u) l[u] = m[u] ? m[u][g[u]] : 0;
-#pragma unroll
-    for (int u = 0; u < kRelabelItems; ++u)
-      if (m[u]) src_local[j0 + u * step] = l[u];
+    for (int u = 0; u < kRelabelItems; ++u) {
+      const int64_t j = j0 + u * 256 + threadIdx.x;
+      if (j < j1) src_local[j] = l[u];
+    }
   }
 }
 
@@ -347,19 +400,13 @@ hipError_t launch_relabel(HopView hv, HopView next, const EtypeStatic *es,
                           hipStream_t stream, StageEv ev, bool xcd_order, uint32_t *clear,
                           int64_t clear_words) {
   // at least one block: block 0 plans the next hop
-  const int64_t blocks =
-      xcd_round(grid_for((n_edges + kRelabelItems - 1) / kRelabelItems, 256, 1 << 20));
+  const bool large = n_edges >= kRelabelLargeFrom;
+  const int64_t blocks = xcd_round(grid_for(n_edges, large ? 1024 : 256));
   const int64_t vecs = clear_words / 4;
   const unsigned grid = unsigned(blocks + (vecs > 0 ? grid_for(vecs, 1024, 2048) : 0));
-  uint4 *clear_v = reinterpret_cast<uint4 *>(clear);
-  if (n_etypes <= kRelabelMaxEtypes)
-    launch_k(k_relabel<true>, dim3(grid), dim3(256), size_t(16) * (n_etypes + 1), stream,
-             ev.start, ev.stop, hv, next, es, tile_base, small, n_types, n_etypes, n_edges,
-             src_gid, src_local, xcd_order, blocks, clear_v, vecs);
-  else
-    launch_k(k_relabel<false>, dim3(grid), dim3(256), 0, stream, ev.start, ev.stop, hv, next,
-             es, tile_base, small, n_types, n_etypes, n_edges, src_gid, src_local, xcd_order, blocks,
-             clear_v, vecs);
+  launch_k(large ? k_relabel<4> : k_relabel<1>, dim3(grid), dim3(256), 0, stream, ev.start, ev.stop,
+           hv, next, es, tile_base, small, n_types, n_etypes, n_edges, src_gid, src_local,
+           xcd_order, blocks, reinterpret_cast<uint4 *>(clear), vecs);
   return hipGetLastError();
 }
 

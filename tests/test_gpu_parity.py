@@ -474,3 +474,54 @@ def test_small_call_limits(olib, n):
                     with pytest.raises(hg.HGError) as ex:
                         g.sample_blocks(gpu_seeds(wrong), fan, n)
                     assert ex.value.status == hg.HG_EINVAL
+
+
+@pytest.mark.parametrize("n", [40_000, 4_300_000])
+def test_new_vertices_by_shares(olib, n):
+    """The compaction numbers a wavefront's new vertices a lane per share of 64
+    vertices, or a share at a time when some share has more new vertices than there
+    are shares with any, or than 17: shares and vertices on either side of both
+    limits, full shares, and the last vertices of the type; in the compaction of one
+    launch and of three."""
+    rng = np.random.default_rng(3)
+    cases = []
+    for shares in (1, 2, 16, 17, 18, 63, 64):
+        for per in (1, 2, 15, 16, 17, 18, 19, 64):
+            cases.append((shares, per))
+    idx = []
+    for shares, per in cases:
+        at = np.sort(rng.choice(64, size=shares, replace=False)) + 64 * int(rng.integers(0, 9))
+        v = np.concatenate([64 * s + np.sort(rng.choice(64, size=per, replace=False)) for s in at])
+        idx.append(np.unique(np.concatenate([v, rng.integers(0, n, size=3), [n - 1]])))
+    deg = [x.size for x in idx]
+    ip = np.concatenate([[0], np.cumsum(deg), np.full(n - len(deg), sum(deg))]).astype(np.int64)
+    ets = [(0, 0, ip, np.concatenate(idx).astype(np.int64))]
+    g = gpu_graph([n], ets, [None])
+    host = oracle.HostGraph([(n, None)], ets, lib=olib)
+    for k in range(0, len(cases), 1 if n < 100_000 else 9):
+        seeds = [np.array([k, n - 5], np.int64)]
+        diffs = compare(host.sample_blocks(seeds, [[-1]], 1),
+                        result_dict(g, g.sample_blocks(gpu_seeds(seeds), [[-1]], 1)), 1, 1, 1)
+        assert not diffs, f"{cases[k]}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("sizes", [(2_097_151, 0, 1), (2_097_152, 3, 0), (1, 2_200_000, 1023),
+                                   (1024, 1024, 2_100_000, 1, 1, 5000)])
+def test_relabel_of_many_edges(olib, sizes):
+    """From 2097152 edges on, a block of the relabel takes 1024 of them: edge types
+    that end within a block, on its edge and one before, with empty ones between."""
+    rng = np.random.default_rng(len(sizes))
+    n = 30_000
+    ets = []
+    for total in sizes:
+        deg = np.full(200, total // 200)
+        deg[:total % 200] += 1
+        ip = np.concatenate([[0], np.cumsum(deg), np.full(n - 200, total)]).astype(np.int64)
+        ets.append((0, 0, ip, rng.integers(0, n, size=total).astype(np.int64)))
+    g = gpu_graph([n], ets, [None])
+    seeds = [rng.permutation(250).astype(np.int64)]
+    fan = [[-1] * len(sizes)]
+    ref = oracle.HostGraph([(n, None)], ets, lib=olib, check=False).sample_blocks(seeds, fan, 2)
+    diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(seeds), fan, 2)), 1, len(sizes),
+                    1)
+    assert not diffs, "\n".join(diffs[:10])
