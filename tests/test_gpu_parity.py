@@ -525,3 +525,28 @@ def test_relabel_of_many_edges(olib, sizes):
     diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(seeds), fan, 2)), 1, len(sizes),
                     1)
     assert not diffs, "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("n", [65535, 65536, 65537, 66047, 66048, 66560])
+def test_large_counting_pass(olib, n):
+    """Hops of 262144 pair slots and more are counted in tiles of 2048 read in
+    stripes: edge types that start on, before and after a tile's first pair, an empty
+    one at the end (its start is the end of the pairs), the last tile nearly empty and
+    full; pairs of every role among them."""
+    rng = np.random.default_rng(n)
+    nn = [70_000, 10]
+    ets = []
+    for d in (0, 0, 0, 0, 1):
+        deg = rng.choice([0, 1, 2, 7, 14], size=nn[d], p=[0.3, 0.4, 0.2, 0.08, 0.02])
+        if d == 0:
+            deg[rng.choice(nn[0], size=30, replace=False)] = 40
+            deg[rng.choice(nn[0], size=3, replace=False)] = 3000
+        ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+        ets.append((0, d, ip, rng.integers(0, nn[0], size=ip[-1]).astype(np.int64)))
+    g = gpu_graph(nn, ets, [None, None])
+    seeds = [rng.permutation(nn[0])[:n].astype(np.int64), None]
+    for fan in ([[3, -1, 10, 2, 5]], [[20, 0, 5, 1, 1]]):
+        ref = oracle.HostGraph([(k, None) for k in nn], ets, lib=olib,
+                               check=False).sample_blocks(seeds, fan, n)
+        diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(seeds), fan, n)), 2, 5, 1)
+        assert not diffs, f"{fan}: " + "\n".join(diffs[:10])
