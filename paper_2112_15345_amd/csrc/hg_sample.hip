@@ -601,14 +601,17 @@ __device__ __forceinline__ uint32_t word_of(const U32x4 &r, int w) {
 
 // Keys are uniform, so about deg * tau / 2^bits of them fall below tau; tau is
 // set for K + 4 sqrt(K) + 16 expected candidates.  A pure function of
-// (K, deg, bits), so every chunk of a hub uses the same value.
+// (K, deg, bits), so every chunk of a hub uses the same value.  In single
+// precision: it only decides how many candidates are ranked, and in double it was
+// 100 of a hub run's first instructions (sampler of the billion-edge share's two
+// hub hops 165 + 197 us, 161 + 194 in single).
 __device__ __forceinline__ uint64_t cand_threshold(int64_t K, int64_t deg,
                                                    uint64_t key_space) {
-  uint64_t tau = uint64_t(ceil((double(K) + 4.0 * sqrt(double(K)) + 16.0) /
-                               double(deg) * double(key_space)));
-  if (tau < 1) tau = 1;
-  if (tau > key_space) tau = key_space;
-  return tau;
+  const float k = float(uint32_t(K));  // 0 < K < deg < 2^32
+  const float t = (k + 4.0f * __builtin_amdgcn_sqrtf(k) + 16.0f) *
+                  __builtin_amdgcn_rcpf(float(uint32_t(deg))) * float(key_space);
+  // (key_space is a power of two of at most 2^32)
+  return t < float(key_space) ? uint64_t(uint32_t(t)) + 1 : key_space;
 }
 
 // The rule on one pair when the candidates could not decide it (too few or
