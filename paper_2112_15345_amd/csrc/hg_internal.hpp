@@ -98,7 +98,7 @@ struct NzType {
   int64_t num_nodes;
   int32_t type, words, n_in, first;
 };
-// Hops of a graph with such a type work on the active pairs, those whose bit is
+// Large hops of a graph with such a type work on the active pairs, those whose bit is
 // set (every pair of the other types): of the pairs of a 200-relation graph 3%
 // are.  The bit of pair (etype e, destination local ID i) is bit i & 63 of word
 // pair_word(pair_base[e], e, i): the words of an etype are followed by at most
@@ -110,6 +110,10 @@ __host__ __device__ inline int64_t pair_word(int64_t pair_base, int e, int64_t i
 __host__ __device__ inline int64_t pair_words(int64_t n_pairs, int32_t n_etypes) {
   return (n_pairs >> 6) + n_etypes;
 }
+// Hops of at most this many pairs go through every pair all the same: listing the
+// active ones is two launches more (a call of 300 seeds on 20 relations: 211 us by
+// active pairs, 165 by all; 500 seeds on 100 relations: 241 and 213).
+constexpr int64_t kActiveFromPairs = int64_t(1) << 18;
 constexpr int kPairListItems = 4;  // words per thread of the pass that lists the active pairs
 
 // Static per node type (per workspace).
@@ -317,6 +321,10 @@ constexpr int64_t kEdgeTile = 2048;
 constexpr int64_t kBinVerts = 8192;
 constexpr int64_t kBinsPerTile = kTile * 32 / kBinVerts;
 constexpr int64_t kMaxBins = 8192;
+// Hops of fewer in-edges use the atomics: a hop's binning is three launches more
+// (academic graph scaled by 0.1, 150 seeds, two hops: 369 us a call with bins, 299
+// without; the whole graph, 1000 seeds, with the first hop's 414 and 388).
+constexpr int64_t kBinsFromEdges = int64_t(1) << 20;
 
 struct LayerArgs {
   HopView hv, next;

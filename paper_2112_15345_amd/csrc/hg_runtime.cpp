@@ -721,7 +721,7 @@ struct SampleRun {
   // bins of a hop with S in-edges, or 0: importance by global atomics
   int64_t layer_bins(int64_t S) const {
     const int64_t n = g->n_tiles * kBinsPerTile;
-    return n <= kMaxBins && S < (int64_t(1) << 31) ? n : 0;
+    return n <= kMaxBins && S >= kBinsFromEdges && S < (int64_t(1) << 31) ? n : 0;
   }
   hg_status close_layer_edges();
   hg_status layer_hop(int32_t h, const HopView &hv, const HopView &nv, const PairArrays &pa,
@@ -1387,7 +1387,8 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
   for (int32_t h = 0; h < H; ++h) {
     const HopView hv = view(h), nv = view(h + 1);
     // ---- 1. counting pass over at most n_items pair slots ----------------
-    const bool active = !nz.empty();  // items are the active pairs
+    // items are the active pairs
+    const bool active = !nz.empty() && n_items > kActiveFromPairs;
     const int64_t tiles = count_tiles(n_items, active);
     const int64_t list_tiles = active ? pair_list_tiles(n_items, R) : 0;
     Carve pc;

@@ -321,8 +321,7 @@ def test_layer_importance_bins(olib, n):
 
 def test_layer_more_bins_than_fit(olib):
     """A bundle whose copies make more than 8192 bins sums the importance with
-    global atomics: each mini-batch equals its own call (binned) and two equal the
-    oracle."""
+    global atomics: each mini-batch equals its own call and two equal the oracle."""
     n, B = 2_120_000, 32  # 130 bitmap tiles of two bins each, per copy
     rng = np.random.default_rng(5)
     ets = bins_graph(n, [70_000, 3000, 3000, 40, 1, 5], rng, True)
@@ -339,3 +338,17 @@ def test_layer_more_bins_than_fit(olib):
         if b in (5, 30):
             diffs = compare(host.sample_layers(seeds[b], sizes, b), got, 1, 1, 2)
             assert not diffs, f"batch {b} vs oracle: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("n,dests", [(8191, 400), (8193, 383), (16384, 400), (40_000, 360)])
+def test_layer_bins_of_large_hops(olib, n, dests):
+    """The bins' ends again, at hops of about 2^20 in-edges, from which on they are
+    used (8193 x 383 stays below in its first hop)."""
+    rng = np.random.default_rng(n)
+    ets = bins_graph(n, [min(3000, n // 3)] * dests + [40, 1, 0], rng, True)
+    g = gpu_graph([n], ets, [None])
+    seeds = [np.concatenate([np.arange(dests + 3)[::-1], [n - 1]])]
+    for sizes in ([[-1]], [[2000], [9]]):
+        _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, 2**50, g=g)
+        diffs = compare(ref, got, 1, 1, len(sizes))
+        assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])

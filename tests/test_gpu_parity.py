@@ -428,6 +428,24 @@ def test_mask_bits_of_the_frontier(olib, R):
         assert not diffs, f"bundle batch {b}: " + "\n".join(diffs[:10])
 
 
+@pytest.mark.parametrize("n0", [4095, 4096, 4161])
+def test_mask_bits_of_large_hops(olib, n0):
+    """Hops of more than 2^18 pairs work on the active pairs: one pair fewer, as
+    many and more, 64 edge types; then a hop whose frontier has grown."""
+    R, n = 64, 6000
+    rng = np.random.default_rng(n0)
+    ets = []
+    for _e in range(R):
+        deg = np.where(rng.random(n) < 0.05, rng.integers(1, 7, n), 0)
+        idx = [np.sort(rng.choice(n, size=k, replace=False)) for k in deg if k]
+        ets.append((0, 0, np.concatenate([[0], np.cumsum(deg)]).astype(np.int64),
+                    np.concatenate(idx).astype(np.int64)))
+    seeds = [rng.permutation(n)[:n0].astype(np.int64)]
+    _, _, ref, got = run_both(olib, [n], ets, [None], seeds, [[3] * R, [2] * R], 9, 32)
+    diffs = compare(ref, got, 1, R, 2)
+    assert not diffs, "\n".join(diffs[:10])
+
+
 # key bits for which a hub's candidate list (about K + 4 sqrt(K) + 16 entries, at
 # most 512) holds equal keys: several to a value, pairs of them, hardly any; lists
 # of 1 to 3 entries past a multiple of four, and of several per lane
