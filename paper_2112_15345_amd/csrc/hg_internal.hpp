@@ -312,6 +312,10 @@ hipError_t launch_compact(HopView hv, const TypeStatic *ts, int32_t n_types,
 constexpr int64_t kLayerTile = 512;
 // In-edges per tile of the layer-wise edge passes (256 threads, eight each).
 constexpr int64_t kEdgeTile = 2048;
+// Pairs of such a tile, empty ones included, that its block goes through to find
+// each position's pair; of more, each position searches for its own (32 rounds of
+// loads against 8 chains of 13).
+constexpr int kTilePairs = 8192;
 
 // The candidates' importance is summed in LDS, a bin of kBinVerts vertices (half a
 // bitmap tile: bin b of all types has frontier words b * kBinVerts / 32 ...) to a

@@ -84,7 +84,7 @@ __device__ __forceinline__ uint64_t layer_weight(int64_t d) {
 __device__ __forceinline__ uint32_t degree_code(int64_t d) {
   return d <= 65536 ? uint32_t(d) : 0u;
 }
-constexpr int kBinBits = 13;
+constexpr int kBinBits = 13, kDegreeBits = 17;
 static_assert(kBinVerts == int64_t(1) << kBinBits, "a place in a bin takes 13 bits");
 __device__ __forceinline__ uint64_t code_weight(uint32_t d) {
   return d ? layer_weight(int64_t(d)) : 0;
@@ -195,55 +195,88 @@ __global__ __launch_bounds__(256) void k_lw_tile_pairs(LayerArgs A) {
   if (gs_start() == 0) A.tile_pair[A.n_edge_tiles] = A.n_pairs - 1;
 }
 
-// The pairs of a tile of positions in LDS: from tile_pair of the tile to
-// tile_pair of the next one (which may hold one pair past the tile).  More than
-// kTilePairs pairs (runs of empty pairs) leave n = 0, and each position then
-// searches the pair offsets.  `w`: the importance that each in-edge of the pair
-// adds to its source (kKind 0), computed once per pair instead of per edge, or its
-// code in a record (kKind 2).
-constexpr int kTilePairs = 512;
+// The pair of every position of a tile, in LDS: the tile's position at which the
+// pair starts (0 for the first pair, which may start before the tile).  Each
+// non-empty pair marks its start, and a running maximum over the positions spreads
+// the marks.  `slot[start]` is the CSC slot that the tile's position 0 would have in
+// the pair (modulo 2^32, as in-edges of a type are fewer), or for kPairs the pair
+// itself, counted from the tile's first.  The marks are taken from the pairs between
+// tile_pair of the tile and of the next one; of more than kTilePairs of them (long
+// runs of empty pairs) no table is made, and each position searches the pair
+// offsets.  A binary search of a table of pairs, for each position, was a chain of
+// LDS reads eight times as long as this scan, and a table of 512 or 1024 pairs did
+// not hold most tiles of sparse types (2^18 in-edges, two a pair: keep flags 28 us
+// and weights 37, now 13 and 23).
+constexpr int kPlaceBits = 11;
+static_assert(kEdgeTile == int64_t(1) << kPlaceBits, "a place in a tile takes 11 bits");
+static_assert(kPlaceBits + kDegreeBits <= 32, "a place and a degree's code share a word");
 struct TilePairs {
-  int64_t off[kTilePairs], plo[kTilePairs];
-  uint64_t w[kTilePairs];
+  // per position its pair's start; at the start, above it, the pair's degree code
+  uint32_t at[kEdgeTile];
+  uint32_t slot[kEdgeTile];
 };
 struct PairRange {
   int64_t p0, p1;
-  int n;
+  int n;  // 0: no table
 };
-template <int kKind>
+template <int kKind, bool kPairs = false>
 __device__ void tile_tables(const LayerArgs &A, int64_t tile, TileSegs &T, TilePairs &Q,
                             PairRange &R) {
+  __shared__ uint32_t s_max[256 / kWave];
   const int64_t pa = A.tile_pair[tile], pb = A.tile_pair[tile + 1];
-  const int n = pb - pa + 1 <= kTilePairs ? int(pb - pa + 1) : 0;
-  for (int k = threadIdx.x; k < n; k += blockDim.x) {
-    const int64_t lo = A.pa.off[pa + k];
-    Q.off[k] = lo;
-    // (an empty pair has no in-edge position: nothing is read of it)
-    const bool any = A.pa.off[pa + k + 1] > lo;
-    Q.plo[k] = any ? A.pa.plo[pa + k] : 0;
-    if (kKind == 0) Q.w[k] = any ? layer_weight(A.pa.pdeg[pa + k]) : 0;
-    if (kKind == 2) Q.w[k] = any ? degree_code(A.pa.pdeg[pa + k]) : 0;
-  }
+  const int64_t j0 = tile * kEdgeTile;
+  R = PairRange{pa, pb, pb - pa + 1 <= kTilePairs ? int(pb - pa + 1) : 0};
   tile_segs_load<kKind>(A, pa, pb, T);
+  if (R.n > 0) {
+    uint4 *at = reinterpret_cast<uint4 *>(Q.at);
+    at[threadIdx.x] = at[threadIdx.x + 256] = uint4{0, 0, 0, 0};
+    __syncthreads();
+#pragma unroll 2
+    for (int64_t p = pa + threadIdx.x; p <= pb; p += 256) {
+      const int64_t lo = A.pa.off[p], hi = A.pa.off[p + 1];
+      // (the last of them may start with the next tile)
+      if (hi <= lo || hi <= j0 || lo >= j0 + kEdgeTile) continue;
+      const uint32_t x = lo > j0 ? uint32_t(lo - j0) : 0u;
+      Q.at[x] = x | (kKind == 1 ? 0u : degree_code(A.pa.pdeg[p]) << kPlaceBits);
+      Q.slot[x] = kPairs ? uint32_t(p - pa) : uint32_t(A.pa.plo[p] - (lo - j0));
+    }
+    __syncthreads();
+    constexpr uint32_t kPlace = uint32_t(kEdgeTile) - 1;
+    uint4 a = at[2 * threadIdx.x], b = at[2 * threadIdx.x + 1];
+    uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t m = 0;  // places ascend: the last start of the thread's positions
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m = max(m, w[k] & kPlace);
+    uint32_t inc = m;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+      const uint32_t o = __shfl_up(inc, d, kWave);
+      if (lane_id() >= d) inc = max(inc, o);
+    }
+    const int wave = int(threadIdx.x) / kWave;
+    if (lane_id() == kWave - 1) s_max[wave] = inc;
+    uint32_t run = __shfl_up(inc, 1, kWave);
+    if (lane_id() == 0) run = 0;
+    __syncthreads();
+    for (int x = 0; x < wave; ++x) run = max(run, s_max[x]);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      run = max(run, w[k] & kPlace);
+      w[k] = (w[k] & ~kPlace) | run;
+    }
+    at[2 * threadIdx.x] = uint4{w[0], w[1], w[2], w[3]};
+    at[2 * threadIdx.x + 1] = uint4{w[4], w[5], w[6], w[7]};
+  }
   __syncthreads();
-  R = PairRange{pa, pb, n};
 }
 
-// Position j: its pair (an index into the block's table, or the pair itself)
-// and CSC slot.
-__device__ __forceinline__ int64_t pair_at(const LayerArgs &A, const TilePairs &Q,
-                                           const PairRange &R, int64_t j) {
-  if (R.n > 0) {
-    int lo = 0, hi = R.n;  // Q.off[lo] <= j
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (Q.off[mid] <= j)
-        lo = mid;
-      else
-        hi = mid;
-    }
-    return lo;
-  }
+// The pair of a position j, as what its tile's table or the pair arrays say of it.
+struct PairAt {
+  int64_t start;  // its place in the tile, or (no table) the pair
+};
+__device__ __forceinline__ PairAt pair_at(const LayerArgs &A, const TilePairs &Q,
+                                          const PairRange &R, int64_t j) {
+  if (R.n > 0) return PairAt{int64_t(Q.at[j & (kEdgeTile - 1)] & uint32_t(kEdgeTile - 1))};
   int64_t lo = R.p0, hi = R.p1 + 1;
   while (hi - lo > 1) {
     const int64_t mid = (lo + hi) >> 1;
@@ -252,11 +285,17 @@ __device__ __forceinline__ int64_t pair_at(const LayerArgs &A, const TilePairs &
     else
       hi = mid;
   }
-  return lo;
+  return PairAt{lo};
 }
+// Its CSC slot (of a table without kPairs), and its degree's code.
 __device__ __forceinline__ int64_t slot_at(const LayerArgs &A, const TilePairs &Q,
-                                           const PairRange &R, int64_t q, int64_t j) {
-  return R.n > 0 ? Q.plo[q] + (j - Q.off[q]) : A.pa.plo[q] + (j - A.pa.off[q]);
+                                           const PairRange &R, PairAt p, int64_t j) {
+  return R.n > 0 ? int64_t(uint32_t(Q.slot[p.start] + uint32_t(j & (kEdgeTile - 1))))
+                 : A.pa.plo[p.start] + (j - A.pa.off[p.start]);
+}
+__device__ __forceinline__ uint32_t code_at(const LayerArgs &A, const TilePairs &Q,
+                                            const PairRange &R, PairAt p) {
+  return R.n > 0 ? Q.at[p.start] >> kPlaceBits : degree_code(A.pa.pdeg[p.start]);
 }
 
 // Blocks of 256 threads take tiles of kEdgeTile positions, each thread every
@@ -268,10 +307,9 @@ constexpr int kEdgeItems = int(kEdgeTile / 256);
 // position needs of its etype and pair.
 struct EdgeItems {
   int seg[kEdgeItems];
-  int64_t pair[kEdgeItems];
+  PairAt pair[kEdgeItems];
   int64_t u[kEdgeItems];
 };
-template <int kKind>
 __device__ __forceinline__ void edge_items(const LayerArgs &A, const TileSegs &T,
                                            const TilePairs &Q, const PairRange &R, int64_t tile,
                                            EdgeItems &I) {
@@ -281,7 +319,7 @@ __device__ __forceinline__ void edge_items(const LayerArgs &A, const TileSegs &T
     const int64_t j = tile * kEdgeTile + k * 256 + threadIdx.x;
     I.u[k] = -1;
     I.seg[k] = 0;
-    I.pair[k] = 0;
+    I.pair[k] = PairAt{0};
     if (j < A.n_all) {
       I.seg[k] = seg_index(A, T, s, j);
       I.pair[k] = pair_at(A, Q, R, j);
@@ -293,12 +331,12 @@ __device__ __forceinline__ void edge_items(const LayerArgs &A, const TileSegs &T
 
 __global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
   __shared__ TileSegs T;
-  __shared__ TilePairs Q;
+  __shared__ __align__(16) TilePairs Q;
   const int64_t tile = blockIdx.x;
   PairRange R;
   tile_tables<0>(A, tile, T, Q, R);
   EdgeItems I;
-  edge_items<0>(A, T, Q, R, tile, I);
+  edge_items(A, T, Q, R, tile, I);
   uint32_t f[kEdgeItems];
 #pragma unroll
   for (int k = 0; k < kEdgeItems; ++k) {
@@ -311,7 +349,7 @@ __global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
     if (u < 0 || ((f[k] >> (u & 31)) & 1u)) continue;
     const SegView v = seg_view<0>(A, T, I.seg[k]);
     v.reached[u] = 1;  // a candidate
-    const uint64_t w = R.n > 0 ? Q.w[I.pair[k]] : layer_weight(A.pa.pdeg[I.pair[k]]);
+    const uint64_t w = code_weight(code_at(A, Q, R, I.pair[k]));
     if (w)
       atomicAdd(reinterpret_cast<unsigned long long *>(static_cast<uint64_t *>(v.per_seg) + u),
                 (unsigned long long)w);
@@ -339,7 +377,7 @@ __device__ __forceinline__ void bin_items(const LayerArgs &A, const TileSegs &T,
                                           const TilePairs &Q, const PairRange &R, int64_t tile,
                                           int32_t (&bin)[kEdgeItems], uint32_t (&rec)[kEdgeItems]) {
   EdgeItems I;
-  edge_items<2>(A, T, Q, R, tile, I);
+  edge_items(A, T, Q, R, tile, I);
 #pragma unroll
   for (int k = 0; k < kEdgeItems; ++k) {
     bin[k] = -1;
@@ -347,7 +385,7 @@ __device__ __forceinline__ void bin_items(const LayerArgs &A, const TileSegs &T,
     if (I.u[k] < 0) continue;
     const int32_t b0 = T.n > 0 ? T.bin0[I.seg[k]]
                                : int32_t(kBinsPerTile * A.tile_base[A.es[I.seg[k]].src_type]);
-    const uint32_t d = R.n > 0 ? uint32_t(Q.w[I.pair[k]]) : degree_code(A.pa.pdeg[I.pair[k]]);
+    const uint32_t d = code_at(A, Q, R, I.pair[k]);
     bin[k] = b0 + int32_t(I.u[k] >> kBinBits);
     rec[k] = uint32_t(I.u[k] & (kBinVerts - 1)) | (d << kBinBits);
   }
@@ -356,7 +394,7 @@ __device__ __forceinline__ void bin_items(const LayerArgs &A, const TileSegs &T,
 // In-edges per bin.
 __global__ __launch_bounds__(256) void k_lw_bin_count(LayerArgs A) {
   __shared__ TileSegs T;
-  __shared__ TilePairs Q;
+  __shared__ __align__(16) TilePairs Q;
   extern __shared__ __align__(16) char bin_lds[];
   uint32_t *cnt = reinterpret_cast<uint32_t *>(bin_lds);
   for (int b = threadIdx.x; b < A.n_bins; b += 256) cnt[b] = 0;
@@ -443,7 +481,7 @@ __global__ __launch_bounds__(1024) void k_lw_bin_starts(LayerArgs A) {
 // and writes them.
 __global__ __launch_bounds__(256) void k_lw_bin_scatter(LayerArgs A) {
   __shared__ TileSegs T;
-  __shared__ TilePairs Q;
+  __shared__ __align__(16) TilePairs Q;
   extern __shared__ __align__(16) char bin_lds[];
   uint32_t *cnt = reinterpret_cast<uint32_t *>(bin_lds);
   for (int b = threadIdx.x; b < A.n_bins; b += 256) cnt[b] = 0;
@@ -643,13 +681,13 @@ constexpr int kKeepWords = int(kEdgeTile / 64);  // words per tile
 
 __global__ __launch_bounds__(256) void k_lw_keep_flags(LayerArgs A) {
   __shared__ TileSegs T;
-  __shared__ TilePairs Q;
+  __shared__ __align__(16) TilePairs Q;
   __shared__ int32_t s_cnt[kKeepWords];
   const int64_t tile = blockIdx.x;
   PairRange R;
   tile_tables<1>(A, tile, T, Q, R);
   EdgeItems I;
-  edge_items<1>(A, T, Q, R, tile, I);
+  edge_items(A, T, Q, R, tile, I);
   const int wave = int(threadIdx.x) / kWave;
 #pragma unroll
   for (int k = 0; k < kEdgeItems; ++k) {
@@ -702,7 +740,7 @@ __device__ __forceinline__ int select_bit(uint64_t m, int k) {
 // x + 256, ...
 __global__ __launch_bounds__(256) void k_lw_keep_emit(LayerArgs A) {
   __shared__ TileSegs T;
-  __shared__ TilePairs Q;
+  __shared__ __align__(16) TilePairs Q;
   __shared__ int32_t s_pre[kKeepWords];
   __shared__ uint64_t s_bits[kKeepWords];
   const int64_t tile = blockIdx.x;
@@ -714,7 +752,7 @@ __global__ __launch_bounds__(256) void k_lw_keep_emit(LayerArgs A) {
     s_bits[threadIdx.x] = A.keep_bits[tile * kKeepWords + threadIdx.x];
   }
   PairRange R;
-  tile_tables<1>(A, tile, T, Q, R);  // also the barrier
+  tile_tables<1, true>(A, tile, T, Q, R);  // also the barrier
   int s = 0;
   for (int x = threadIdx.x; x < n; x += 256) {
     int w = 0;  // the last word with s_pre <= x
@@ -723,12 +761,13 @@ __global__ __launch_bounds__(256) void k_lw_keep_emit(LayerArgs A) {
       if (s_pre[w + d] <= x) w += d;
     const int64_t j = tile * kEdgeTile + w * 64 + select_bit(s_bits[w], x - s_pre[w]);
     const int sg = seg_index(A, T, s, j);
-    const int64_t q = pair_at(A, Q, R, j);
-    const int64_t slot = slot_at(A, Q, R, q, j);
+    const PairAt at = pair_at(A, Q, R, j);
+    const int64_t p = R.n > 0 ? R.p0 + Q.slot[at.start] : at.start;
+    const int64_t slot = A.pa.plo[p] + (j - A.pa.off[p]);
     const SegView v = seg_view<1>(A, T, sg);
     A.out_eid[first + x] = slot;
     A.out_dst_local[first + x] =
-        int32_t(A.pa.pair_of(R.n > 0 ? R.p0 + q : q) - v.pair_base);
+        int32_t(A.pa.pair_of(p) - v.pair_base);
     A.out_src_local[first + x] = static_cast<const int32_t *>(v.per_seg)[v.indices[slot]];
   }
 }

@@ -1,0 +1,40 @@
+"""The rules that choose a call's kernels by its sizes, and the sizes that they rest
+on: the expressions of the internal header, compiled and evaluated on the CPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+
+
+@pytest.fixture(scope="module")
+def evaluate(tmp_path_factory):
+    """evaluate([C++ integer expressions]) -> their values."""
+    where = tmp_path_factory.mktemp("rules")
+
+    def run(exprs):
+        src, exe = str(where / "rules.cpp"), str(where / "rules")
+        lines = "\n".join(f'std::printf("%lld\\n", (long long)({e}));' for e in exprs)
+        with open(src, "w") as f:
+            f.write('#include <cstdio>\n#include "hg_internal.hpp"\nusing namespace hg;\n'
+                    f"int main() {{\n{lines}\n}}\n")
+        cmd = ["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__=1", "-I",
+               os.path.join(ROOT, "include"), "-I",
+               os.path.join(ROOT, "paper_2112_15345_amd", "csrc"), "-isystem", "/opt/rocm/include",
+               src, "-o", exe]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        assert res.returncode == 0, res.stderr
+        out = subprocess.run([exe], capture_output=True, text=True, check=True).stdout
+        return [int(x) for x in out.split()]
+
+    return run
+
+
+def test_tiles_of_sparse_types_have_a_pair_table(evaluate):
+    """A tile of the layer-wise edge passes whose pairs have one in-edge each, and
+    as many empty pairs between them, still has the table of its positions' pairs."""
+    pairs, tile = evaluate(["kTilePairs", "kEdgeTile"])
+    assert pairs >= 2 * tile

@@ -265,9 +265,8 @@ def test_layer_many_relations(olib, R):
 @pytest.mark.parametrize("pairs", [1, 3, 700])
 def test_layer_edge_tiles(olib, total, pairs):
     """The frontier's in-edges end on, before and after the edges of a flag
-    word (64 positions) and of a tile (2048); 700 pairs (most of one in-edge
-    when there are few) overflow the tile's pair table (512).  Kept: none, a
-    few, all."""
+    word (64 positions) and of a tile (2048), with few pairs and with many (most
+    of one in-edge when there are few).  Kept: none, a few, all."""
     pairs = min(pairs, total)
     rng = np.random.default_rng(100 * total + pairs)
     n = 9000
@@ -350,5 +349,27 @@ def test_layer_bins_of_large_hops(olib, n, dests):
     seeds = [np.concatenate([np.arange(dests + 3)[::-1], [n - 1]])]
     for sizes in ([[-1]], [[2000], [9]]):
         _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, 2**50, g=g)
+        diffs = compare(ref, got, 1, 1, len(sizes))
+        assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("pairs", [8191, 8192, 8193, 20_000])
+@pytest.mark.parametrize("total", [300, 2048, 5000])
+def test_layer_tiles_of_empty_pairs(olib, total, pairs):
+    """Tiles among many empty pairs: a block finds its positions' pairs by going
+    through up to 8192 of them, and of more each position searches.  Pairs that start
+    before the tile, on its first position and on its last."""
+    rng = np.random.default_rng(total + pairs)
+    n = 25_000
+    deg = np.zeros(n, np.int64)
+    at = np.unique(np.concatenate([[0, 1, pairs // 2], rng.choice(pairs, size=120)]))
+    deg[at] = rng.multinomial(total - at.size, np.full(at.size, 1 / at.size)) + 1
+    idx = [np.sort(rng.choice(n, size=k, replace=False)) for k in deg if k]
+    ets = [(0, 0, np.concatenate([[0], np.cumsum(deg)]).astype(np.int64),
+            np.concatenate(idx).astype(np.int64))]
+    g = gpu_graph([n], ets, [None])
+    seeds = [np.arange(pairs)]
+    for sizes in ([[-1]], [[9]], [[200], [-1]]):
+        _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, total, g=g)
         diffs = compare(ref, got, 1, 1, len(sizes))
         assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
