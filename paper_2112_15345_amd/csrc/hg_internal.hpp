@@ -325,6 +325,15 @@ constexpr int kTilePairs = 8192;
 constexpr int64_t kBinVerts = 8192;
 constexpr int64_t kBinsPerTile = kTile * 32 / kBinVerts;
 constexpr int64_t kMaxBins = 8192;
+// Bins of more records than this are summed in parts of about as many, each by a
+// block, through sums in memory; a call of n in-edges has fewer than n / kBinPart of
+// them.
+constexpr int64_t kBinPart = 32768;
+__host__ __device__ inline int64_t bin_parts(int64_t records) {  // 0: not in parts
+  return records > kBinPart ? (records + kBinPart - 1) / kBinPart : 0;
+}
+inline int64_t most_large_bins(int64_t n) { return n / kBinPart + 1; }
+inline int64_t most_bin_parts(int64_t n) { return 2 * (n / kBinPart) + 1; }
 // Hops of fewer in-edges use the atomics: a hop's binning is three launches more
 // (academic graph scaled by 0.1, 150 seeds, two hops: 369 us a call with bins, 299
 // without; the whole graph, 1000 seeds, with the first hop's 414 and 388).
@@ -361,6 +370,8 @@ struct LayerArgs {
   const uint32_t *fbits;   // frontier bits of all types
   uint32_t *bin_edges, *bin_at;
   int64_t *bin_rec, *bin_cap;  // [n_bins + 1]
+  int64_t *bin_part, *bin_big;  // [n_bins + 1] parts of, and number of, the large bins before it
+  unsigned long long *big_sums;  // [large bins * kBinVerts], zero between hops
   uint32_t *rec;           // [n_all] (edge_record)
   int32_t *bin_cand_off;   // per candidate: its vertex's place in the bin
   uint64_t *bin_cand_pre;  // per candidate: importance before it in the bin

@@ -211,6 +211,7 @@ struct Workspace {
   Scratch lw_weight;               // layer-wise calls: importance per vertex (zero between uses)
   Scratch lw_edges, lw_cand;       // layer-wise calls: every in-edge of a hop; candidates
   Scratch lw_bins;                 // layer-wise calls: in-edges per bin (zero between uses)
+  Scratch lw_sums;                 // layer-wise calls: sums of large bins (zero between uses)
   uint32_t epoch = 0;              // look-back launches so far (mod kEpochLimit)
   // Recorded at the end of every call on that call's stream (`last`); the
   // next call on another stream waits for it.  An event must never outlive
@@ -416,6 +417,7 @@ void free_workspace(Workspace *w) {
   w->lw_edges.release();
   w->lw_cand.release();
   w->lw_bins.release();
+  w->lw_sums.release();
   if (w->hsmall) (void)hipHostFree(w->hsmall);
   if (w->htab) (void)hipHostFree(w->htab);
   delete w;
@@ -1245,6 +1247,8 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
     cc.add(&A.bin_at, A.n_bins);
     cc.add(&A.bin_rec, A.n_bins + 1);
     cc.add(&A.bin_cap, A.n_bins + 1);
+    cc.add(&A.bin_part, A.n_bins + 1);
+    cc.add(&A.bin_big, A.n_bins + 1);
     cc.add(&A.bin_n, A.n_bins);
     cc.add(&A.bin_n_pre, A.n_bins + 1);
     cc.add(&A.bin_w, A.n_bins);
@@ -1268,6 +1272,15 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
     A.bin_edges = static_cast<uint32_t *>(ws->lw_bins.p);
     if (ws->lw_bins.fresh &&
         (e = launch_fill_u32(A.bin_edges, A.n_bins, 0u, stream)) != hipSuccess)
+      return fail_device(e, "fill");
+    // the sums of the large bins, zero between hops
+    if (!ws->lw_sums.ensure(sizeof(uint64_t) * size_t(most_large_bins(S) * kBinVerts), stream))
+      return fail(HG_ENOMEM, "hop %d: layer-wise scratch", h);
+    A.big_sums = static_cast<unsigned long long *>(ws->lw_sums.p);
+    if (ws->lw_sums.fresh &&
+        (e = launch_fill_u32(static_cast<uint32_t *>(ws->lw_sums.p),
+                             int64_t(ws->lw_sums.cap / sizeof(uint32_t)), 0u, stream)) !=
+            hipSuccess)
       return fail_device(e, "fill");
   } else {
     // the importance array: one uint64 per vertex, zero between uses

@@ -1,6 +1,9 @@
 """Runs the HIP path and the oracle on the same inputs and compares them."""
 from __future__ import annotations
 
+import os
+import re
+
 import numpy as np
 import torch
 
@@ -101,3 +104,27 @@ def many_relations(rng, R, n0=300, n1=80):
         ets.append((s, d, np.array(indptr, np.int64), np.array(indices, np.int64)))
     feats = [rng.standard_normal((n0, 4)).astype(np.float32), None]
     return nn, ets, feats
+
+
+def internal(name):
+    """The value of an integer constant of the library's internal header, so that a
+    test can check that its sizes reach the kernels that it is about."""
+    path = os.path.join(os.path.dirname(hg.__file__), "csrc", "hg_internal.hpp")
+    m = re.search(rf"constexpr \w+ {name} = ([^;]+);", open(path).read())
+    return int(eval(m.group(1).replace("int64_t", "int"), {"__builtins__": {"int": int}}))
+
+
+def csc(rng, deg, n_src):
+    """(indptr, indices) of destinations with in-degrees deg from random sources."""
+    ip = np.concatenate([[0], np.cumsum(deg)]).astype(np.int64)
+    return ip, rng.integers(0, n_src, size=int(ip[-1])).astype(np.int64)
+
+
+def frontier_in_edges(ets, ref, hop):
+    """In-edges of a hop's frontier, over all edge types."""
+    n = 0
+    for _, d, ip, _ in ets:
+        n_dst, gid = ref["nodes"][(hop, d)]
+        v = gid[:n_dst]
+        n += int((ip[v + 1] - ip[v]).sum())
+    return n

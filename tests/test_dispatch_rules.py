@@ -38,3 +38,17 @@ def test_tiles_of_sparse_types_have_a_pair_table(evaluate):
     as many empty pairs between them, still has the table of its positions' pairs."""
     pairs, tile = evaluate(["kTilePairs", "kEdgeTile"])
     assert pairs >= 2 * tile
+
+
+def test_large_bins_are_shared_by_blocks(evaluate):
+    """A bin of any number of records is summed in parts of at most 32768 records, one
+    to a block, and the bounds on the parts and on the bins in parts hold."""
+    sizes = [1, 32767, 32768, 32769, 65536, 65537, 1 << 20, (1 << 31) - 1]
+    part, *n = evaluate(["kBinPart"] + [f"bin_parts({r})" for r in sizes])
+    for r, k in zip(sizes, n):
+        assert (k == 0 and r <= part) or (k >= 2 and (k - 1) * part < r <= k * part)
+    # bins that make the most of n in-edges: all just over a part
+    for n_bins in (1, 3, 100):
+        total = n_bins * (part + 1)
+        large, parts = evaluate([f"most_large_bins({total})", f"most_bin_parts({total})"])
+        assert large >= n_bins and parts >= 2 * n_bins

@@ -13,7 +13,8 @@ import oracle
 import paper_2112_15345_amd as hg
 import pins
 import workloads as W
-from gpu_harness import compare, gpu_graph, gpu_seeds, many_relations, result_dict
+from gpu_harness import (compare, csc, frontier_in_edges, gpu_graph, gpu_seeds, internal,
+                         many_relations, result_dict)
 
 pytestmark = pytest.mark.gpu
 
@@ -372,4 +373,78 @@ def test_layer_tiles_of_empty_pairs(olib, total, pairs):
     for sizes in ([[-1]], [[9]], [[200], [-1]]):
         _, _, ref, got = run_layer_both(olib, [n], ets, [None], seeds, sizes, total, g=g)
         diffs = compare(ref, got, 1, 1, len(sizes))
+        assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("records", [32767, 32768, 32769, 65536, 65537, 400_001])
+def test_layer_large_bins(olib, records):
+    """Bins of more than 32768 records are summed in parts: a type of one full bin
+    with as many, one fewer and more; beside it a type of many bins, one of them with
+    a candidate from a destination past 65536 in-edges (no importance) and one of
+    65536 (importance 1) in every bin.  Twice, as the sums have to be clean again."""
+    assert internal("kBinPart") == 32768 and internal("kBinVerts") == 8192
+    rng = np.random.default_rng(records)
+    nn = [2000, 8192, 50_000]
+    deg1 = rng.multinomial(records, np.full(1500, 1 / 1500))
+    deg1 = np.concatenate([deg1, np.zeros(nn[0] - 1500, np.int64)])
+    deg2 = np.full(nn[0], 450)
+    deg2[:4] = [65537, 65536, 70_000, 0]
+    ets = [(1, 0, *csc(rng, deg1, nn[1])), (2, 0, *csc(rng, deg2, nn[2]))]
+    g = gpu_graph(nn, ets, [None] * 3)
+    seeds = [rng.permutation(nn[0]), np.array([5]), None]
+    for sizes in ([[-1, -1, -1]], [[0, 40, 3000]], [[0, 40, 3000]]):
+        _, _, ref, got = run_layer_both(olib, nn, ets, [None] * 3, seeds, sizes, records, g=g)
+        assert frontier_in_edges(ets, ref, 0) >= internal("kBinsFromEdges")
+        diffs = compare(ref, got, 3, 2, 1)
+        assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("copies", [1, 3])
+def test_layer_bins_of_bundles(olib, copies):
+    """Importance by bins over three node types with partial last bins (sizes on and
+    off a bin's and a bitmap tile's), and over the copies of a bundle, each keyed as its
+    own call: every kind of draw, two hops above the bins' threshold."""
+    rng = np.random.default_rng(copies)
+    nn = [40_001, 8193, 16_384]
+    ets = []
+    for s, d, mean in ((0, 0, 40), (1, 0, 30), (2, 0, 35), (0, 1, 50), (2, 1, 3), (1, 2, 20)):
+        deg = rng.geometric(1 / mean, size=nn[d]) - 1
+        ets.append((s, d, *csc(rng, deg, nn[s])))
+    g = gpu_graph(nn, ets, [None] * 3)
+    host = oracle.HostGraph([(n, None) for n in nn], ets, lib=olib, check=False)
+    n = 16_000 // copies
+    for sizes in ([[30, -1, 500], [-1, 7, 0]], [[0, 64, -1], [2000, 2000, 2000]]):
+        batches = [[rng.permutation(nn[0])[:n + b], rng.permutation(nn[1])[:n // 4 + 7 * b],
+                    rng.permutation(nn[2])[:n // 9]] for b in range(copies)]
+        refs = [host.sample_layers(s, sizes, 90 + b) for b, s in enumerate(batches)]
+        for h in range(2):
+            total = sum(frontier_in_edges(ets, r, h) for r in refs)
+            assert total >= internal("kBinsFromEdges")
+        bl = g.sample_layers_bundle([gpu_seeds(s) for s in batches], sizes,
+                                    [90 + b for b in range(copies)], gather=[])
+        for b in range(copies):
+            diffs = compare(refs[b], result_dict(g, bl[b]), 3, len(ets), 2)
+            assert not diffs, f"sizes {sizes} batch {b}: " + "\n".join(diffs[:10])
+
+
+def test_layer_bins_past_the_tile_tables(olib):
+    """Importance by bins where a tile of positions spans more than 32 edge types and
+    more than 8192 pairs (no table of either), between two edge types of full tiles."""
+    rng = np.random.default_rng(17)
+    nn = [12_000, 30_000]
+    full = np.full(nn[0], 60)
+    ets = [(1, 0, *csc(rng, full, nn[1]))]
+    for _ in range(45):
+        deg = np.zeros(nn[0], np.int64)
+        deg[rng.choice(nn[0], size=9, replace=False)] = rng.integers(1, 5, size=9)
+        ets.append((int(rng.integers(0, 2)), 0, *csc(rng, deg, nn[0])))
+    # 45 types of 9000 pairs and some 20 in-edges each: less than a tile together
+    assert sum(int(e[2][-1]) for e in ets[1:]) < internal("kEdgeTile")
+    ets.append((0, 0, *csc(rng, full, nn[0])))
+    g = gpu_graph(nn, ets, [None] * 2)
+    seeds = [rng.permutation(nn[0])[:9000], None]
+    for sizes in ([[-1, -1]], [[500, 900]]):
+        _, _, ref, got = run_layer_both(olib, nn, ets, [None] * 2, seeds, sizes, 4, g=g)
+        assert frontier_in_edges(ets, ref, 0) >= internal("kBinsFromEdges")
+        diffs = compare(ref, got, 2, len(ets), 1)
         assert not diffs, f"sizes {sizes}: " + "\n".join(diffs[:10])
