@@ -110,10 +110,21 @@ __host__ __device__ inline int64_t pair_word(int64_t pair_base, int e, int64_t i
 __host__ __device__ inline int64_t pair_words(int64_t n_pairs, int32_t n_etypes) {
   return (n_pairs >> 6) + n_etypes;
 }
-// Hops of at most this many pairs go through every pair all the same: listing the
-// active ones is two launches more (a call of 300 seeds on 20 relations: 211 us by
-// active pairs, 165 by all; 500 seeds on 100 relations: 241 and 213).
-constexpr int64_t kActiveFromPairs = int64_t(1) << 18;
+// Whether a hop of n_pairs pairs, n_active of them active, works on the active ones.
+// Listing them is two launches and a walk over the mask's words (15 us with 64 edge
+// types into the type, 25 with 200), and an active pair then costs about 190 ps,
+// where going through every pair costs 50 ps a pair and 60 more an active one: the
+// list pays from about kActiveFromPairs + 9/4 n_active pairs (and never past 4/9 of
+// them active).  Single calls of one hop, us by the list and by every pair (64 edge
+// types, fanout 5): 3% active, 2^18, 2^19 and 2^20 pairs 104 / 98, 110 / 116, 114 /
+// 147; 20%, 2^19 and 2^20: 127 / 124, 145 / 161; 30%, 2^20 and 2^21: 166 / 165, 225 /
+// 254; 50%, 2^18, 2^20 and 2^22: 151 / 109, 209 / 178, 493 / 436.  200 edge types, 3%,
+// 2^19 and 2^20: 135 / 130, 135 / 163.
+constexpr int64_t kActiveFromPairs = int64_t(320) << 10;
+constexpr int64_t kActivePerWord = int64_t(1) << 15;  // per 32 edge types into the type
+inline bool active_pairs_pay(int64_t n_pairs, int64_t n_active, int32_t mask_words) {
+  return n_pairs > kActiveFromPairs + kActivePerWord * mask_words + n_active / 4 * 9;
+}
 constexpr int kPairListItems = 4;  // words per thread of the pass that lists the active pairs
 
 // Static per node type (per workspace).
@@ -458,8 +469,10 @@ hipError_t launch_start(void *dst, const void *src, int64_t n, HopView hv, const
 // The non-empty mask of one destination type: for v < n, bit k of row v
 // (words per row) is set when indptrs[k][v + 1] > indptrs[k][v]; indptrs is a
 // device array of n_etypes pointers.
+// *n_set (device) gets the number of set bits added.
 hipError_t launch_nonempty_mask(const int64_t *const *indptrs, int32_t n_etypes, int32_t words,
-                                int64_t n, uint32_t *mask, hipStream_t stream);
+                                int64_t n, uint32_t *mask, unsigned long long *n_set,
+                                hipStream_t stream);
 
 // Graph check of one edge type: indptr[0] == 0, non-decreasing,
 // indptr[n_dst] == nnz, indices in [0, n_src).  Sets *err on a violation.

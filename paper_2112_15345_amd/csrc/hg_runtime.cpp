@@ -84,6 +84,9 @@ struct NTypeInfo {
   int32_t dim;
   int64_t row_bytes;
   bool host;         // the table lives in pinned host memory
+  // of a type with a non-empty mask: how many of its incoming edge types have
+  // in-edges at a vertex, on average
+  double mean_active = 0;
 };
 
 // A feature table is device memory or pinned host memory (hipHostMalloc):
@@ -1400,8 +1403,17 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
   for (int32_t h = 0; h < H; ++h) {
     const HopView hv = view(h), nv = view(h + 1);
     // ---- 1. counting pass over at most n_items pair slots ----------------
-    // items are the active pairs
-    const bool active = !nz.empty() && n_items > kActiveFromPairs;
+    // whether items are the active pairs (their number as the vertices' average has it)
+    double n_active = 0;
+    int32_t mask_words = 0;
+    int64_t most = 0;  // vertices of a type in the frontier
+    for (const NzType &N : nz) {
+      const int64_t n = front[size_t(N.type)];
+      n_active += double(n) * (N.mask ? g->nt[N.type].mean_active : double(N.n_in));
+      mask_words = std::max(mask_words, N.words);
+      most = std::max(most, n);
+    }
+    const bool active = !nz.empty() && active_pairs_pay(n_items, int64_t(n_active), mask_words);
     const int64_t tiles = count_tiles(n_items, active);
     const int64_t list_tiles = active ? pair_list_tiles(n_items, R) : 0;
     Carve pc;
@@ -1434,8 +1446,6 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
     StageEv ev_count = stage_ev(h, HG_STAGE_COUNT);
     uint32_t epoch;
     if (active) {
-      int64_t most = 0;
-      for (const NzType &N : nz) most = std::max(most, front[size_t(N.type)]);
       if ((e = next_epoch(&epoch)) != hipSuccess ||
           (e = launch_pair_list(hv, ws->d_nz, ws->d_nz_et, int32_t(nz.size()), R, most, n_items,
                                 pa, lb, epoch, ticket_base, ws->dsmall, stream,
@@ -1651,9 +1661,9 @@ hg_status SampleRun::hops(std::vector<int64_t> &nF, int64_t n_items) {
 namespace {
 
 // Node types with many incoming edge types get a per-vertex mask of the edge
-// types that have in-edges there, so that the counting pass skips the indptr
-// reads of empty (vertex, edge type) pairs.  Built once; a type whose mask
-// cannot be allocated goes without one.
+// types that have in-edges there, from which large hops list their non-empty
+// (vertex, edge type) pairs.  Built once; a type whose mask cannot be allocated
+// goes without one.
 hipError_t build_nonempty_masks(hg_graph *g, hipStream_t stream) {
   for (int32_t t = 0; t < g->T; ++t) {
     std::vector<int32_t> ets;
@@ -1671,14 +1681,20 @@ hipError_t build_nonempty_masks(hg_graph *g, hipStream_t stream) {
     g->nz_masks.push_back(mask);
     std::vector<const int64_t *> h(ets.size());
     for (size_t k = 0; k < ets.size(); ++k) h[k] = g->et[ets[k]].indptr;
+    h.push_back(nullptr);  // the place of the set bits' count
     hipError_t e = hipMalloc(&ptrs, sizeof(int64_t *) * h.size());
     if (e == hipSuccess)
       e = hipMemcpy(ptrs, h.data(), sizeof(int64_t *) * h.size(), hipMemcpyHostToDevice);
+    unsigned long long *d_set = reinterpret_cast<unsigned long long *>(ptrs + ets.size());
+    unsigned long long n_set = 0;
     if (e == hipSuccess)
-      e = launch_nonempty_mask(ptrs, int32_t(ets.size()), words, n, mask, stream);
+      e = launch_nonempty_mask(ptrs, int32_t(ets.size()), words, n, mask, d_set, stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(&n_set, d_set, sizeof(n_set), hipMemcpyDeviceToHost, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     (void)hipFree(ptrs);
     if (e != hipSuccess) return e;
+    g->nt[t].mean_active = double(n_set) / double(n);
     for (size_t k = 0; k < ets.size(); ++k) {
       ETypeInfo &E = g->et[ets[k]];
       E.nz_mask = mask;
@@ -1749,7 +1765,8 @@ hg_status hg_create(const hg_ntype_desc *ntypes, int32_t n_ntypes,
         return st;
       }
     }
-    g->nt.push_back({d.num_nodes, addr, d.dtype, d.dim, dtype_size(d.dtype) * int64_t(d.dim), host});
+    g->nt.push_back(NTypeInfo{d.num_nodes, addr, d.dtype, d.dim,
+                              dtype_size(d.dtype) * int64_t(d.dim), host});
   }
   layout_types(g);
   for (int32_t i = 0; i < n_etypes; ++i) {

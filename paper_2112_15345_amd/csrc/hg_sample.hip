@@ -1474,9 +1474,11 @@ __global__ void k_check_etype(const int64_t *indptr, int64_t n_dst,
 }
 
 // One thread per destination vertex: its row of the non-empty mask, from
-// the indptr of every edge type into its node type (coalesced across threads).
+// the indptr of every edge type into its node type (coalesced across threads);
+// the set bits are counted, with one atomic per wavefront.
 __global__ void k_nonempty_mask(const int64_t *const *indptrs, int32_t n_etypes, int32_t words,
-                                int64_t n, uint32_t *mask) {
+                                int64_t n, uint32_t *mask, unsigned long long *n_set) {
+  int64_t set = 0;
   for (int64_t v = grid_stride_start(); v < n; v += grid_stride_step()) {
     uint32_t w = 0;
     for (int32_t k = 0; k < n_etypes; ++k) {
@@ -1484,10 +1486,13 @@ __global__ void k_nonempty_mask(const int64_t *const *indptrs, int32_t n_etypes,
       if (ip[v + 1] > ip[v]) w |= 1u << (k & 31);
       if ((k & 31) == 31 || k == n_etypes - 1) {
         mask[v * words + (k >> 5)] = w;
+        set += __popc(w);
         w = 0;
       }
     }
   }
+  set = wave_sum_i64(set);
+  if (lane_id() == 0 && set) atomicAdd(n_set, (unsigned long long)set);
 }
 
 __global__ void k_philox(const uint32_t *ctr, uint32_t k0, uint32_t k1,
@@ -1762,10 +1767,11 @@ hipError_t launch_check_etype(const int64_t *indptr, int64_t n_dst,
 }
 
 hipError_t launch_nonempty_mask(const int64_t *const *indptrs, int32_t n_etypes, int32_t words,
-                                int64_t n, uint32_t *mask, hipStream_t stream) {
+                                int64_t n, uint32_t *mask, unsigned long long *n_set,
+                                hipStream_t stream) {
   if (n <= 0 || n_etypes <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_nonempty_mask, dim3(grid_for(n, 256, 16384)), dim3(256), 0, stream,
-                     indptrs, n_etypes, words, n, mask);
+                     indptrs, n_etypes, words, n, mask, n_set);
   return hipGetLastError();
 }
 

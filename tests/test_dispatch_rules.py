@@ -52,3 +52,19 @@ def test_large_bins_are_shared_by_blocks(evaluate):
         total = n_bins * (part + 1)
         large, parts = evaluate([f"most_large_bins({total})", f"most_bin_parts({total})"])
         assert large >= n_bins and parts >= 2 * n_bins
+
+
+def test_active_pairs_of_sparse_masks_only(evaluate):
+    """A hop lists its active pairs where they are few of many: never with half of
+    them active (going through every pair is faster at all sizes), and from some size
+    on with a few per cent, later with more active ones or more edge types."""
+    sizes = [1 << k for k in range(10, 31)]
+
+    def first(share, words):
+        pays = evaluate([f"active_pairs_pay({p}, {int(p * share)}, {words})" for p in sizes])
+        assert pays == sorted(pays)  # from some size on
+        return sizes[pays.index(1)] if 1 in pays else None
+
+    assert first(0.5, 1) is None and first(1.0, 7) is None
+    assert 1 << 18 < first(0.03, 1) <= first(0.03, 7) <= 1 << 20
+    assert first(0.03, 2) <= first(0.2, 2) <= first(0.3, 2) <= 1 << 21
