@@ -126,6 +126,21 @@ inline bool active_pairs_pay(int64_t n_pairs, int64_t n_active, int32_t mask_wor
   return n_pairs > kActiveFromPairs + kActivePerWord * mask_words + n_active / 4 * 9;
 }
 constexpr int kPairListItems = 4;  // words per thread of the pass that lists the active pairs
+// The blocks of the pass that makes their bits: x over the largest frontier, y over the
+// node types of all copies; at most 2^16 in all (each strides over what is left), as a
+// bundle of a graph of 2048 types has more of them than a grid's y takes, and most of
+// those have few vertices or none in the frontier.
+struct PairBitsGrid {
+  unsigned x, y;
+};
+inline PairBitsGrid pair_bits_grid(int64_t max_front, int32_t n_nz) {
+  constexpr int64_t kPerBlock = 256;  // frontier vertices, a wavefront for each 64
+  const int64_t y = n_nz < 1024 ? (n_nz < 1 ? 1 : n_nz) : 1024;
+  int64_t x = (max_front + 64 + kPerBlock - 1) / kPerBlock;
+  x = x < 4096 ? x : 4096;
+  x = x < (int64_t(1) << 16) / y ? x : (int64_t(1) << 16) / y;
+  return PairBitsGrid{unsigned(x), unsigned(y)};
+}
 
 // Static per node type (per workspace).
 // Per node type one flag byte and one frontier bit per vertex: the sampler

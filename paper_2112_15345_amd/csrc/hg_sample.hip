@@ -128,7 +128,7 @@ __global__ __launch_bounds__(kStartThreads) void k_start(uint64_t *dst, const ui
 
 // ---- counting pass ---------------------------------------------------------
 
-// The pairs' bits for the frontier of node type nz[blockIdx.y]: a wavefront per
+// The pairs' bits for the frontiers of node types nz[blockIdx.y], ...: a wavefront per
 // 64 frontier vertices loads their mask rows (one read of each row, where the
 // pairs of every edge type would each read a word of it) and turns two words of
 // them into 64 ballots, one per edge type, which the lanes write.  One step past
@@ -143,39 +143,41 @@ __global__ __launch_bounds__(kStartThreads) void k_start(uint64_t *dst, const ui
 // instead of 1148.  A graph without a mask (fewer than kNzMaskMinEtypes edge
 // types into every node type) keeps every pair: most are non-empty there.
 __global__ __launch_bounds__(256) void k_pair_bits(HopView hv, const NzType *nz,
-                                                   const int32_t *nz_et, int32_t n_etypes,
+                                                   int32_t n_nz, const int32_t *nz_et,
                                                    int64_t n_words, PairArrays pa) {
-  const NzType N = nz[blockIdx.y];
-  const int64_t n = hv.nF[N.type];
-  const int64_t *front = hv.frontier[N.type];
   const int lane = lane_id();
   const int64_t waves = int64_t(gridDim.x) * (256 / kWave);
-  for (int64_t c = int64_t(blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
-       c * kWave < n + kWave; c += waves) {
-    const int64_t i = c * kWave + lane;
-    const int64_t v = i < n ? front[i] : -1;
-    // (an out-of-range seed has been flagged already: it has no active pair)
-    const bool ok = v >= 0 && v < N.num_nodes;
-    for (int32_t q = 0; q * 32 < N.n_in; q += 2) {
-      uint32_t m0 = 0, m1 = 0;
-      if (ok) {
-        m0 = N.mask ? N.mask[v * N.words + q] : ~0u;
-        m1 = !N.mask ? ~0u : (q + 1 < N.words ? N.mask[v * N.words + q + 1] : 0);
-      }
-      uint64_t mine = 0;
+  for (int32_t y = blockIdx.y; y < n_nz; y += gridDim.y) {
+    const NzType N = nz[y];
+    const int64_t n = hv.nF[N.type];
+    const int64_t *front = hv.frontier[N.type];
+    for (int64_t c = int64_t(blockIdx.x) * (256 / kWave) + threadIdx.x / kWave;
+         c * kWave < n + kWave; c += waves) {
+      const int64_t i = c * kWave + lane;
+      const int64_t v = i < n ? front[i] : -1;
+      // (an out-of-range seed has been flagged already: it has no active pair)
+      const bool ok = v >= 0 && v < N.num_nodes;
+      for (int32_t q = 0; q * 32 < N.n_in; q += 2) {
+        uint32_t m0 = 0, m1 = 0;
+        if (ok) {
+          m0 = N.mask ? N.mask[v * N.words + q] : ~0u;
+          m1 = !N.mask ? ~0u : (q + 1 < N.words ? N.mask[v * N.words + q + 1] : 0);
+        }
+        uint64_t mine = 0;
 #pragma unroll
-      for (int k = 0; k < 32; ++k) {
-        const uint64_t b0 = __ballot((m0 >> k) & 1u), b1 = __ballot((m1 >> k) & 1u);
-        if (lane == k) mine = b0;
-        if (lane == k + 32) mine = b1;
-      }
-      const int32_t s = q * 32 + lane;
-      if (s < N.n_in) {
-        const int e = nz_et[N.first + s];
-        const int64_t x = pair_word(hv.pair_base[e], e, c * kWave);
-        if (x < pair_word(hv.pair_base[e + 1], e + 1, 0) && x < n_words) {
-          pa.bits[x] = mine;
-          pa.word_et[x] = e;
+        for (int k = 0; k < 32; ++k) {
+          const uint64_t b0 = __ballot((m0 >> k) & 1u), b1 = __ballot((m1 >> k) & 1u);
+          if (lane == k) mine = b0;
+          if (lane == k + 32) mine = b1;
+        }
+        const int32_t s = q * 32 + lane;
+        if (s < N.n_in) {
+          const int e = nz_et[N.first + s];
+          const int64_t x = pair_word(hv.pair_base[e], e, c * kWave);
+          if (x < pair_word(hv.pair_base[e + 1], e + 1, 0) && x < n_words) {
+            pa.bits[x] = mine;
+            pa.word_et[x] = e;
+          }
         }
       }
     }
@@ -1575,8 +1577,9 @@ hipError_t launch_pair_list(HopView hv, const NzType *nz, const int32_t *nz_et, 
                             int32_t n_etypes, int64_t max_front, int64_t n_items, PairArrays pa,
                             Lookback lb, uint32_t epoch, uint64_t ticket_base, int64_t *small,
                             hipStream_t stream, StageEv ev) {
-  launch_k(k_pair_bits, dim3(grid_for(max_front + kWave, 256, 4096), unsigned(n_nz)), dim3(256), 0,
-           stream, ev.start, nullptr, hv, nz, nz_et, n_etypes, pair_words(n_items, n_etypes), pa);
+  const PairBitsGrid grid = pair_bits_grid(max_front, n_nz);
+  launch_k(k_pair_bits, dim3(grid.x, grid.y), dim3(256), 0, stream, ev.start, nullptr, hv, nz,
+           n_nz, nz_et, pair_words(n_items, n_etypes), pa);
   launch_k(k_pair_list, dim3(unsigned(pair_list_tiles(n_items, n_etypes))), dim3(kTileThreads), 0,
            stream, nullptr, ev.stop, hv, n_etypes, n_items, pa, lb, epoch, ticket_base, small);
   return hipGetLastError();

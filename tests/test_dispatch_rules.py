@@ -68,3 +68,17 @@ def test_active_pairs_of_sparse_masks_only(evaluate):
     assert first(0.5, 1) is None and first(1.0, 7) is None
     assert 1 << 18 < first(0.03, 1) <= first(0.03, 7) <= 1 << 20
     assert first(0.03, 2) <= first(0.2, 2) <= first(0.3, 2) <= 1 << 21
+
+
+def test_pair_bits_grid(evaluate):
+    """The pass over the node types of every copy of a bundle (here up to 32 of more
+    than 2048 types) launches a grid that the device takes, with few idle blocks, and
+    enough of them for one type's frontier."""
+    cases = [(f, t) for t in (1, 4, 1024, 1025, 67_200, 1_000_000)
+             for f in (0, 1, 193, 100_000, 1 << 31)]
+    got = evaluate([f"pair_bits_grid({f}, {t}).{c}" for f, t in cases for c in "xy"])
+    for (front, types), x, y in zip(cases, got[::2], got[1::2]):
+        assert 1 <= y <= min(types, 65_535) and 1 <= x <= 4096 and x * y <= 1 << 16
+        assert y == types or types > 1024
+        if types <= 4:
+            assert x == min(4096, (front + 64 + 255) // 256)

@@ -176,3 +176,25 @@ def test_edge_seeds_with_exclusion(olib, copies):
     for b in range(copies):
         diffs = compare_edges(refs[b], edge_result_dict(g, bl[b]), 1, R, 2)
         assert not diffs, f"batch {b}: " + "\n".join(diffs[:10])
+
+
+def test_many_node_types(olib):
+    """More node types with edges into them, over the copies of a bundle, than a row of
+    the grid that makes their pairs' bits: one of them with a mask and most of the pairs."""
+    rng = np.random.default_rng(12)
+    T, R, copies = 60, 40, 20
+    nn = [4000] + [30] * (T - 1)
+    ets = [(int(rng.integers(0, T)), 0) for _ in range(R)]
+    ets += [(int(rng.integers(0, T)), t) for t in range(1, T)]
+    ets = [(s, d, *sparse_type(rng, nn[d], nn[s], 0.05 if d == 0 else 0.5)) for s, d in ets]
+    n_et = len(ets)
+    g = gpu_graph(nn, ets, [None] * T)
+    host = oracle.HostGraph([(n, None) for n in nn], ets, lib=olib, check=False)
+    batches = [[rng.permutation(nn[0])[:900 + b]] + [rng.permutation(30)[:t % 4]
+               for t in range(1, T)] for b in range(copies)]
+    assert copies * T > 1024 and rule(nn, ets)([sizes(s) for s in batches])
+    fan = [[2] * n_et]
+    bl = g.sample_bundle([gpu_seeds(s) for s in batches], fan, list(range(copies)), gather=[])
+    for b in (0, 1, 11, 17, 19):
+        diffs = compare(host.sample_blocks(batches[b], fan, b), result_dict(g, bl[b]), T, n_et, 1)
+        assert not diffs, f"batch {b}: " + "\n".join(diffs[:10])
