@@ -603,15 +603,20 @@ __device__ __forceinline__ uint32_t word_of(const U32x4 &r, int w) {
 
 // Keys are uniform, so about deg * tau / 2^bits of them fall below tau; tau is
 // set for K + 4 sqrt(K) + 16 expected candidates.  A pure function of
-// (K, deg, bits), so every chunk of a hub uses the same value.  In single
-// precision: it only decides how many candidates are ranked, and in double it was
-// 100 of a hub run's first instructions (sampler of the billion-edge share's two
+// (K, deg, bits), so every chunk of a hub uses the same value, and the launch that
+// selects from the hub's list too, which concludes from the list's length where the
+// K-th key lies.  They compute it in several places: each operation is spelled out and
+// none may be contracted or reordered, so that all of them get the same bits.  In
+// single precision: it only decides how many candidates are ranked, and in double it
+// was 100 of a hub run's first instructions (sampler of the billion-edge share's two
 // hub hops 165 + 197 us, 161 + 194 in single).
 __device__ __forceinline__ uint64_t cand_threshold(int64_t K, int64_t deg,
                                                    uint64_t key_space) {
+#pragma clang fp contract(off) reassociate(off)
   const float k = float(uint32_t(K));  // 0 < K < deg < 2^32
-  const float t = (k + 4.0f * __builtin_amdgcn_sqrtf(k) + 16.0f) *
-                  __builtin_amdgcn_rcpf(float(uint32_t(deg))) * float(key_space);
+  const float cand = __builtin_fmaf(4.0f, __builtin_amdgcn_sqrtf(k), k) + 16.0f;
+  const float share = cand * __builtin_amdgcn_rcpf(float(uint32_t(deg)));
+  const float t = share * float(key_space);
   // (key_space is a power of two of at most 2^32)
   return t < float(key_space) ? uint64_t(uint32_t(t)) + 1 : key_space;
 }

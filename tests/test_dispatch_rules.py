@@ -1,6 +1,7 @@
 """The rules that choose a call's kernels by its sizes, and the sizes that they rest
 on: the expressions of the internal header, compiled and evaluated on the CPU."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -82,3 +83,22 @@ def test_pair_bits_grid(evaluate):
         assert y == types or types > 1024
         if types <= 4:
             assert x == min(4096, (front + 64 + 255) // 256)
+
+
+def test_candidate_threshold_has_one_value(tmp_path):
+    """The sampler computes a hub's candidate threshold in several places, which must
+    agree to the bit: the compiler may contract or reorder none of its operations (a
+    multiply and an add fused in one place and not in another would differ)."""
+    from paper_2112_15345_amd import build
+    try:
+        hipcc = build.hipcc()
+    except RuntimeError:
+        pytest.skip("hipcc not available")
+    out = str(tmp_path / "sample.ll")
+    cmd = [hipcc, "-x", "hip", *build.COMMON, "--offload-device-only", "-S", "-emit-llvm",
+           os.path.join(build.CSRC, "hg_sample.hip"), "-o", out]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+    ops = re.findall(r"= (f(?:add|sub|mul|div)\b[^%]*)float", open(out).read())
+    assert ops  # its operations are there
+    assert not [x for x in ops if x.split()[1:]], "arithmetic with fast-math flags"
