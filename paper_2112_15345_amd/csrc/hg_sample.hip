@@ -238,7 +238,10 @@ constexpr uint32_t kPairWave = 1u << 30, kPairHub = 1u << 31, kPairChunks = kPai
 
 // Per edge type, what the counting pass reads for every pair; staged in
 // (dynamic) LDS, 36 bytes per edge type, when the graph has at most
-// kCountMaxEtypes edge types (a bundle's virtual graph counts each copy).
+// kCountMaxEtypes edge types (a bundle's virtual graph counts each copy): with the
+// striped pass's 16 KiB that is half of a CU's LDS, and its registers leave no more
+// than two blocks a CU either (1728 edge types, 2^18 pairs: 414 us a call, 440 with
+// the table in memory and no stripes).
 constexpr int kCountMaxEtypes = 1800;
 struct CountTable {
   int64_t *pbase;  // [n + 1]
@@ -257,7 +260,7 @@ struct CountTable {
     fanout = reinterpret_cast<int32_t *>(n_dst + n);
   }
 };
-static_assert(CountTable::bytes(kCountMaxEtypes) <= 64 * 1024, "the table fits 64 KiB of LDS");
+constexpr size_t kCuLds = 160 * 1024;
 
 template <bool kStaged>
 struct CountView {
@@ -306,6 +309,10 @@ __global__ __launch_bounds__(kTileThreads) void k_count_scan(
   constexpr int64_t kPerTile = int64_t(kTileThreads) * kPairItems;
   // large tiles of pairs are read and written in stripes (below)
   constexpr bool kStriped = kPairItems == kPairItemsLarge && !kActive;
+  constexpr size_t kOwnLds =
+      sizeof(int64_t) * (16 + (kStriped ? kPerTile : 1) + kTileThreads / kWave);
+  static_assert(!kStaged || kOwnLds + CountTable::bytes(kCountMaxEtypes) <= kCuLds / 2,
+                "two blocks fit a CU with the largest table");
   int64_t n_tiles = gridDim.x;
   if (kActive) {
     n_tiles = min(n_tiles, small[kSlotActive] / kPerTile + 1);  // items 0 .. active

@@ -85,20 +85,42 @@ def test_pair_bits_grid(evaluate):
             assert x == min(4096, (front + 64 + 255) // 256)
 
 
-def test_candidate_threshold_has_one_value(tmp_path):
-    """The sampler computes a hub's candidate threshold in several places, which must
-    agree to the bit: the compiler may contract or reorder none of its operations (a
-    multiply and an add fused in one place and not in another would differ)."""
+@pytest.fixture(scope="module")
+def compile_sampler(tmp_path_factory):
+    """compile_sampler(*options) -> the sampler's device code as the compiler's text."""
     from paper_2112_15345_amd import build
     try:
         hipcc = build.hipcc()
     except RuntimeError:
         pytest.skip("hipcc not available")
-    out = str(tmp_path / "sample.ll")
-    cmd = [hipcc, "-x", "hip", *build.COMMON, "--offload-device-only", "-S", "-emit-llvm",
-           os.path.join(build.CSRC, "hg_sample.hip"), "-o", out]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr
-    ops = re.findall(r"= (f(?:add|sub|mul|div)\b[^%]*)float", open(out).read())
+
+    def run(*options):
+        out = str(tmp_path_factory.mktemp("sampler") / "sample.txt")
+        cmd = [hipcc, "-x", "hip", *build.COMMON, "--offload-device-only", "-S", *options,
+               os.path.join(build.CSRC, "hg_sample.hip"), "-o", out]
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        assert res.returncode == 0, res.stderr
+        return open(out).read()
+
+    return run
+
+
+def test_candidate_threshold_has_one_value(compile_sampler):
+    """The sampler computes a hub's candidate threshold in several places, which must
+    agree to the bit: the compiler may contract or reorder none of its operations (a
+    multiply and an add fused in one place and not in another would differ)."""
+    ops = re.findall(r"= (f(?:add|sub|mul|div)\b[^%]*)float", compile_sampler("-emit-llvm"))
     assert ops  # its operations are there
     assert not [x for x in ops if x.split()[1:]], "arithmetic with fast-math flags"
+
+
+def test_counting_pass_leaves_room_for_two_blocks(compile_sampler):
+    """Every variant of the counting pass, as built, and the largest table of edge
+    types that it is launched with take at most half of a CU's 160 KiB of LDS."""
+    code = compile_sampler()
+    limit = int(re.search(r"kCountMaxEtypes = (\d+)", open(os.path.join(
+        ROOT, "paper_2112_15345_amd", "csrc", "hg_sample.hip")).read()).group(1))
+    own = [int(n) for n in re.findall(
+        r"\.amdhsa_kernel \S*k_count_scan\S*\n\s*\.amdhsa_group_segment_fixed_size (\d+)", code)]
+    assert len(own) == 6 and max(own) >= 16 * 1024  # the striped ones among them
+    assert max(own) + 36 * limit + 8 <= 160 * 1024 // 2

@@ -12,7 +12,7 @@ import oracle
 import paper_2112_15345_amd as hg
 import pins
 import workloads as W
-from gpu_harness import many_relations, compare, gpu_graph, gpu_seeds, result_dict
+from gpu_harness import many_relations, compare, csc, gpu_graph, gpu_seeds, result_dict
 
 pytestmark = pytest.mark.gpu
 
@@ -568,3 +568,30 @@ def test_large_counting_pass(olib, n):
                                check=False).sample_blocks(seeds, fan, n)
         diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(seeds), fan, n)), 2, 5, 1)
         assert not diffs, f"{fan}: " + "\n".join(diffs[:10])
+
+
+@pytest.mark.parametrize("copies", [18, 19, 25, 26])
+def test_large_counting_pass_of_many_edge_types(olib, copies):
+    """A bundle's copies make 1296, 1368, 1800 (the most whose table is held in LDS,
+    81 KB with the stripes) and 1872 edge types, none with a mask, at 262144 pair slots
+    and more; edge types of few pairs, some of none."""
+    rng = np.random.default_rng(copies)
+    T = 8
+    nn = [9000, 800, 3000, 2500, 700, 3000, 2500, 40]
+    ets = [(int(rng.integers(0, T)), d) for d in range(T) for _ in range(9)]
+    ets = [(s, d, *csc(rng, rng.choice([0, 1, 3, 20, 60], size=nn[d], p=[.4, .3, .2, .08, .02]),
+                       nn[s])) for s, d in ets]
+    g = gpu_graph(nn, ets, [None] * T)
+    host = oracle.HostGraph([(n, None) for n in nn], ets, lib=olib, check=False)
+    per = 262_144 // (9 * copies) + 40
+    batches = []
+    for b in range(copies):
+        n = [per - 230 - 7 * b, 0, 90 + b, 60, 40 + 2 * b, 3, 37, b % 3]
+        n[0] += per + 60 - sum(n)
+        batches.append([rng.permutation(nn[t])[:n[t]] for t in range(T)])
+    assert sum(9 * s.size for x in batches for s in x) >= 262_144
+    fan = [[int(rng.choice([-1, 0, 2, 10])) for _ in ets]]
+    bl = g.sample_bundle([gpu_seeds(s) for s in batches], fan, list(range(copies)), gather=[])
+    for b in (0, 1, copies // 2, copies - 1):
+        diffs = compare(host.sample_blocks(batches[b], fan, b), result_dict(g, bl[b]), T, len(ets), 1)
+        assert not diffs, f"batch {b}: " + "\n".join(diffs[:10])
