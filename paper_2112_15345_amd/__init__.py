@@ -152,6 +152,13 @@ def _bind(lib: ctypes.CDLL) -> ctypes.CDLL:
     return lib
 
 
+def _accessors(lib: ctypes.CDLL):
+    """The addresses of the accessors that the native module calls, in its order."""
+    return [ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.hg_blocks_nodes, lib.hg_blocks_edges, lib.hg_blocks_input_nodes,
+        lib.hg_blocks_features, lib.hg_blocks_seeds, lib.hg_blocks_edge_pairs)]
+
+
 _lib = None
 _views = None
 
@@ -167,9 +174,7 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                   "`python -m paper_2112_15345_amd.build`")
         lib = _bind(ctypes.CDLL(path))
         from . import _hgviews
-        _hgviews.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-            lib.hg_blocks_nodes, lib.hg_blocks_edges, lib.hg_blocks_input_nodes,
-            lib.hg_blocks_features, lib.hg_blocks_seeds, lib.hg_blocks_edge_pairs)))
+        _hgviews.bind(*_accessors(lib))
         _views = _hgviews
         _lib = lib
     return _lib

@@ -15,6 +15,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+#include <memory>
 
 #include "hg.h"
 
@@ -29,6 +30,31 @@ struct Api {
   decltype(&hg_blocks_edge_pairs) edge_pairs = nullptr;
 } api;
 
+// A new reference, dropped unless it is released.
+struct Ref {
+  PyObject *o;
+  explicit Ref(PyObject *x) : o(x) {}
+  Ref(const Ref &) = delete;
+  ~Ref() { Py_XDECREF(o); }
+  PyObject *release() {
+    PyObject *x = o;
+    o = nullptr;
+    return x;
+  }
+};
+
+// A reference to owner that any thread may drop, and that is dropped once, by the
+// last copy.
+std::shared_ptr<PyObject> keep(PyObject *owner) {
+  Py_INCREF(owner);
+  return std::shared_ptr<PyObject>(owner, [](PyObject *o) {
+    if (!Py_IsInitialized()) return;  // the interpreter has ended
+    const PyGILState_STATE gil = PyGILState_Ensure();
+    Py_DECREF(o);
+    PyGILState_Release(gil);
+  });
+}
+
 // A tensor of this shape over the device memory at p, holding a reference to
 // owner; an empty one of its own when there is nothing to show.
 PyObject *wrap(const void *p, at::IntArrayRef shape, at::ScalarType type, PyObject *owner,
@@ -40,15 +66,9 @@ PyObject *wrap(const void *p, at::IntArrayRef shape, at::ScalarType type, PyObje
   if (n == 0 || !p) {
     t = at::empty(shape, at::TensorOptions().dtype(type).device(where));
   } else {
-    Py_INCREF(owner);
     t = at::from_blob(
         const_cast<void *>(p), shape,
-        [owner](void *) {
-          if (!Py_IsInitialized()) return;  // the interpreter has ended
-          const PyGILState_STATE gil = PyGILState_Ensure();
-          Py_DECREF(owner);
-          PyGILState_Release(gil);
-        },
+        [ref = keep(owner)](void *) mutable { ref.reset(); },
         at::TensorOptions().dtype(type).device(at::kCUDA));  // the device of p
     if (device >= 0 && t.device() != where) t = t.to(where);
   }
@@ -92,16 +112,11 @@ PyObject *guarded(F f) {
 
 // (a, b, ...) from new references, any of which may be NULL (an error).
 template <int N>
-PyObject *tuple(PyObject *(&x)[N]) {
-  bool ok = true;
-  for (PyObject *o : x) ok = ok && o;
-  PyObject *t = ok ? PyTuple_New(N) : nullptr;
-  for (int i = 0; i < N; ++i) {
-    if (t)
-      PyTuple_SET_ITEM(t, i, x[i]);
-    else
-      Py_XDECREF(x[i]);
-  }
+PyObject *tuple(Ref (&x)[N]) {
+  for (const Ref &r : x)
+    if (!r.o) return nullptr;
+  PyObject *t = PyTuple_New(N);
+  for (int i = 0; t && i < N; ++i) PyTuple_SET_ITEM(t, i, x[i].release());
   return t;
 }
 
@@ -114,7 +129,8 @@ PyObject *nodes(PyObject *, PyObject *const *args, Py_ssize_t n) {
     const int64_t *p = nullptr;
     const hg_status st = api.nodes(blocks(v[0]), int32_t(v[1]), int32_t(v[2]), &nd, &ns, &p);
     if (st != HG_OK) return PyLong_FromLong(st);
-    PyObject *x[2] = {PyLong_FromLongLong(nd), wrap(p, {p ? ns : 0}, at::kLong, args[4], v[3])};
+    Ref x[2] = {Ref(PyLong_FromLongLong(nd)),
+                Ref(wrap(p, {p ? ns : 0}, at::kLong, args[4], v[3]))};
     return tuple(x);
   });
 }
@@ -134,10 +150,10 @@ PyObject *edges(PyObject *, PyObject *const *args, Py_ssize_t n) {
     if (st != HG_OK) return PyLong_FromLong(st);
     PyObject *const owner = args[5];
     // (no indptr: an empty array, as for every absent array)
-    PyObject *x[4] = {wrap(ip, {ip ? nd + 1 : 0}, at::kLong, owner, v[4]),
-                      wrap(sl, {sl ? ne : 0}, at::kInt, owner, v[4]),
-                      wrap(dl, {dl ? ne : 0}, at::kInt, owner, v[4]),
-                      wrap(eid, {eid ? ne : 0}, at::kLong, owner, v[4])};
+    Ref x[4] = {Ref(wrap(ip, {ip ? nd + 1 : 0}, at::kLong, owner, v[4])),
+                Ref(wrap(sl, {sl ? ne : 0}, at::kInt, owner, v[4])),
+                Ref(wrap(dl, {dl ? ne : 0}, at::kInt, owner, v[4])),
+                Ref(wrap(eid, {eid ? ne : 0}, at::kLong, owner, v[4]))};
     return tuple(x);
   });
 }
@@ -188,9 +204,9 @@ PyObject *edge_pairs(PyObject *, PyObject *const *args, Py_ssize_t n) {
     const int32_t *ps = nullptr, *pd = nullptr, *pn = nullptr;
     const hg_status st = api.edge_pairs(blocks(v[0]), int32_t(v[1]), &np, &ps, &pd, &nn, &pn);
     if (st != HG_OK) return PyLong_FromLong(st);
-    PyObject *x[3] = {wrap(ps, {ps ? np : 0}, at::kInt, args[3], v[2]),
-                      wrap(pd, {pd ? np : 0}, at::kInt, args[3], v[2]),
-                      wrap(pn, {pn ? nn : 0}, at::kInt, args[3], v[2])};
+    Ref x[3] = {Ref(wrap(ps, {ps ? np : 0}, at::kInt, args[3], v[2])),
+                Ref(wrap(pd, {pd ? np : 0}, at::kInt, args[3], v[2])),
+                Ref(wrap(pn, {pn ? nn : 0}, at::kInt, args[3], v[2]))};
     return tuple(x);
   });
 }
