@@ -4,7 +4,8 @@ generation on MI355X (DistDGLv2, arXiv 2112.15345, Sec. 3.2 and Sec. 4.2).
 Argument marshalling only: every step of the path runs in the library's gfx950
 kernels.  PyTorch supplies device memory (the graph, feature tables, outputs)
 and the stream (the current torch stream).  The tensors over a mini-batch's
-arrays are made by the native module _hgviews.so.  Import fails loudly if either
+arrays are made by the native module _hgviews, built for one version of Python
+and PyTorch.  Import fails loudly if either
 is not built; there is no CPU path.
 
     g = Graph(ntypes=[(num_nodes, feat_or_None), ...],
@@ -19,13 +20,17 @@ from __future__ import annotations
 
 import collections
 import ctypes
+import importlib.util
 import os
+import sys
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libhg.so")
-VIEWS_PATH = os.path.join(_HERE, "_hgviews.so")
+# compiled against PyTorch's C++ headers: the name says which PyTorch's
+VIEWS_PATH = os.path.join(
+    _HERE, f"_hgviews.{sys.implementation.cache_tag}.torch-{torch.__version__}.so")
 
 HG_OK, HG_EINVAL, HG_ENOMEM, HG_EDEVICE, HG_EUNSUPPORTED = 0, -1, -2, -3, -4
 HG_DT_NONE, HG_DT_F32, HG_DT_F16, HG_DT_BF16 = 0, 1, 2, 3
@@ -170,12 +175,15 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     if _lib is None:
         for need in (path, VIEWS_PATH):
             if not os.path.exists(need):
-                raise ImportError(f"{need} is missing: build it with "
+                raise ImportError(f"{need} is missing: build it (again for another "
+                                  "Python or PyTorch) with "
                                   "`python -m paper_2112_15345_amd.build`")
         lib = _bind(ctypes.CDLL(path))
-        from . import _hgviews
-        _hgviews.bind(*_accessors(lib))
-        _views = _hgviews
+        spec = importlib.util.spec_from_file_location(f"{__name__}._hgviews", VIEWS_PATH)
+        views = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(views)
+        views.bind(*_accessors(lib))
+        _views = views
         _lib = lib
     return _lib
 

@@ -1,9 +1,9 @@
 """Builds libhg.so (the gfx950 kernels and the C ABI of include/hg.h) and the
-Python binding's native module _hgviews.so in-tree.
+Python binding's native module _hgviews in-tree.
 
 Every source of the library is compiled with hipcc for gfx950 only, then linked
-into one shared library next to this file; _hgviews.so is host code against the
-installed PyTorch.  `python -m paper_2112_15345_amd.build` runs it.
+into one shared library next to this file; _hgviews is host code against the
+installed PyTorch, whose version its file name has.  `python -m paper_2112_15345_amd.build` runs it.
 """
 from __future__ import annotations
 
@@ -19,14 +19,13 @@ REPO = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(REPO, "include")
 LIB = os.path.join(HERE, "libhg.so")
-VIEWS = os.path.join(HERE, "_hgviews.so")
 OBJDIR = os.path.join(REPO, "_build", "hg")
 
 SOURCES = ["hg_sample.hip", "hg_compact.hip", "hg_gather.hip", "hg_edges.hip",
            "hg_layers.hip", "hg_runtime.cpp", "hg_pipeline.cpp"]
 ARCH = "gfx950"
 
-# Packed FP32 instructions stay off (the kernels do no float math; the flag
+# Packed FP32 instructions stay off (the kernels do hardly any float math; the flag
 # keeps the compiler from forming them anywhere).
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -52,11 +51,12 @@ def _compile(src: str, verbose: bool) -> str:
 
 
 def _build_views(verbose: bool) -> None:
-    """Compiles and links _hgviews.so (host code only)."""
+    """Compiles and links _hgviews (host code only)."""
     import torch
+    from . import VIEWS_PATH
     import torch.utils.cpp_extension as ext
     libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
-    tmp = VIEWS + ".tmp"
+    tmp = VIEWS_PATH + ".tmp"
     inc = [x for p in (*ext.include_paths(), sysconfig.get_paths()["include"], "/opt/rocm/include")
            for x in ("-isystem", p)]
     cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
@@ -69,12 +69,12 @@ def _build_views(verbose: bool) -> None:
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"g++ failed on hg_views.cpp:\n{res.stdout}\n{res.stderr}")
-    os.replace(tmp, VIEWS)
+    os.replace(tmp, VIEWS_PATH)
 
 
 def build(verbose: bool = False) -> str:
     """Compiles every source for gfx950 and links libhg.so (returns its path), and
-    builds _hgviews.so."""
+    builds _hgviews."""
     os.makedirs(OBJDIR, exist_ok=True)
     with concurrent.futures.ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as ex:
         views = ex.submit(_build_views, verbose)

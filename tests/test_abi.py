@@ -3,6 +3,8 @@
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -94,3 +96,17 @@ def test_create_descriptor_checks_without_device(lib):
     assert create([nt()], [et(nnz=1 << 32)]) == hg.HG_EUNSUPPORTED
     assert b"below 2^32" in hg._lib.hg_last_error()
     assert out.value is None
+
+
+def test_another_pytorch_needs_another_build():
+    """The binding's native module is compiled against PyTorch's C++ headers: under a
+    PyTorch that it was not built for, loading stops with what to do, before any of its
+    code runs."""
+    code = ("import torch; torch.__version__ = '0.0.1+other'\n"
+            "import paper_2112_15345_amd as hg\n"
+            "try:\n    hg.load_library()\n"
+            "except ImportError as e:\n    print('ImportError', e)\n"
+            "else:\n    print('loaded')\n")
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert res.returncode == 0, res.stderr
+    assert res.stdout.startswith("ImportError") and "paper_2112_15345_amd.build" in res.stdout
