@@ -8,18 +8,20 @@
 // One hop, after the counting pass has numbered every in-edge of the frontier
 // (fanout -1: pair p's in-edges are positions off[p] .. off[p+1]-1); no
 // sampler runs, and the edges are read from the CSC where needed:
-//  1-3. k_lw_tile_pairs, k_lw_bin_* : the first pair of every 2048-position tile;
+//  1-4. k_lw_tile_pairs, k_lw_bin_* : the first pair of every 2048-position tile;
 //                    then the in-edges grouped into bins of 8192 sources, each
-//                    bin's importance summed in LDS and its candidates listed
-//                    with its prefix; k_lw_bin_draw draws among them.  Calls of
-//                    more than kMaxBins bins instead:
+//                    bin's importance summed in LDS (a large bin's by several
+//                    blocks) and its candidates listed with its prefix;
+//                    k_lw_bin_draw draws among them.  Hops of fewer than
+//                    kBinsFromEdges in-edges, and calls whose vertices make more
+//                    than kMaxBins bins, instead:
 //  1. k_lw_tile_pairs, k_lw_weights : the first pair of every 2048-position
 //                    tile; then the importance of every candidate (a source
 //                    not in the frontier, which is marked reached): sum of
 //                    floor(2^32 / deg(v)^2) over its edges into the frontier,
 //                    64-bit atomics (exact in any order), a block per tile of
-//                    positions whose etypes and pairs are staged in LDS (as in
-//                    the kept-edge passes);
+//                    positions whose etypes, and each position's pair, are in
+//                    LDS (as in the kept-edge passes);
 //  2. compaction   : (collect mode) the candidates of each type, ascending;
 //  3. k_lw_scan_*  : exclusive prefix of their importance per type
 //                    (reduce-then-scan over 512-candidate tiles);
@@ -59,10 +61,6 @@ unsigned grid_for(int64_t n, int threads, int64_t cap = 1 << 16) {
   if (b < 1) b = 1;
   if (b > cap) b = cap;
   return unsigned(b);
-}
-
-__device__ __forceinline__ bool in_frontier(const uint32_t *fbits, int64_t v) {
-  return (fbits[v >> 5] >> (v & 31)) & 1u;
 }
 
 // floor(2^32 / d^2) for d >= 1 (zero once d^2 > 2^32).  The correctly
@@ -160,7 +158,6 @@ __device__ __forceinline__ int tile_seg(const TileSegs &T, int s, int64_t j) {
 
 // What a position needs of its etype.
 struct SegView {
-  const uint32_t *fbits;
   void *per_seg;
   const int64_t *indices;
   uint8_t *reached;
@@ -176,10 +173,9 @@ __device__ __forceinline__ int seg_index(const LayerArgs &A, const TileSegs &T, 
 template <int kKind>
 __device__ __forceinline__ SegView seg_view(const LayerArgs &A, const TileSegs &T, int x) {
   if (T.n > 0)
-    return SegView{T.fbits[x], T.per_seg[x], T.indices[x], T.reached[x], T.pair_base[x]};
+    return SegView{T.per_seg[x], T.indices[x], T.reached[x], T.pair_base[x]};
   const EtypeStatic &E = A.es[x];
-  return SegView{A.ts[E.src_type].fbits,
-                 kKind == 0 ? static_cast<void *>(A.wt[E.src_type]) : static_cast<void *>(E.src_map),
+  return SegView{kKind == 0 ? static_cast<void *>(A.wt[E.src_type]) : static_cast<void *>(E.src_map),
                  E.indices, E.src_reached, A.hv.pair_base[x]};
 }
 
@@ -364,9 +360,11 @@ __global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
 // Grouped by bin first (count, scan, scatter: 4 bytes an in-edge), a bin's sums
 // live in LDS, its candidates come out in ascending ID with their prefix, and only
 // the bins are scanned: 170 us counting, 270 scattering, 200 summing and 20 for the
-// scans in place of 1.5 ms.  A call whose vertices make more than kMaxBins bins
-// (67M vertices) keeps the atomics: its in-edges are few next to its vertices, and
-// a block's counts of the bins would no longer fit in LDS beside its tables.
+// scans in place of 1.5 ms.  Two kinds of hops keep the atomics: those of fewer than
+// kBinsFromEdges in-edges, where the launches cost more than the atomics, and those of
+// a call whose vertices make more than kMaxBins bins (67M vertices), whose in-edges
+// are few next to its vertices and whose counts of the bins would no longer fit in a
+// block's LDS beside its tables.
 
 // Blocks of 256 threads take kBinTiles tiles of positions.
 constexpr int kBinTiles = 2;
@@ -1006,13 +1004,10 @@ hipError_t launch_lw_weights(const LayerArgs &A, hipStream_t stream) {
 hipError_t launch_lw_bins(const LayerArgs &A, hipStream_t stream) {
   const size_t lds = sizeof(uint32_t) * size_t(A.n_bins);
   const unsigned grid = unsigned((A.n_edge_tiles + kBinTiles - 1) / kBinTiles);
-  if (A.n_all > 0) {
-    hipLaunchKernelGGL(k_lw_tile_pairs, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);
-    hipLaunchKernelGGL(k_lw_bin_count, dim3(grid), dim3(256), lds, stream, A);
-  }
+  hipLaunchKernelGGL(k_lw_tile_pairs, dim3(grid_for(A.n_pairs, 256)), dim3(256), 0, stream, A);
+  hipLaunchKernelGGL(k_lw_bin_count, dim3(grid), dim3(256), lds, stream, A);
   hipLaunchKernelGGL(k_lw_bin_starts, dim3(1), dim3(1024), 0, stream, A);
-  if (A.n_all > 0)
-    hipLaunchKernelGGL(k_lw_bin_scatter, dim3(grid), dim3(256), lds, stream, A);
+  hipLaunchKernelGGL(k_lw_bin_scatter, dim3(grid), dim3(256), lds, stream, A);
   hipLaunchKernelGGL(k_lw_bin_parts, dim3(unsigned(most_bin_parts(A.n_all))), dim3(kBinThreads), 0,
                      stream, A);
   hipLaunchKernelGGL(k_lw_bin_sum, dim3(unsigned(A.n_bins)), dim3(kBinThreads), 0, stream, A);

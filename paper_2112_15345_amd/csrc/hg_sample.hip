@@ -230,7 +230,6 @@ __global__ __launch_bounds__(kTileThreads) void k_pair_list(HopView hv, int32_t 
   }
 }
 
-// Per pair: kept edges s, hub chunks, "one wavefront" flag, hub flag.
 // What the counting pass keeps of a pair until its outputs are written, next
 // to its kept count: its hub chunk count (a pair has fewer than 2^32 in-edges,
 // so fewer than 2^21 chunks) and whether it takes the wavefront or the hub role.
