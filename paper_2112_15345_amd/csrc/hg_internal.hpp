@@ -358,7 +358,9 @@ constexpr int64_t kBinPart = 32768;
 __host__ __device__ inline int64_t bin_parts(int64_t records) {  // 0: not in parts
   return records > kBinPart ? (records + kBinPart - 1) / kBinPart : 0;
 }
-inline int64_t most_large_bins(int64_t n) { return n / kBinPart + 1; }
+inline int64_t most_large_bins(int64_t n, int64_t n_bins) {
+  return n / kBinPart + 1 < n_bins ? n / kBinPart + 1 : n_bins;
+}
 inline int64_t most_bin_parts(int64_t n) { return 2 * (n / kBinPart) + 1; }
 // Hops of fewer in-edges use the atomics: a hop's binning is three launches more
 // (academic graph scaled by 0.1, 150 seeds, two hops: 369 us a call with bins, 299

@@ -1277,7 +1277,8 @@ hg_status SampleRun::layer_hop(int32_t h, const HopView &hv, const HopView &nv,
         (e = launch_fill_u32(A.bin_edges, A.n_bins, 0u, stream)) != hipSuccess)
       return fail_device(e, "fill");
     // the sums of the large bins, zero between hops
-    if (!ws->lw_sums.ensure(sizeof(uint64_t) * size_t(most_large_bins(S) * kBinVerts), stream))
+    if (!ws->lw_sums.ensure(sizeof(uint64_t) * size_t(most_large_bins(S, A.n_bins) * kBinVerts),
+                            stream))
       return fail(HG_ENOMEM, "hop %d: layer-wise scratch", h);
     A.big_sums = static_cast<unsigned long long *>(ws->lw_sums.p);
     if (ws->lw_sums.fresh &&

@@ -51,8 +51,11 @@ def test_large_bins_are_shared_by_blocks(evaluate):
     # bins that make the most of n in-edges: all just over a part
     for n_bins in (1, 3, 100):
         total = n_bins * (part + 1)
-        large, parts = evaluate([f"most_large_bins({total})", f"most_bin_parts({total})"])
-        assert large >= n_bins and parts >= 2 * n_bins
+        large, parts = evaluate([f"most_large_bins({total}, {n_bins})",
+                                 f"most_bin_parts({total})"])
+        assert large == n_bins and parts >= 2 * n_bins
+    # many in-edges from a type of few bins: no more sums than it has bins
+    assert evaluate([f"most_large_bins({(1 << 31) - 1}, {b})" for b in (2, 8192)]) == [2, 8192]
 
 
 def test_active_pairs_of_sparse_masks_only(evaluate):
