@@ -128,3 +128,22 @@ def frontier_in_edges(ets, ref, hop):
         v = gid[:n_dst]
         n += int((ip[v + 1] - ip[v]).sum())
     return n
+
+
+def active_rule(nn, ets):
+    """active(fronts): whether a hop whose frontiers (of every copy of a bundle) have
+    these sizes works on its active pairs, by the library's rule over the graph's own
+    masks."""
+    n_in = np.bincount([d for _, d, _, _ in ets], minlength=len(nn))
+    masked = n_in >= internal("kNzMaskMinEtypes")
+    mean = [sum(int((np.diff(ip) > 0).sum()) for _, d, ip, _ in ets if d == t) / nn[t]
+            if masked[t] else float(n_in[t]) for t in range(len(nn))]
+    words = max((int(k) + 31) // 32 for k, m in zip(n_in, masked) if m)
+    least = internal("kActiveFromPairs") + internal("kActivePerWord") * words
+
+    def active(fronts):
+        pairs = sum(int(n_in[t]) * f[t] for f in fronts for t in range(len(nn)))
+        n_active = int(sum(mean[t] * f[t] for f in fronts for t in range(len(nn))))
+        return pairs + 1 > least + n_active // 4 * 9
+
+    return active

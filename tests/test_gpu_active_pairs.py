@@ -7,7 +7,7 @@ import torch
 
 import oracle
 import pins
-from gpu_harness import (compare, compare_edges, csc, edge_result_dict, frontier_in_edges,
+from gpu_harness import (active_rule, compare, compare_edges, csc, edge_result_dict, frontier_in_edges,
                          gpu_graph, gpu_seeds, internal, result_dict)
 
 pytestmark = pytest.mark.gpu
@@ -36,25 +36,6 @@ def masked_graph(rng, R, nn, share, most=6):
     return ets
 
 
-def rule(nn, ets):
-    """active(fronts): whether a hop whose frontiers (of every copy of a bundle) have
-    these sizes works on its active pairs, by the library's rule over the graph's own
-    masks."""
-    n_in = np.bincount([d for _, d, _, _ in ets], minlength=len(nn))
-    masked = n_in >= internal("kNzMaskMinEtypes")
-    mean = [sum(int((np.diff(ip) > 0).sum()) for _, d, ip, _ in ets if d == t) / nn[t]
-            if masked[t] else float(n_in[t]) for t in range(len(nn))]
-    words = max((int(k) + 31) // 32 for k, m in zip(n_in, masked) if m)
-    least = internal("kActiveFromPairs") + internal("kActivePerWord") * words
-
-    def active(fronts):
-        pairs = sum(int(n_in[t]) * f[t] for f in fronts for t in range(len(nn)))
-        n_active = int(sum(mean[t] * f[t] for f in fronts for t in range(len(nn))))
-        return pairs + 1 > least + n_active // 4 * 9
-
-    return active
-
-
 def sizes(seeds):
     return [0 if s is None else s.size for s in seeds]
 
@@ -79,12 +60,12 @@ def test_frontier_edges(olib, R):
         n = (64 * (per * 2 // 3) + d0, 64 * (per // 3) + d1, n2)
         batches.append([rng.permutation(nn[t])[:n[t]] for t in range(3)])
     for b, s in enumerate(batches):
-        assert rule(nn, ets)([sizes(s)])
+        assert active_rule(nn, ets)([sizes(s)])
         ref = host.sample_blocks(s, fan, 5 + b)
         diffs = compare(ref, result_dict(g, g.sample_blocks(gpu_seeds(s), fan, 5 + b)), 3, n_et, 2)
         assert not diffs, f"seeds {sizes(s)}: " + "\n".join(diffs[:10])
     parts = [[x[:x.size // 3 + k] for x in s] for k, s in enumerate(batches)]
-    assert rule(nn, ets)([sizes(s) for s in parts])
+    assert active_rule(nn, ets)([sizes(s) for s in parts])
     bl = g.sample_bundle([gpu_seeds(s) for s in parts], fan, [5, 6, 7], gather=[])
     for b, s in enumerate(parts):
         diffs = compare(host.sample_blocks(s, fan, 5 + b), result_dict(g, bl[b]), 3, n_et, 2)
@@ -100,7 +81,7 @@ def test_rule_edges(olib, share):
     ets = [(0, 0, *sparse_type(rng, n, n, share, 4)) for _ in range(R)]
     g = gpu_graph([n], ets, [None])
     host = oracle.HostGraph([(n, None)], ets, lib=olib, check=False)
-    active = rule([n], ets)
+    active = active_rule([n], ets)
     first = next((m for m in range(1, n + 1) if active([[m]])), None)
     if share == 0.5:
         assert first is None
@@ -129,7 +110,7 @@ def test_layers(olib, most, copies):
     k = copies
     batches = [[rng.permutation(nn[0])[:12_000 // k + b], rng.permutation(nn[1])[:4000 // k - b],
                 rng.permutation(nn[2])[:65]] for b in range(k)]
-    assert rule(nn, ets)([sizes(s) for s in batches])
+    assert active_rule(nn, ets)([sizes(s) for s in batches])
     for draws in ([[-1, 70, 0], [9, 9, 9]], [[500, -1, -1]], [[0, 0, 3]]):
         H = len(draws)
         refs = [host.sample_layers(s, draws, 31 + b) for b, s in enumerate(batches)]
@@ -170,7 +151,7 @@ def test_edge_seeds_with_exclusion(olib, copies):
     fan = [[2] * R, [3] * R]
     refs = [host.sample_edge_blocks(tg, fan, 8 + b, n_neg=1, exclude=2, rev_etype=rev_et,
                                     rev_eid=rev_eid) for b, tg in enumerate(batches)]
-    assert rule([n], ets)([[r["seeds"][0].size] for r in refs])
+    assert active_rule([n], ets)([[r["seeds"][0].size] for r in refs])
     bl = g.sample_edge_bundle([dev(tg) for tg in batches], fan, [8 + b for b in range(copies)],
                               n_neg=1, exclude=2, rev_etype=rev_et, rev_eid=dev(rev_eid))
     for b in range(copies):
@@ -192,7 +173,7 @@ def test_many_node_types(olib):
     host = oracle.HostGraph([(n, None) for n in nn], ets, lib=olib, check=False)
     batches = [[rng.permutation(nn[0])[:900 + b]] + [rng.permutation(30)[:t % 4]
                for t in range(1, T)] for b in range(copies)]
-    assert copies * T > 1024 and rule(nn, ets)([sizes(s) for s in batches])
+    assert copies * T > 1024 and active_rule(nn, ets)([sizes(s) for s in batches])
     fan = [[2] * n_et]
     bl = g.sample_bundle([gpu_seeds(s) for s in batches], fan, list(range(copies)), gather=[])
     for b in (0, 1, 11, 17, 19):

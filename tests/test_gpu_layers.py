@@ -231,9 +231,8 @@ def sparse_relations(rng, R, n0=300, n1=80):
 
 @pytest.mark.parametrize("R", [6, 40, 70])
 def test_layer_many_relations(olib, R):
-    """Many sparse edge types: a tile of in-edges (2048 in the importance
-    kernel, 512 in the kept-edge scan) then spans more etypes than the
-    kernels' per-tile tables hold (32), and the etype of each edge is searched
+    """Many sparse edge types: a tile of 2048 in-edges then spans more etypes than
+    the kernels' per-tile tables hold (32), and the etype of each edge is searched
     for instead; with 6 a tile spans few.  Single calls and a bundle of 4
     against the oracle."""
     rng = np.random.default_rng(8800 + R)
@@ -304,9 +303,10 @@ def bins_graph(n, degs, rng, near):
 
 @pytest.mark.parametrize("n", [8191, 8192, 8193, 16384, 16385, 40_000])
 def test_layer_importance_bins(olib, n):
-    """The candidates' importance is summed a bin of 8192 vertices at a time: node
-    types that end on, before and after a bin and a bitmap tile (two bins), sources
-    at the bins' ends, candidates reached by several destinations."""
+    """Hops of few in-edges, whose importance is summed by atomics, on the graphs of
+    the bins' tests (test_layer_bins_of_large_hops): node types that end on, before
+    and after a bitmap tile and half of one, candidates there that are reached by
+    several destinations."""
     rng = np.random.default_rng(n)
     degs = [min(3000, n // 3), 500, 40, 3, 1, 1, 0, 700]
     ets = bins_graph(n, degs, rng, True)
@@ -321,7 +321,8 @@ def test_layer_importance_bins(olib, n):
 
 def test_layer_more_bins_than_fit(olib):
     """A bundle whose copies make more than 8192 bins sums the importance with
-    global atomics: each mini-batch equals its own call and two equal the oracle."""
+    global atomics whatever its in-edges: each mini-batch equals its own call and two
+    equal the oracle."""
     n, B = 2_120_000, 32  # 130 bitmap tiles of two bins each, per copy
     rng = np.random.default_rng(5)
     ets = bins_graph(n, [70_000, 3000, 3000, 40, 1, 5], rng, True)
@@ -329,6 +330,9 @@ def test_layer_more_bins_than_fit(olib):
     host = oracle.HostGraph([(n, None)], ets, lib=olib)
     sizes = [[300], [-1]]
     seeds = [[rng.permutation(6)[:1 + b % 6].astype(np.int64)] for b in range(B)]
+    deg = np.diff(ets[0][2])
+    assert sum(int(deg[s[0]].sum()) for s in seeds) >= internal("kBinsFromEdges")
+    assert B * -(-n // 16_384) * 2 > internal("kMaxBins")
     bl = g.sample_layers_bundle([gpu_seeds(s) for s in seeds], sizes, list(range(B)), gather=[])
     for b in range(B):
         got = result_dict(g, bl[b])
@@ -342,8 +346,9 @@ def test_layer_more_bins_than_fit(olib):
 
 @pytest.mark.parametrize("n,dests", [(8191, 400), (8193, 383), (16384, 400), (40_000, 360)])
 def test_layer_bins_of_large_hops(olib, n, dests):
-    """The bins' ends again, at hops of about 2^20 in-edges, from which on they are
-    used (8193 x 383 stays below in its first hop)."""
+    """The candidates' importance is summed a bin of 8192 vertices at a time from 2^20
+    in-edges on (8193 x 383 stays just below in its first hop): node types that end on,
+    before and after a bin and a bitmap tile (two bins), sources at the bins' ends."""
     rng = np.random.default_rng(n)
     ets = bins_graph(n, [min(3000, n // 3)] * dests + [40, 1, 0], rng, True)
     g = gpu_graph([n], ets, [None])

@@ -12,7 +12,7 @@ import oracle
 import paper_2112_15345_amd as hg
 import pins
 import workloads as W
-from gpu_harness import many_relations, compare, csc, gpu_graph, gpu_seeds, result_dict
+from gpu_harness import active_rule, many_relations, compare, csc, gpu_graph, gpu_seeds, result_dict
 
 pytestmark = pytest.mark.gpu
 
@@ -392,11 +392,11 @@ def test_reached_bit_mode(olib, pad):
 
 @pytest.mark.parametrize("R", [16, 31, 32, 33, 64, 65, 130])
 def test_mask_bits_of_the_frontier(olib, R):
-    """Node types with a non-empty mask: the frontier's mask rows are transposed
-    64 vertices and 64 edge types at a time.  Frontiers that end on, before and
-    after a wavefront's 64 vertices, edge types on, before and after a mask
-    word's 32; two such node types; single calls and a bundle, whose copies'
-    pairs start anywhere in a word."""
+    """Node types with a non-empty mask, on hops of so few pairs that they go through
+    every pair all the same (the larger ones, over the listed pairs, are in
+    test_gpu_active_pairs.py): most pairs are empty.  Frontiers that end on, before
+    and after a wavefront's 64 vertices, edge types on, before and after a mask
+    word's 32; two such node types; single calls and a bundle."""
     rng = np.random.default_rng(300 + R)
     nn = [400, 150]
     ets = []
@@ -430,9 +430,10 @@ def test_mask_bits_of_the_frontier(olib, R):
 
 @pytest.mark.parametrize("n0", [4095, 4096, 4161])
 def test_mask_bits_of_large_hops(olib, n0):
-    """Hops of more than 2^18 pairs work on the active pairs: one pair fewer, as
-    many and more, 64 edge types; then a hop whose frontier has grown."""
-    R, n = 64, 6000
+    """A call whose first hop goes through every pair (2^18 of them, one frontier
+    vertex fewer and some more) and whose second, the frontier having grown, works on
+    the active ones."""
+    R, n = 64, 12_000
     rng = np.random.default_rng(n0)
     ets = []
     for _e in range(R):
@@ -442,6 +443,8 @@ def test_mask_bits_of_large_hops(olib, n0):
                     np.concatenate(idx).astype(np.int64)))
     seeds = [rng.permutation(n)[:n0].astype(np.int64)]
     _, _, ref, got = run_both(olib, [n], ets, [None], seeds, [[3] * R, [2] * R], 9, 32)
+    active = active_rule([n], ets)
+    assert not active([[n0]]) and active([[int(ref["nodes"][(1, 0)][0])]])
     diffs = compare(ref, got, 1, R, 2)
     assert not diffs, "\n".join(diffs[:10])
 
