@@ -23,8 +23,10 @@ constexpr int kPairItemsSmall = 2;
 constexpr int kPairItemsLarge = 8;
 constexpr int64_t kPairLargeFrom = int64_t(kTileThreads) * kPairItemsSmall * 512;
 // Items per thread of a counting pass over active pairs, whose number the host
-// only bounds: between the two, since they are few or many.
-constexpr int kPairItemsActive = 4;
+// only bounds, so that one size has to do.  Single calls with 2, 4 and 8 of them:
+// 2^24 pairs, 25% active 1059, 859 and 769 us, 3% active 279, 262 and 249; 2^20
+// pairs, 3% 144, 146 and 142 (runs differ by 4%).
+constexpr int kPairItemsActive = 8;
 
 // Candidate capacity of one bottom-K selection (LDS entries per wavefront,
 // and per hub in the global candidate lists).
@@ -362,9 +364,10 @@ inline int64_t most_large_bins(int64_t n, int64_t n_bins) {
   return n / kBinPart + 1 < n_bins ? n / kBinPart + 1 : n_bins;
 }
 inline int64_t most_bin_parts(int64_t n) { return 2 * (n / kBinPart) + 1; }
-// Hops of fewer in-edges use the atomics: a hop's binning is three launches more
-// (academic graph scaled by 0.1, 150 seeds, two hops: 369 us a call with bins, 299
-// without; the whole graph, 1000 seeds, with the first hop's 414 and 388).
+// Hops of fewer in-edges use the atomics: a hop's binning is four launches more.
+// Single calls of one hop, us by bins and by atomics, from a type of 100k, 2M and 20M
+// vertices (12, 245 and 2442 bins): 2^19 in-edges 204 / 178, 190 / 196, 236 / 234;
+// 2^20 215 / 206, 208 / 230, 251 / 288; 2^21 233 / 260, 240 / 288, 294 / 382.
 constexpr int64_t kBinsFromEdges = int64_t(1) << 20;
 
 struct LayerArgs {
