@@ -15,7 +15,6 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
-#include <memory>
 
 #include "hg.h"
 
@@ -43,16 +42,12 @@ struct Ref {
   }
 };
 
-// A reference to owner that any thread may drop, and that is dropped once, by the
-// last copy.
-std::shared_ptr<PyObject> keep(PyObject *owner) {
-  Py_INCREF(owner);
-  return std::shared_ptr<PyObject>(owner, [](PyObject *o) {
-    if (!Py_IsInitialized()) return;  // the interpreter has ended
-    const PyGILState_STATE gil = PyGILState_Ensure();
-    Py_DECREF(o);
-    PyGILState_Release(gil);
-  });
+// Drops a reference; any thread may call it.
+void drop(void *owner) {
+  if (!Py_IsInitialized()) return;  // the interpreter has ended
+  const PyGILState_STATE gil = PyGILState_Ensure();
+  Py_DECREF(static_cast<PyObject *>(owner));
+  PyGILState_Release(gil);
 }
 
 // A tensor of this shape over the device memory at p, holding a reference to
@@ -66,10 +61,12 @@ PyObject *wrap(const void *p, at::IntArrayRef shape, at::ScalarType type, PyObje
   if (n == 0 || !p) {
     t = at::empty(shape, at::TensorOptions().dtype(type).device(where));
   } else {
-    t = at::from_blob(
-        const_cast<void *>(p), shape,
-        [ref = keep(owner)](void *) mutable { ref.reset(); },
-        at::TensorOptions().dtype(type).device(at::kCUDA));  // the device of p
+    // (the maker owns the reference from here on: a failed one drops it)
+    Py_INCREF(owner);
+    t = at::for_blob(const_cast<void *>(p), shape)
+            .context(owner, drop)
+            .options(at::TensorOptions().dtype(type).device(at::kCUDA))  // the device of p
+            .make_tensor();
     if (device >= 0 && t.device() != where) t = t.to(where);
   }
   return THPVariable_Wrap(std::move(t));
