@@ -65,14 +65,14 @@ DEFAULTS = {1: (2, 32, 320), 2: (3, 32, 384), 3: (3, 2, 40), 4: (3, 4, 96), 5: (
 # by a digest of the kernel and runtime sources, the workload and the bundle
 # size; any other run reports them as null.
 COUNTER_TRAFFIC = [
-    {"sources": "56dfd8cef016cf90", "workload": 3, "bundle": 2, "task": "vertex",
-     "sample_compact": 556421428, "k_sample_per_launch": 113970779,
-     "gather": 176148581, "gather_per_launch": 352297162,
-     "sample_compact_l2_hit_rate": 0.5455, "gather_l2_hit_rate": 0.3312},
-    {"sources": "56dfd8cef016cf90", "workload": 2, "bundle": 32, "task": "vertex",
-     "sample_compact": 76145261, "k_sample_per_launch": 553555963,
-     "gather": 249191661, "gather_per_launch": 7974133152,
-     "sample_compact_l2_hit_rate": 0.727, "gather_l2_hit_rate": 0.3327},
+    {"sources": "390d8c233e172f82", "workload": 3, "bundle": 2, "task": "vertex",
+     "sample_compact": 552950958, "k_sample_per_launch": 113594919,
+     "gather": 176155950, "gather_per_launch": 352311900,
+     "sample_compact_l2_hit_rate": 0.4725, "gather_l2_hit_rate": 0.3312},
+    {"sources": "390d8c233e172f82", "workload": 2, "bundle": 32, "task": "vertex",
+     "sample_compact": 72349798, "k_sample_per_launch": 546628999,
+     "gather": 249195860, "gather_per_launch": 7974267531,
+     "sample_compact_l2_hit_rate": 0.6377, "gather_l2_hit_rate": 0.3328},
 ]
 
 
