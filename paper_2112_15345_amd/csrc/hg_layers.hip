@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void k_lw_weights(LayerArgs A) {
 // (44M in-edges), and the candidates then have to be listed and scanned (0.27 ms).
 // Grouped by bin first (count, scan, scatter: 4 bytes an in-edge), a bin's sums
 // live in LDS, its candidates come out in ascending ID with their prefix, and only
-// the bins are scanned: 170 us counting, 270 scattering, 200 summing and 20 for the
+// the bins are scanned: 183 us counting, 302 scattering, 199 summing and 30 for the
 // scans in place of 1.5 ms.  Two kinds of hops keep the atomics: those of fewer than
 // kBinsFromEdges in-edges, where the launches cost more than the atomics, and those of
 // a call whose vertices make more than kMaxBins bins (67M vertices), whose in-edges
@@ -722,8 +722,8 @@ __global__ __launch_bounds__(256) void k_lw_bin_draw(LayerArgs A) {
 // counts only the set bits are looked at again, and the kept edges before any
 // position are tile_pre + keep_pre + a population count.  The flags pass is
 // bound by its reads (8 B a position and a frontier word); the academic graph's
-// second hop in bundles of 16 (44M in-edges, 0.3M kept) takes 243 us for the
-// flags, 18 for the scan and 43 for the kept edges, where a reduce and an apply
+// second hop in bundles of 16 (44M in-edges, 0.3M kept) takes 215 us for the
+// flags, 18 for the scan and 61 for the kept edges, where a reduce and an apply
 // pass that both read every source and wrote a prefix for every position took
 // 690 with their scan.  Ordering the blocks per XCD changed none of them.
 constexpr int kKeepWords = int(kEdgeTile / 64);  // words per tile

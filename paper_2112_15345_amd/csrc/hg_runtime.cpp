@@ -126,11 +126,20 @@ struct ETypeInfo {
 
 // A device buffer that grows (stream-ordered) and is reused across calls.
 // The library's stream-ordered pool on a device, for the scratch buffers and
-// the default output arrays.  Memory freed into it stays reserved (release
-// threshold at its maximum): a call that needs no more than earlier calls maps
-// no new memory, where a pool that trims at each synchronisation would map
-// gigabytes again (tens of ms) whenever a call outgrows what it kept.  The pool
-// lives until the process ends, since blocks handles may outlive their graph.
+// the default output arrays.  With its release threshold at the maximum, it keeps
+// at a synchronisation what was freed into it, where the default trims all of that
+// and a call that outgrows what is left maps gigabytes again (tens of ms).  The
+// runtime has another rule that no attribute turns off: a free that leaves the pool
+// more than about twice as much free as used memory gives most of the free back
+// (eight blocks of 256 MiB freed one after the other: reserved 2 GiB until the
+// sixth, then 0.8), and later calls map it again.  A caller that keeps the results
+// of a call or two, as a training loop does, stays clear of it; one that drops them
+// all while the GPU is idle pays for the mapping in its next pass (the billion-edge
+// share in a pipeline of 3 streams: 6.3 instead of 5.6 ms, and in about every other
+// process now and then 0.04 to 3 s, spent in hipMallocFromPoolAsync while the other
+// workers' HIP calls wait for it).  Such a caller can give hg_create an allocator of
+// its own.  The pool lives until the process ends, since blocks handles may outlive
+// their graph.
 hipMemPool_t library_pool(int device) {
   static std::mutex mu;
   static std::map<int, hipMemPool_t> pools;

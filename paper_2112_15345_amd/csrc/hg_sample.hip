@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kStartThreads) void k_start(uint64_t *dst, const ui
 // 442 us (each block stages its edge types, scans and looks back for 2048 pairs
 // that are nearly all empty) and the sampler 228 us, most of it block-CSC entries
 // written one pair per lane.  Bits, list, a counting pass over the active pairs
-// and the sampler take 22 + 30 + 35 + 75 us there, the whole call 565 us
+// and the sampler take 23 + 37 + 42 + 85 us there, the whole call 510 us
 // instead of 1148.  A graph without a mask (fewer than kNzMaskMinEtypes edge
 // types into every node type) keeps every pair: most are non-empty there.
 __global__ __launch_bounds__(256) void k_pair_bits(HopView hv, const NzType *nz,
